@@ -316,6 +316,14 @@ int carve(gm_ctx* c, unsigned char** base, const Piece* pieces, int k, int zero_
 
 int hip_rc(hipError_t e) { return e == hipSuccess ? GM_OK : GM_ERR_HIP; }
 
+// Whether work enqueued on st now goes into a graph (or may not be enqueued).
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
 double fact(int k) {
@@ -1440,7 +1448,15 @@ int gm_fes_hills(gm_ctx* c, const double* lo, const double* hi, const int32_t* n
   }
   if (total > kMaxFesBins) return GM_ERR_INVALID_ARG;
   const double scale = c->p.gamma > 1.0 ? c->p.gamma / (c->p.gamma - 1.0) : 1.0;
-  return hip_rc(launch_fes_hills(make_bias(c, nullptr, 0), lo, hi, nbins, scale, F_dev, c->stream));
+  const BiasArgs b = make_bias(c, nullptr, 0);
+  // The split sum wants a workspace; a captured stream (whose allocations
+  // would belong to the graph) or a full device takes the direct sum.
+  double* part = nullptr;
+  if (capturing(c->stream) || dalloc(c->stream, &part, fes_hills_scratch_doubles(b, nbins) * 8) != GM_OK)
+    return hip_rc(launch_fes_hills(b, lo, hi, nbins, scale, F_dev, c->stream));
+  const hipError_t e = launch_fes_hills_split(b, lo, hi, nbins, scale, F_dev, part, c->stream);
+  dfree(c->stream, part);
+  return hip_rc(e);
 }
 
 }  // extern "C"

@@ -272,10 +272,22 @@ __global__ __launch_bounds__(kSmallBlock) void k_zero_f64(double* p, int64_t n) 
     p[i] = 0.0;
 }
 
-// F = -scale V on the grid of bin centres, hills in index order.  Every
-// grid point of a workgroup reads every hill, so the hills pass through LDS
-// in tiles (one coalesced read of each hill per workgroup instead of one per
-// wave).
+// F = -scale V on the grid of bin centres.
+//
+// k_fes_hills is the direct sum, every hill in index order at every grid
+// point, hills through LDS in tiles (one coalesced read of each hill per
+// workgroup instead of one per wave).  It needs no workspace and serves the
+// calls that must not allocate (a captured stream); an FP64 exponential per
+// point and hill bounds it (256 x 256 points, 20,000 hills: 4.44 ms).
+//
+// Otherwise the hills are split over workgroups that leave partial sums in a
+// workspace, summed in a fixed order by k_fes_hills_sum:
+//  * 1-D, k_fes_hills_line: the direct sum over the workgroup's share of the
+//    hills.  A 1-D grid alone fills a few workgroups (486 points: 2).
+//  * 2-D, k_fes_hills_grid: a hill is a product over the dimensions, so
+//    V_ij = sum_k A_ki B_kj with A_ki = exp(-(g_i - c_k0)^2 / 2 sigma_0^2) and
+//    B_kj = h_k exp(-(g_j - c_k1)^2 / 2 sigma_1^2): nb0 + nb1 exponentials per
+//    hill instead of nb0 nb1, and a matrix product.
 constexpr int kHillTile = 512;
 
 __global__ __launch_bounds__(kSmallBlock) void k_fes_hills(BiasArgs b, double lo0, double lo1, double w0,
@@ -310,6 +322,146 @@ __global__ __launch_bounds__(kSmallBlock) void k_fes_hills(BiasArgs b, double lo
     }
   }
   if (i < nbins) F[i] = -scale * v;
+}
+
+// The share of K hills that split `part` of `parts` sums: [*k0, *k1), whole
+// multiples of `step` hills apart from the last.
+__device__ __forceinline__ void hill_share(int64_t K, int32_t part, int32_t parts, int32_t step, int64_t* k0,
+                                           int64_t* k1) {
+  const int64_t per = ((K + parts - 1) / parts + step - 1) / step * step;
+  *k0 = part * per < K ? part * per : K;
+  *k1 = *k0 + per < K ? *k0 + per : K;
+}
+
+// exp(-(g - c)^2 inv2s2) with the nearest periodic image of g - c (ip: 1/period,
+// 0 without).  x * ip picks another image than x / period only where the two
+// are equally near to rounding.
+__device__ __forceinline__ double hill_factor(double g, double c, double period, double ip, double inv2s2) {
+  double x = g - c;
+  if (period > 0.0) x -= period * rint(x * ip);
+  return exp(-(x * x * inv2s2));
+}
+
+__global__ __launch_bounds__(kSmallBlock) void k_fes_hills_line(BiasArgs b, double lo, double w, int32_t nb,
+                                                                double* __restrict__ part) {
+  __shared__ double tc[kHillTile], th[kHillTile];
+  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  const double g = lo + ((i < nb ? i : nb - 1) + 0.5) * w;
+  const double period = b.period[0], ip = period > 0.0 ? 1.0 / period : 0.0, inv = b.inv2s2[0];
+  int64_t k0, k1;
+  hill_share(*b.count, (int32_t)blockIdx.y, (int32_t)gridDim.y, 1, &k0, &k1);
+  double v = 0.0;
+  for (int64_t t0 = k0; t0 < k1; t0 += kHillTile) {
+    const int32_t n = (int32_t)(k1 - t0 < kHillTile ? k1 - t0 : kHillTile);
+    __syncthreads();
+    for (int32_t q = threadIdx.x; q < n; q += blockDim.x) {
+      tc[q] = b.centres[t0 + q];
+      th[q] = b.heights[t0 + q];
+    }
+    __syncthreads();
+    for (int32_t q = 0; q < n; q++) v += th[q] * hill_factor(g, tc[q], period, ip, inv);
+  }
+  if (i < nb) part[(int64_t)blockIdx.y * nb + i] = v;
+}
+
+// The 2-D product on the FP64 matrix instruction.  A workgroup of 8 waves
+// holds a kGridTile x kGridTile tile of the grid (each wave 64 x 32 points, 8
+// accumulators of 16 x 16) and walks its share of the hills kGridHills at a
+// time: the waves fill one half of the LDS tables with the next hills'
+// exponentials while the products of the current ones run, so the vector and
+// the matrix pipes overlap.  A 128-point tile halves the exponentials of a
+// 64-point one (each grid row's are computed once per tile column): with them
+// at 40-60 instructions each, 20,000 hills on 256 x 256 points are about as
+// much vector as matrix work.  Rows of the tables are padded by 16 doubles so
+// that the four hills a wave reads at once lie in different banks.
+// Measured at that size: 4.44 ms for the direct sum -> 94 us (the next hills'
+// centres loaded one fill ahead: 105 -> 94).
+constexpr int kGridTile = 128, kGridHills = 8, kGridThreads = 512, kGridRow = kGridTile + 16;
+using dbl4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
+
+__global__ __launch_bounds__(kGridThreads) void k_fes_hills_grid(BiasArgs b, double lo0, double lo1, double w0,
+                                                                 double w1, int32_t nb0, int32_t nb1,
+                                                                 double* __restrict__ part) {
+  __shared__ double tab[2][2][kGridHills][kGridRow];  // [half][dimension][hill][point]
+  const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int32_t tiles0 = (nb0 + kGridTile - 1) / kGridTile;
+  const int32_t r0 = (int32_t)(blockIdx.x % tiles0) * kGridTile, c0 = (int32_t)(blockIdx.x / tiles0) * kGridTile;
+  int64_t k0, k1;
+  hill_share(*b.count, (int32_t)blockIdx.y, (int32_t)gridDim.y, kGridHills, &k0, &k1);
+  // table entries of this thread: dimension d, point p of it (both fixed), hills hq, hq + 2, ...
+  const int d = (t >> 7) & 1, p = t & (kGridTile - 1), hq = t >> 8;
+  const double g = d ? lo1 + ((c0 + p) + 0.5) * w1 : lo0 + ((r0 + p) + 0.5) * w0;
+  const double period = b.period[d], ip = period > 0.0 ? 1.0 / period : 0.0, inv = b.inv2s2[d];
+  // the hills of the next fill are loaded one fill ahead
+  constexpr int kStep = kGridThreads / (2 * kGridTile), kMine = kGridHills / kStep;
+  double cen[kMine], hgt[kMine];
+  auto load = [&](int64_t k) {
+#pragma unroll
+    for (int q = 0; q < kMine; q++) {
+      const int64_t at = k + q * kStep + hq;
+      cen[q] = at < k1 ? b.centres[at * 2 + d] : 0.0;
+      hgt[q] = at < k1 ? (d ? b.heights[at] : 1.0) : 0.0;  // hills past the share add nothing
+    }
+  };
+  auto fill = [&](int half) {
+#pragma unroll
+    for (int q = 0; q < kMine; q++)
+      tab[half][d][q * kStep + hq][p] = hgt[q] * hill_factor(g, cen[q], period, ip, inv);
+  };
+  // wave -> 32 points of dimension 0 (columns of the accumulators, whose lanes
+  // are then consecutive in memory) x 64 of dimension 1 (rows)
+  const int w1p = (wave & 1) * 64, w0p = (wave >> 1) * 32, l16 = lane & 15, lk = lane >> 4;
+  dbl4 acc[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; i++)
+#pragma unroll
+    for (int j = 0; j < 2; j++) acc[i][j] = dbl4{0.0, 0.0, 0.0, 0.0};
+  load(k0);
+  fill(0);
+  load(k0 + kGridHills);
+  __syncthreads();
+  int half = 0;
+  for (int64_t k = k0; k < k1; k += kGridHills, half ^= 1) {
+    if (k + kGridHills < k1) {
+      fill(half ^ 1);
+      load(k + 2 * kGridHills);
+    }
+#pragma unroll
+    for (int q = 0; q < kGridHills; q += 4) {
+      double a[4], c[2];
+#pragma unroll
+      for (int i = 0; i < 4; i++) a[i] = tab[half][1][q + lk][w1p + 16 * i + l16];
+#pragma unroll
+      for (int j = 0; j < 2; j++) c[j] = tab[half][0][q + lk][w0p + 16 * j + l16];
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], c[j], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
+  }
+  double* out = part + (int64_t)blockIdx.y * nb0 * nb1;
+  // lane l of an accumulator holds column l % 16, rows l / 16 + 4 r
+#pragma unroll
+  for (int i = 0; i < 4; i++)
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int32_t x = r0 + w0p + 16 * j + l16, y = c0 + w1p + 16 * i + lk + 4 * r;
+        if (x < nb0 && y < nb1) out[x + (int64_t)y * nb0] = acc[i][j][r];
+      }
+}
+
+// F = -scale times the partial sums, added in the order of the splits.
+__global__ __launch_bounds__(kSmallBlock) void k_fes_hills_sum(const double* __restrict__ part, int32_t nbins,
+                                                               int32_t parts, double scale, double* __restrict__ F) {
+  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nbins) return;
+  double v = 0.0;
+#pragma unroll 8
+  for (int32_t p = 0; p < parts; p++) v += part[(int64_t)p * nbins + i];
+  F[i] = -scale * v;
 }
 
 unsigned grid_for(int64_t n, int block, int64_t cap) {
@@ -456,6 +608,48 @@ hipError_t launch_fes_hills(const BiasArgs& b, const double* lo, const double* h
   const double w0 = (hi[0] - lo[0]) / nb0, w1 = b.dims > 1 ? (hi[1] - lo[1]) / nb1 : 0.0;
   k_fes_hills<<<grid_for(nbins, kSmallBlock, 1 << 20), kSmallBlock, 0, st>>>(b, lo[0], b.dims > 1 ? lo[1] : 0.0, w0, w1,
                                                                              nb0, nbins, scale, F);
+  return hipGetLastError();
+}
+
+// Splits of the hills: enough workgroups for the chip (two per CU of 8 waves
+// on the 2-D product: 105 us with 512 workgroups, 117 with 256, 116 with 768;
+// four of 4 waves on a line), each with hills worth
+// splitting for (capacity: the count is on the device), and partial sums that
+// stay small beside the work.
+static int32_t fes_hills_parts(const BiasArgs& b, const int32_t* nb) {
+  int64_t blocks, want, most;
+  if (b.dims > 1) {
+    blocks = (int64_t)((nb[0] + kGridTile - 1) / kGridTile) * ((nb[1] + kGridTile - 1) / kGridTile);
+    want = (512 + blocks - 1) / blocks;
+    most = b.capacity / (4 * kGridHills);
+  } else {
+    blocks = (nb[0] + kSmallBlock - 1) / kSmallBlock;
+    want = (1024 + blocks - 1) / blocks;
+    most = b.capacity / 16;
+  }
+  const int64_t p = want < most ? want : most;
+  return (int32_t)(p < 1 ? 1 : p);
+}
+
+size_t fes_hills_scratch_doubles(const BiasArgs& b, const int32_t* nb) {
+  return (size_t)fes_hills_parts(b, nb) * nb[0] * (b.dims > 1 ? nb[1] : 1);
+}
+
+hipError_t launch_fes_hills_split(const BiasArgs& b, const double* lo, const double* hi, const int32_t* nb, double scale,
+                                  double* F, double* part, hipStream_t st) {
+  const int32_t parts = fes_hills_parts(b, nb);
+  const double w0 = (hi[0] - lo[0]) / nb[0];
+  int32_t nbins = nb[0];
+  if (b.dims > 1) {
+    const unsigned tiles = (unsigned)(((nb[0] + kGridTile - 1) / kGridTile) * ((nb[1] + kGridTile - 1) / kGridTile));
+    nbins *= nb[1];
+    k_fes_hills_grid<<<dim3(tiles, (unsigned)parts), kGridThreads, 0, st>>>(b, lo[0], lo[1], w0, (hi[1] - lo[1]) / nb[1],
+                                                                            nb[0], nb[1], part);
+  } else {
+    k_fes_hills_line<<<dim3(grid_for(nb[0], kSmallBlock, 1 << 20), (unsigned)parts), kSmallBlock, 0, st>>>(b, lo[0], w0,
+                                                                                                        nb[0], part);
+  }
+  k_fes_hills_sum<<<grid_for(nbins, kSmallBlock, 1 << 20), kSmallBlock, 0, st>>>(part, nbins, parts, scale, F);
   return hipGetLastError();
 }
 

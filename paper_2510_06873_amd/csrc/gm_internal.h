@@ -258,6 +258,11 @@ hipError_t launch_fes_reweight_noalloc(const double* s, const double* V, int64_t
                                        const double* hi, const int32_t* nb, double kBT, double* F, hipStream_t st);
 hipError_t launch_fes_hills(const BiasArgs& b, const double* lo, const double* hi, const int32_t* nb, double scale,
                             double* F, hipStream_t st);
+// The same with the hills split over workgroups, through a workspace of
+// fes_hills_scratch_doubles(b, nb) doubles.
+size_t fes_hills_scratch_doubles(const BiasArgs& b, const int32_t* nb);
+hipError_t launch_fes_hills_split(const BiasArgs& b, const double* lo, const double* hi, const int32_t* nb, double scale,
+                                  double* F, double* part, hipStream_t st);
 void allow_fes_lds();
 // Opt the staging kernels in to `bytes` of dynamic LDS.
 void allow_cv_lds(int bytes);
