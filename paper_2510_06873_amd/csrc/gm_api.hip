@@ -1418,8 +1418,22 @@ int gm_fes_reweight(const double* s_dev, const double* V_dev, int64_t T, int32_t
   if (total > kMaxFesBins) return GM_ERR_INVALID_ARG;
   static std::once_flag lds_once;
   std::call_once(lds_once, allow_fes_lds);
-  return hip_rc(launch_fes_reweight(s_dev, V_dev, T, dims, lo, hi, nbins, kBT, F_dev,
-                                    reinterpret_cast<hipStream_t>(hip_stream)));
+  // The scratch comes from the library's filed blocks (a pool allocation and
+  // free cost tens of microseconds of host time per call); while the stream is
+  // captured, from the stream-ordered allocator, whose memory the graph owns.
+  hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
+  const size_t bytes = fes_reweight_scratch_doubles(T, (int32_t)total) * 8;
+  const bool graph = capturing(st);
+  double* buf = nullptr;
+  if (graph ? hipMallocAsync(reinterpret_cast<void**>(&buf), bytes, st) != hipSuccess : dalloc(st, &buf, bytes) != GM_OK)
+    return GM_ERR_HIP;
+  const hipError_t e = launch_fes_reweight(s_dev, V_dev, T, dims, lo, hi, nbins, kBT, F_dev, buf, st);
+  hipError_t f = hipSuccess;
+  if (graph)
+    f = hipFreeAsync(buf, st);
+  else
+    dfree(st, buf);
+  return hip_rc(e != hipSuccess ? e : f);
 }
 
 int gm_fes_reweight_noalloc(const double* s_dev, const double* V_dev, int64_t T, int32_t dims, const double* lo,

@@ -21,6 +21,8 @@ namespace {
 
 constexpr int kSmallBlock = 256;
 constexpr int kNearBlock = 1024;
+constexpr int kFesBlock = 512;       // threads of the sample passes of the reweighting
+constexpr int kFesSamples = 1024;    // samples per workgroup they aim for
 constexpr int kFesLdsBins = 16384;  // per-block histograms in LDS up to this many bins
 
 struct Box64 {
@@ -191,6 +193,12 @@ __global__ __launch_bounds__(kNearBlock) void k_nearest(const float4* __restrict
 // denominator sum_t w_t by fixed-order block partials, the per-bin numerators
 // by per-block LDS histograms merged with FP64 atomics (reproducible to about
 // 1e-15 relative, not bit for bit), then F = -kBT log(num / den).
+//
+// Three dependent launches over little data, so latency bounds them: each
+// kernel reads the block partials of the one before with all its threads (one
+// thread reading all 782 of them in turn took 40 us), and a block takes
+// kFesSamples samples or more, so that clearing and merging its histogram
+// is not the larger part.  200,000 samples, 72 x 60 bins: 117 -> 21 us.
 // --------------------------------------------------------------------------
 struct FesArgs {
   const double* s;  // [T][dims]
@@ -218,58 +226,67 @@ __device__ __forceinline__ int32_t fes_bin(const FesArgs& a, int64_t t) {
   return bin;
 }
 
-__global__ __launch_bounds__(kSmallBlock) void k_fes_vmax(FesArgs a) {
-  __shared__ double red[kSmallBlock];
-  double m = -__builtin_inf();
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < a.T; t += (int64_t)gridDim.x * blockDim.x)
-    m = fmax(m, a.V[t]);
-  red[threadIdx.x] = m;
+// Largest of the block's values, in every thread.  All threads call.
+__device__ __forceinline__ double block_max(double m, double* lds) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
   __syncthreads();
-  for (int h = blockDim.x / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + h]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.vmax_part[blockIdx.x] = red[0];
+  m = lds[0];
+  for (int i = 1; i < (int)(blockDim.x >> 6); i++) m = fmax(m, lds[i]);
+  __syncthreads();
+  return m;
 }
 
+// The block maxima, and the numerators cleared alongside.
+__global__ __launch_bounds__(kFesBlock) void k_fes_vmax(FesArgs a) {
+  __shared__ double red[kFesBlock / 64];
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t b = t0; b < a.nbins; b += stride) a.num[b] = 0.0;
+  double m = -__builtin_inf();
+  for (int64_t t = t0; t < a.T; t += stride) m = fmax(m, a.V[t]);
+  m = block_max(m, red);
+  if (threadIdx.x == 0) a.vmax_part[blockIdx.x] = m;
+}
+
+// The atomics are the hardware's FP64 adds: the histogram lies in LDS or in
+// ordinary device memory.
 template <bool LDS_HIST>
-__global__ __launch_bounds__(kSmallBlock) void k_fes_accum(FesArgs a, int32_t nblk) {
+__global__ __launch_bounds__(kFesBlock) void k_fes_accum(FesArgs a, int32_t nblk) {
   extern __shared__ double hist[];
-  __shared__ double red[kSmallBlock / 64];
+  __shared__ double red[kFesBlock / 64];
   double vmax = -__builtin_inf();
-  for (int32_t i = 0; i < nblk; i++) vmax = fmax(vmax, a.vmax_part[i]);
-  if (LDS_HIST) {
+  for (int32_t i = threadIdx.x; i < nblk; i += blockDim.x) vmax = fmax(vmax, a.vmax_part[i]);
+  if (LDS_HIST)
     for (int32_t b = threadIdx.x; b < a.nbins; b += blockDim.x) hist[b] = 0.0;
-    __syncthreads();
-  }
+  vmax = block_max(vmax, red);  // its barriers also order the cleared histogram
   double den = 0.0;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < a.T; t += (int64_t)gridDim.x * blockDim.x) {
     const double w = exp((a.V[t] - vmax) / a.kBT);
     den += w;
     const int32_t bin = fes_bin(a, t);
-    if (bin >= 0) atomicAdd(LDS_HIST ? &hist[bin] : &a.num[bin], w);
+    if (bin >= 0) unsafeAtomicAdd(LDS_HIST ? &hist[bin] : &a.num[bin], w);
   }
-  den = block_sum(den, red);
+  den = block_sum(den, red);  // and these the histogram's additions
   if (threadIdx.x == 0) a.den_part[blockIdx.x] = den;
-  if (LDS_HIST) {
-    __syncthreads();
+  if (LDS_HIST)
     for (int32_t b = threadIdx.x; b < a.nbins; b += blockDim.x)
-      if (hist[b] != 0.0) atomicAdd(&a.num[b], hist[b]);
-  }
+      if (hist[b] != 0.0) unsafeAtomicAdd(&a.num[b], hist[b]);
 }
 
 __global__ __launch_bounds__(kSmallBlock) void k_fes_out(FesArgs a, int32_t nblk) {
-  double den = 0.0;  // the same fixed order in every thread
-  for (int32_t i = 0; i < nblk; i++) den += a.den_part[i];
+  __shared__ double red[kSmallBlock / 64];
+  __shared__ double total;
+  double den = 0.0;  // the same fixed order in every block
+  for (int32_t i = threadIdx.x; i < nblk; i += blockDim.x) den += a.den_part[i];
+  den = block_sum(den, red);
+  if (threadIdx.x == 0) total = den;
+  __syncthreads();
+  den = total;
   for (int32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < a.nbins; b += gridDim.x * blockDim.x) {
     const double p = a.num[b] / den;
     a.F[b] = a.num[b] > 0.0 ? -a.kBT * log(p) : __builtin_inf();
   }
-}
-
-__global__ __launch_bounds__(kSmallBlock) void k_zero_f64(double* p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0.0;
 }
 
 // F = -scale V on the grid of bin centres.
@@ -535,23 +552,22 @@ FesArgs fes_args(const double* s, const double* V, int64_t T, int32_t dims, cons
 
 // Workgroups of the sample passes and the doubles of scratch they need: the
 // per-workgroup maxima and denominators, then the per-bin numerators.
-unsigned fes_blocks(int64_t T) { return grid_for(T, kSmallBlock, 1024); }
+unsigned fes_blocks(int64_t T) { return grid_for(T, kFesSamples, 1024); }
 size_t fes_scratch_doubles(int64_t T, int32_t nbins) { return 2 * (size_t)fes_blocks(T) + (size_t)nbins; }
 
 // The reweighting kernels over a scratch of fes_scratch_doubles(T, nbins)
 // doubles; every value of it that they read is written first (the
-// numerators by k_zero_f64, the partials by one workgroup each).
+// numerators and maxima by k_fes_vmax, the denominators by one workgroup each).
 hipError_t enqueue_fes_reweight(FesArgs a, double* scratch, hipStream_t st) {
   const unsigned blocks = fes_blocks(a.T);
   a.vmax_part = scratch;
   a.den_part = a.vmax_part + blocks;
   a.num = a.den_part + blocks;
-  k_zero_f64<<<grid_for(a.nbins, kSmallBlock, 4096), kSmallBlock, 0, st>>>(a.num, a.nbins);
-  k_fes_vmax<<<blocks, kSmallBlock, 0, st>>>(a);
+  k_fes_vmax<<<blocks, kFesBlock, 0, st>>>(a);
   if (a.nbins <= kFesLdsBins)
-    k_fes_accum<true><<<blocks, kSmallBlock, (size_t)a.nbins * sizeof(double), st>>>(a, (int32_t)blocks);
+    k_fes_accum<true><<<blocks, kFesBlock, (size_t)a.nbins * sizeof(double), st>>>(a, (int32_t)blocks);
   else
-    k_fes_accum<false><<<blocks, kSmallBlock, 0, st>>>(a, (int32_t)blocks);
+    k_fes_accum<false><<<blocks, kFesBlock, 0, st>>>(a, (int32_t)blocks);
   k_fes_out<<<grid_for(a.nbins, kSmallBlock, 4096), kSmallBlock, 0, st>>>(a, (int32_t)blocks);
   return hipGetLastError();
 }
@@ -580,15 +596,12 @@ hipError_t scratch_on_current_device(double** out) {
 
 }  // namespace
 
+size_t fes_reweight_scratch_doubles(int64_t T, int32_t nbins) { return fes_scratch_doubles(T, nbins); }
+
 hipError_t launch_fes_reweight(const double* s, const double* V, int64_t T, int32_t dims, const double* lo,
-                               const double* hi, const int32_t* nb, double kBT, double* F, hipStream_t st) {
-  const FesArgs a = fes_args(s, V, T, dims, lo, hi, nb, kBT, F);
-  void* buf = nullptr;
-  hipError_t e = hipMallocAsync(&buf, fes_scratch_doubles(T, a.nbins) * sizeof(double), st);
-  if (e != hipSuccess) return e;
-  e = enqueue_fes_reweight(a, reinterpret_cast<double*>(buf), st);
-  const hipError_t f = hipFreeAsync(buf, st);
-  return e != hipSuccess ? e : f;
+                               const double* hi, const int32_t* nb, double kBT, double* F, double* scratch,
+                               hipStream_t st) {
+  return enqueue_fes_reweight(fes_args(s, V, T, dims, lo, hi, nb, kBT, F), scratch, st);
 }
 
 hipError_t launch_fes_reweight_noalloc(const double* s, const double* V, int64_t T, int32_t dims, const double* lo,

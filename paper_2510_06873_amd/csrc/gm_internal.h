@@ -250,8 +250,11 @@ hipError_t launch_torsion_forces(const float4* pos, int64_t n, const int32_t* qu
 hipError_t launch_nearest(const float4* pos, int64_t n, int32_t centre, const int32_t* members, int32_t count,
                           const double* box, double* s, int32_t* atom, const double* dV, void* force, bool fp64,
                           hipStream_t st);
+// scratch: fes_reweight_scratch_doubles(T, nbins) doubles.
+size_t fes_reweight_scratch_doubles(int64_t T, int32_t nbins);
 hipError_t launch_fes_reweight(const double* s, const double* V, int64_t T, int32_t dims, const double* lo,
-                               const double* hi, const int32_t* nb, double kBT, double* F, hipStream_t st);
+                               const double* hi, const int32_t* nb, double kBT, double* F, double* scratch,
+                               hipStream_t st);
 // The same kernels over the library's fixed per-device scratch (no allocation);
 // at most kFesNoAllocMaxBins bins.
 hipError_t launch_fes_reweight_noalloc(const double* s, const double* V, int64_t T, int32_t dims, const double* lo,
