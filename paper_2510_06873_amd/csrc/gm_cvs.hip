@@ -102,24 +102,70 @@ __global__ __launch_bounds__(kSmallBlock) void k_torsions(const float4* __restri
   phi[t] = load_quad(quads, t, n, q) ? torsion(pos, q, box, nullptr) : __builtin_nan("");
 }
 
-// F_i -= sum_t dV/dphi_t dphi_t/dx_i, one thread in torsion order (torsions
-// share atoms; the order fixes the result).
+// F_i -= sum_t dV/dphi_t dphi_t/dx_i, every atom's terms added in torsion
+// order (torsions share atoms; the order, and a rounding to F after each
+// term, fixes the result).  One workgroup takes kTorsionChunk torsions at a
+// time: each thread computes one atom's term (the torsion's latency is paid
+// once per chunk instead of once per torsion) and leaves it in LDS; the first
+// entry of each atom then adds the atom's entries in order.  The scan for the
+// entries of an atom reads every id of the chunk (broadcast reads), which grows
+// with the square of the chunk: 64 torsions keep it near a microsecond.
+// 32 torsions that share atoms along a chain: 45 us in one thread -> 4.2 us.
+constexpr int kTorsionChunk = 64;
+
 template <typename F>
-__global__ void k_torsion_forces(const float4* __restrict__ pos, int64_t n, const int32_t* __restrict__ quads,
-                                 int32_t count, Box64 box, const double* __restrict__ dV, F* force) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  for (int32_t t = 0; t < count; t++) {
-    int32_t q[4];
-    if (!load_quad(quads, t, n, q)) continue;
-    double g[4][3];
-    torsion(pos, q, box, g);
-    const double f = dV[t];
-    for (int k = 0; k < 4; k++) {
-      F* r = force + 4 * (int64_t)q[k];
-      r[0] = (F)((double)r[0] - f * g[k][0]);
-      r[1] = (F)((double)r[1] - f * g[k][1]);
-      r[2] = (F)((double)r[2] - f * g[k][2]);
+__global__ __launch_bounds__(4 * kTorsionChunk) void k_torsion_forces(const float4* __restrict__ pos, int64_t n,
+                                                                      const int32_t* __restrict__ quads, int32_t count,
+                                                                      Box64 box, const double* __restrict__ dV,
+                                                                      F* force) {
+  __shared__ __align__(16) int32_t ids[4 * kTorsionChunk];
+  __shared__ double term[4 * kTorsionChunk][4];  // dV/dphi, then dphi/dx of the entry's atom
+  const int e = (int)threadIdx.x, k = e & 3;
+  for (int32_t t0 = 0; t0 < count; t0 += kTorsionChunk) {
+    const int32_t t = t0 + (e >> 2);
+    int32_t id = -1;  // no atom
+    if (t < count) {
+      int32_t q[4];
+      if (load_quad(quads, t, n, q)) {
+        double g[4][3];
+        torsion(pos, q, box, g);
+        id = k < 2 ? (k == 0 ? q[0] : q[1]) : (k == 2 ? q[2] : q[3]);
+        term[e][0] = dV[t];
+#pragma unroll
+        for (int a = 0; a < 3; a++)
+          term[e][1 + a] = k < 2 ? (k == 0 ? g[0][a] : g[1][a]) : (k == 2 ? g[2][a] : g[3][a]);
+      }
     }
+    ids[e] = id;
+    bool owner = id >= 0;
+    F* r = force + 4 * (int64_t)(owner ? id : 0);
+    F f[3] = {F(0), F(0), F(0)};
+    if (owner)
+      for (int a = 0; a < 3; a++) f[a] = r[a];
+    __syncthreads();
+    // the entries of this atom as bits, then the owner's walk over them
+    const int entries = (count - t0 < kTorsionChunk ? count - t0 : kTorsionChunk) * 4;
+#pragma unroll
+    for (int w = 0; w < 4 * kTorsionChunk; w += 32) {
+      if (w >= entries) break;
+      uint32_t m = 0;
+#pragma unroll
+      for (int i = 0; i < 32; i += 4) {
+        const int4 four = *reinterpret_cast<const int4*>(&ids[w + i]);
+        m |= (four.x == id ? 1u << i : 0u) | (four.y == id ? 2u << i : 0u) | (four.z == id ? 4u << i : 0u) |
+             (four.w == id ? 8u << i : 0u);
+      }
+      if (w + __ffs(m) - 1 < e && m != 0) owner = false;  // an earlier entry adds this atom's terms
+      if (owner)
+        for (; m != 0; m &= m - 1) {
+          const double* x = term[w + __ffs(m) - 1];
+#pragma unroll
+          for (int a = 0; a < 3; a++) f[a] = (F)((double)f[a] - x[0] * x[1 + a]);
+        }
+    }
+    if (owner)
+      for (int a = 0; a < 3; a++) r[a] = f[a];
+    __syncthreads();  // forces and LDS entries before the next chunk
   }
 }
 
@@ -502,9 +548,9 @@ hipError_t launch_torsion_forces(const float4* pos, int64_t n, const int32_t* qu
   const Box64 b{{box[0], box[1], box[2]}};
   if (count > 0) {
     if (fp64)
-      k_torsion_forces<double><<<1, 64, 0, st>>>(pos, n, quads, count, b, dV, reinterpret_cast<double*>(force));
+      k_torsion_forces<double><<<1, 4 * kTorsionChunk, 0, st>>>(pos, n, quads, count, b, dV, reinterpret_cast<double*>(force));
     else
-      k_torsion_forces<float><<<1, 64, 0, st>>>(pos, n, quads, count, b, dV, reinterpret_cast<float*>(force));
+      k_torsion_forces<float><<<1, 4 * kTorsionChunk, 0, st>>>(pos, n, quads, count, b, dV, reinterpret_cast<float*>(force));
   }
   return hipGetLastError();
 }

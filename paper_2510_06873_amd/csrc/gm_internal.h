@@ -15,7 +15,7 @@ constexpr int kBuildGroup = 8;          // lanes that build one atom's row toget
 constexpr int kBuildFillBlocks = 1024;  // workgroups a neighbour build aims for (4 per CU)
 constexpr int kBuildMaxSplit = 32;      // most workgroups sharing one brick in the build
 constexpr int kXcd = 8;      // workgroups are dealt to the 8 XCDs round-robin
-constexpr int32_t kMaxTorsions = 1 << 16;   // torsion forces are summed by one thread in order
+constexpr int32_t kMaxTorsions = 1 << 16;   // torsion forces are summed by one workgroup in order
 constexpr int64_t kMaxFesBins = 1 << 24;
 constexpr int32_t kFesNoAllocMaxBins = 1 << 16;  // bins of the allocation-free reweighting
 
