@@ -595,7 +595,7 @@ GatherArgs gather_args(gm_ctx* c, const float* pos4) {
   g.n = c->n;
   g.pos_s = c->pos_s;
   g.err = c->err;
-  for (int d = 0; d < 3; d++) g.L[d] = (float)c->geom.L[d];
+  for (int d = 0; d < 3; d++) g.L[d] = c->geom.L[d];
   return g;
 }
 

@@ -252,8 +252,15 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int64_t t) {
   if (!(isfinite(p.x) && isfinite(p.y) && isfinite(p.z))) atomicOr(a.err, kErrNonFinite);
   // A coordinate outside [0, L) may sit in a cell of another image: the CV
   // passes then take the minimum image for every pair until the next rebuild
-  // clears the flag (one atomic per wave).
-  const bool out = !(p.x >= 0.f && p.x < a.L[0] && p.y >= 0.f && p.y < a.L[1] && p.z >= 0.f && p.z < a.L[2]);
+  // clears the flag (one atomic per wave), and the build tests every pair in
+  // FP64.  The comparison is with the FP64 length: where L rounds down to
+  // FP32, a wrapped coordinate just below L rounds to that value, which is
+  // inside.  Compared with the rounded length, one such atom (at 1.02M atoms
+  // of a crystal with a plane on the face there usually is one) put the whole
+  // system on the slow variants: build 316 us instead of 223,
+  // the four CV passes 451 us instead of 434.
+  const double px = (double)p.x, py = (double)p.y, pz = (double)p.z;
+  const bool out = !(px >= 0.0 && px < a.L[0] && py >= 0.0 && py < a.L[1] && pz >= 0.0 && pz < a.L[2]);
   const uint64_t m = __ballot(out);
   if (m != 0 && (int)(threadIdx.x & 63) == __ffsll((unsigned long long)m) - 1) atomicOr(a.err + 1, 1);
   vec4_t<T> q;

@@ -169,7 +169,7 @@ struct GatherArgs {
   int64_t n;
   void* pos_s;
   int32_t* err;  // err[0]: error bits; err[1] set when a coordinate lies outside [0, L)
-  float L[3];    // box lengths
+  double L[3];   // box lengths
 };
 
 // Everything one walker's neighbour rebuild reads and writes, kept in device
