@@ -496,21 +496,58 @@ CvArgs<T> make_args(gm_ctx* c) {
   return a;
 }
 
+// Time of the CV passes of one step (us, to a scale) for bricks of `own` owned
+// and `halo` staged atoms, nb workgroups of blk threads, tpa lanes per atom
+// and lists of `list` atoms: a launch, the walk of one workgroup's longest
+// lane (what a system of few workgroups takes however many CUs are idle), and
+// the work a CU gets when it holds several (staging, and each wave's walk).
+// Fitted to steps timed over 26 systems of 864 to 203,000 atoms, fcc and
+// wurtzite, with up to 42 brick shapes and lane counts each; its choice is
+// within 2% (mean) and 8% (worst) of the fastest of them.
+struct PassCost {
+  double launch, walk, stage_halo, cu_halo, cu_walk, cu_brick;
+};
+constexpr PassCost kCostQ6[2] = {{14.4, 0.954, 0.0, 0.00862, 0.0993, 6.71}, {14.3, 1.33, 0.0, 0.00408, 0.412, 13.8}};
+constexpr PassCost kCostCoord[2] = {{10.0, 0.0886, 0.162, 0.000925, 0.00855, 1.05},
+                                    {13.3, 0.0782, 0.0723, 0.00028, 0.0201, 0.725}};
+
+// Atoms of a full brick where the mean is `own`: a workgroup whose lanes the
+// mean just fills takes a second round in most of its bricks.
+double full_brick(double own) { return own + 1.5 * std::sqrt(own); }
+
+double pass_cost(const PassCost& k, double own, double halo, double list, double nb, int blk, int tpa) {
+  const double lanes = own * tpa, walk = list / tpa * std::ceil(tpa * full_brick(own) / blk);
+  const double waves = std::ceil((lanes < blk ? lanes : (double)blk) / 64.0), per_cu = nb < 256.0 ? 1.0 : nb / 256.0;
+  return k.launch + k.walk * walk + k.stage_halo * halo / blk +
+         per_cu * (k.cu_halo * halo + k.cu_walk * waves * walk + k.cu_brick);
+}
+
 // Brick size and threads per atom: among the bricks whose expected halo (atoms
-// of the (b+2)^3 cells around them, 5% margin) fits the LDS staging budget,
-// the one that keeps the most lanes of a 256-thread workgroup busy
-// (owned atoms x threads per atom, at most 92% of 256 so that fluctuations
-// rarely need a second pass), discounted by the halo re-load ratio.
+// of the (b+2)^3 cells around them, 5% margin) fits the LDS staging budget, the
+// pair of least estimated time.  Large systems get bricks that fill a
+// workgroup with few lanes per atom (the least staging per atom), small ones
+// small bricks and four lanes per atom (the shortest walk): with the large
+// bricks alone 864 atoms ran in 8 workgroups (30.6 us per step in FP64, now
+// 16.2) and 16,632 in 96 (46.7, now 36.3).
+//
+// q6 bricks may stage at most kStage times the cells they own: the choice must
+// not depend on what else runs (a batched walker equals the same walker alone),
+// and in a batch that fills the chip small bricks cost their staging (2x2x2
+// bricks of four lanes 215 us against 113 for 3x3x4 of two at 201,600 atoms,
+// 2x3x3 144).  Systems below kSmallAtoms, a small part of any such batch, and
+// FP64 ones may stage more: 5,376 atoms 45 -> 34 us, 2,048 in FP64 60 -> 45.
+constexpr double kStage = 5.6, kStageSmall = 8.0, kStageFp64 = 10.0;
+constexpr int64_t kSmallAtoms = 8192;
 void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
   const int rec = c->fp64 ? slot_bytes<double>(c->has_q6) : slot_bytes<float>(c->has_q6);
-  // pass 1 stages positions only and adds the rank keys; with q6 rows the
-  // row staging of passes 2-4 is the larger user
-  const int rank = c->fp64 ? rank_lds_bytes<double>() : rank_lds_bytes<float>();
-  const int cap = c->has_q6 ? c->lds_budget / rec : (c->lds_budget - rank) / rec;
+  const int cap = c->lds_budget / rec;  // pass 1 of a q6 CV adds rank keys to its positions, still less than the rows
   const int blk = c->fp64 ? BrickBlock<double>::value : BrickBlock<float>::value;
   const double rho = (double)c->n / ((double)nc[0] * nc[1] * nc[2]);
   int best[3] = {1, 1, 1}, best_tpa = 1;
-  double best_score = -1.0;
+  double best_cost = -1.0;
+  const PassCost& model = (c->has_q6 ? kCostQ6 : kCostCoord)[c->fp64 ? 1 : 0];
+  const double list = 4.0 / 3.0 * M_PI * rho;  // atoms within one cell width
+  const double stage = c->fp64 ? kStageFp64 : (c->n < kSmallAtoms ? kStageSmall : kStage);
   const bool fixed = c->p.brick[0] > 0;
   for (int bx = 1; bx <= kMaxBrick && bx <= nc[0]; bx++)
     for (int by = 1; by <= kMaxBrick && by <= nc[1]; by++)
@@ -522,12 +559,15 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
         const double halo = (double)(bx + 2) * (by + 2) * (bz + 2) * rho;
         const double own = (double)bx * by * bz * rho;
         if (!fixed && halo * 1.05 > cap) continue;
+        // pass 1 ranks at most a workgroup of atoms (the others keep cell order)
+        if (!fixed && c->has_q6 && full_brick(own) > blk) continue;
+        const double nb = std::ceil((double)nc[0] / bx) * std::ceil((double)nc[1] / by) * std::ceil((double)nc[2] / bz);
+        const double over = c->has_q6 && halo > stage * own ? 1e9 : 0.0;  // only where nothing else fits
         for (int tpa = 1; tpa <= 4; tpa *= 2) {
           if (c->p.tpa > 0 && tpa != c->p.tpa) continue;
-          if (own * tpa > 0.92 * blk && !(fixed && tpa == (c->p.tpa > 0 ? c->p.tpa : 1))) continue;
-          const double score = own * tpa * (1.0 - 0.02 * halo / own);
-          if (score > best_score) {
-            best_score = score;
+          const double cost = pass_cost(model, own, halo, list, nb, blk, tpa) + over;
+          if (best_cost < 0.0 || cost < best_cost) {
+            best_cost = cost;
             best[0] = bx;
             best[1] = by;
             best[2] = bz;
@@ -535,7 +575,7 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
           }
         }
       }
-  if (best_score < 0.0 && c->p.tpa > 0) best_tpa = c->p.tpa;  // no brick fits the lanes: 1x1x1
+  if (best_cost < 0.0 && c->p.tpa > 0) best_tpa = c->p.tpa;  // no brick fits the lanes: 1x1x1
   BrickGeom& g = c->bg;
   for (int a = 0; a < 3; a++) {
     g.nc[a] = nc[a];
@@ -543,7 +583,21 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
     g.nb[a] = (nc[a] + best[a] - 1) / best[a];
   }
   g.nbricks = g.nb[0] * g.nb[1] * g.nb[2];
+  const double own = (double)best[0] * best[1] * best[2] * rho;
+  const double halo = (double)(best[0] + 2) * (best[1] + 2) * (best[2] + 2) * rho;
+  const int expect = (int)std::ceil(1.25 * halo) + 64;
+  // The coordination pass stages positions only and its registers allow four
+  // workgroups per CU: it takes the largest share of a CU's LDS (a quarter, a
+  // third, a half) that still holds the halo it expects.
   g.cap = cap;
+  if (!c->has_q6)
+    for (int wg = 4; wg > 2; wg--) {
+      const int share = (160 * 1024 / wg - 2048) / rec;
+      if (share >= expect) {
+        g.cap = share < cap ? share : cap;
+        break;
+      }
+    }
   g.blocks = (g.nbricks + kXcd - 1) / kXcd * kXcd;
   g.tpa = best_tpa;
   g.kpart = ((c->kmax + best_tpa - 1) / best_tpa + 7) / 8 * 8;
@@ -554,10 +608,7 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
   // splits each brick's atoms over several workgroups (each stages the
   // whole halo) so that the launch still fills the device, down to about one
   // atom per lane group; the rows are the same for any split.
-  const double own = (double)best[0] * best[1] * best[2] * rho;
-  const double halo = (double)(best[0] + 2) * (best[1] + 2) * (best[2] + 2) * rho;
-  const int bcap = (int)std::ceil(1.25 * halo) + 64;
-  g.build_cap = bcap < cap ? bcap : cap;
+  g.build_cap = expect < cap ? expect : cap;
   g.build_threads = g.build_cap * (int)sizeof(float4) > 32768 ? kBuildMaxThreads : kBlock;
   g.build_split = 1;
   if (g.nbricks < kBuildFillBlocks) {

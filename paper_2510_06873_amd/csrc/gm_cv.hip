@@ -869,21 +869,22 @@ __global__ __launch_bounds__(kBlock) void k_atom_values(CvArgs<T> a, int what, i
 // --------------------------------------------------------------------------
 // Launchers
 // --------------------------------------------------------------------------
+// rows: positions and rows (passes 2-4); rank: pass 1's rank keys (q6 CVs).
 template <typename T>
-static size_t lds_bytes(const CvArgs<T>& a, bool rows) {
-  return (size_t)a.bg.cap * (size_t)slot_bytes<T>(rows) + (rows ? 0 : (size_t)rank_lds_bytes<T>());
+static size_t lds_bytes(int32_t cap, bool rows, bool rank = false) {
+  return (size_t)cap * (size_t)slot_bytes<T>(rows) + (rank ? (size_t)rank_lds_bytes<T>() : 0);
 }
 
 template <typename T>
 hipError_t launch_q6_forward(const CvArgs<T>& a, bool with_cn, hipStream_t st) {
   const unsigned g = (unsigned)a.bg.blocks;
   if (with_cn) {
-    k_pass1<T, true, true><<<g, BrickBlock<T>::value, lds_bytes(a, false), st>>>(a);
-    k_pass2<T, true><<<g, BrickBlock<T>::value, lds_bytes(a, true), st>>>(a);
+    k_pass1<T, true, true><<<g, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, false, true), st>>>(a);
+    k_pass2<T, true><<<g, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, true), st>>>(a);
     k_finish<T, true, false><<<1, kBlock, 0, st>>>(a);
   } else {
-    k_pass1<T, false, true><<<g, BrickBlock<T>::value, lds_bytes(a, false), st>>>(a);
-    k_pass2<T, false><<<g, BrickBlock<T>::value, lds_bytes(a, true), st>>>(a);
+    k_pass1<T, false, true><<<g, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, false, true), st>>>(a);
+    k_pass2<T, false><<<g, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, true), st>>>(a);
     k_finish<T, false, false><<<1, kBlock, 0, st>>>(a);
   }
   return hipGetLastError();
@@ -891,7 +892,7 @@ hipError_t launch_q6_forward(const CvArgs<T>& a, bool with_cn, hipStream_t st) {
 
 template <typename T>
 hipError_t launch_q6_adjoint(const CvArgs<T>& a, hipStream_t st) {
-  k_pass3<T><<<(unsigned)a.bg.blocks, BrickBlock<T>::value, lds_bytes(a, true), st>>>(a);
+  k_pass3<T><<<(unsigned)a.bg.blocks, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, true), st>>>(a);
   return hipGetLastError();
 }
 
@@ -899,15 +900,15 @@ template <typename T>
 hipError_t launch_q6_force(const CvArgs<T>& a, bool with_cn, hipStream_t st) {
   const unsigned g = (unsigned)a.bg.blocks;
   if (with_cn)
-    k_pass4<T, true><<<g, BrickBlock<T>::value, lds_bytes(a, true), st>>>(a);
+    k_pass4<T, true><<<g, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, true), st>>>(a);
   else
-    k_pass4<T, false><<<g, BrickBlock<T>::value, lds_bytes(a, true), st>>>(a);
+    k_pass4<T, false><<<g, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, true), st>>>(a);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_cn_forward(const CvArgs<T>& a, hipStream_t st) {
-  k_pass1<T, true, false><<<(unsigned)a.bg.blocks, BrickBlock<T>::value, lds_bytes(a, false), st>>>(a);
+  k_pass1<T, true, false><<<(unsigned)a.bg.blocks, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, false), st>>>(a);
   k_finish<T, false, true><<<1, kBlock, 0, st>>>(a);
   return hipGetLastError();
 }
@@ -927,8 +928,8 @@ hipError_t launch_atom_values(const CvArgs<T>& a, int what, int cv_kind, double*
 template <typename T>
 hipError_t launch_pass_batch(int pass, bool with_cn, bool fp_rows, const CvArgs<T>* tab, const int32_t* blk_start,
                              int32_t W, int32_t blocks, int32_t cap, hipStream_t st) {
-  const size_t lds_pos = (size_t)cap * slot_bytes<T>(false) + (size_t)rank_lds_bytes<T>(),
-               lds_rows = (size_t)cap * slot_bytes<T>(true);
+  const size_t lds_cn = lds_bytes<T>(cap, false), lds_pos = lds_bytes<T>(cap, false, true),
+               lds_rows = lds_bytes<T>(cap, true);
   (void)fp_rows;
   const unsigned g = (unsigned)blocks;
   switch (pass) {
@@ -957,7 +958,7 @@ hipError_t launch_pass_batch(int pass, bool with_cn, bool fp_rows, const CvArgs<
         k_pass4_batch<T, false><<<g, BrickBlock<T>::value, lds_rows, st>>>(tab, blk_start, W);
       break;
     case 5:  // coordination alone: forward
-      k_pass1_batch<T, true, false><<<g, BrickBlock<T>::value, lds_pos, st>>>(tab, blk_start, W);
+      k_pass1_batch<T, true, false><<<g, BrickBlock<T>::value, lds_cn, st>>>(tab, blk_start, W);
       k_finish_batch<T, false, true><<<(unsigned)W, kBlock, 0, st>>>(tab);
       break;
     case 6:  // coordination alone: forces
