@@ -606,14 +606,15 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
   // take a CU's LDS for little use; 512 threads when that staging is large
   // (fewer workgroups share a CU), else 256.  A system with few bricks
   // splits each brick's atoms over several workgroups (each stages the
-  // whole halo) so that the launch still fills the device, down to about one
-  // atom per lane group; the rows are the same for any split.
+  // whole halo) so that the launch still fills the device, down to a few
+  // atoms per wave; the rows are the same for any split.
   g.build_cap = expect < cap ? expect : cap;
   g.build_threads = g.build_cap * (int)sizeof(float4) > 32768 ? kBuildMaxThreads : kBlock;
+  g.build_win = build_window(c->kmax, g.build_threads);
   g.build_split = 1;
   if (g.nbricks < kBuildFillBlocks) {
     int split = (kBuildFillBlocks + g.nbricks - 1) / g.nbricks;
-    int most = (int)std::ceil(own / (g.build_threads / kBuildGroup));
+    int most = (int)std::ceil(own / (g.build_threads / 64 * kBuildAtoms));
     most = most < 1 ? 1 : most;
     split = split < most ? split : most;
     g.build_split = split < kBuildMaxSplit ? split : kBuildMaxSplit;
@@ -803,7 +804,9 @@ int gm_create(gm_ctx** out, const gm_params* params, int64_t n_atoms, void* hip_
     std::lock_guard<std::mutex> lock(g_lds_mu);
     if (c->lds_budget > g_lds_max) g_lds_max = c->lds_budget;
     allow_cv_lds(g_lds_max);
-    allow_build_lds(g_lds_max);
+    // the neighbour build's staging is at most the budget, its rows beside it
+    const int rows = kBuildMaxThreads / 64 * build_row_width(4096) * 2 + 64 * 2;
+    allow_build_lds(g_lds_max + rows < lim ? g_lds_max + rows : lim);
   }
 
   const size_t n = c->external ? 1 : (size_t)n_atoms, T = c->fp64 ? 8 : 4;  // no atom buffers for external CVs

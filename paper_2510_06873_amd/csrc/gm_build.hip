@@ -416,136 +416,256 @@ __global__ __launch_bounds__(kBlock) void k_brick_fill(const int32_t* __restrict
 // r^2 = (dx dx + dy dy) + dz dz < r_list^2.  (rint(d * (1/L)) picks the same
 // image as rint(d / L) for every pair that can pass the test, since such pairs
 // have |d/L| far from a half integer.)  It is taken in FP32 first: r^2 in
-// FP32 is within 4e-7 (relative) of the FP64 value (pair difference, three
-// squares and two sums, each rounded once), so outside a band of 4e-6 around
+// FP32 is within 4e-7 (relative) of the FP64 value (pair difference, a
+// square and two fused multiply-adds, each rounded once), so outside a band of 4e-6 around
 // r_list^2 the FP32 answer is the FP64 one, and only pairs inside the band
 // are tested in FP64.  The bound needs coordinates inside [0, L) (then the
-// minimum image rounds once, at the pair's magnitude); if the gather flagged
+// nearest image is that of the halo cell); if the gather flagged
 // any outside, every pair takes the FP64 test.  Candidates are the atoms of
 // the 27 cells around the atom's own cell: nine runs of three x-adjacent halo
 // cells, whose slots are contiguous, visited in a fixed order.
 //
-// A group of kBuildGroup lanes builds one atom's row: it tests kBuildGroup
-// consecutive candidates of a run at once, and a ballot gives each lane that
-// passes the number of passing lanes before it, i.e. its entry index.  The
-// row therefore holds the candidates in run order and slot order within a
-// run, the order of a sequential scan.  Entry e lives in sub-row e % tpa at
-// index e / tpa; the rest of each sub-row's last 16-byte piece is zeroed,
-// since the CV passes read rows in whole pieces.
-// MODE 0: FP32 plain differences (halo off the faces), 1: FP32 minimum image,
-// 2: FP64 only (coordinates outside the box).  STAGED: every halo slot of the
-// brick is in LDS (no per-candidate check for slots read from global memory).
-template <int MODE, bool STAGED, typename T>
-__device__ __forceinline__ void build_rows(const vec4_t<T>* __restrict__ pos_s, const CellGeom& cg,
-                                           const BrickGeom& g, const BrickIndex& bi, double rl2, uint16_t* nbr,
-                                           int32_t kmax, int32_t* cnt, int32_t* err, const float4* hpos,
-                                           const int32_t* hp, int32_t hb, int32_t ob, int32_t O, int32_t k0,
-                                           int32_t k1,
-                                           int32_t hx, int32_t hxy, uint32_t wmask, int32_t& mymax, double& mysum) {
-#pragma clang fp contract(off)
-  float Lf[3], iLf[3], Llo[3];
+// A wave builds the rows of atoms of one cell together: their candidates are
+// the same, so its lanes hold kBuildChunks x 64 of them in registers and test
+// them against one atom after another, whose position comes from a lane
+// register (a scalar operand: no LDS read, no address and no loop over runs per
+// test).  The nine runs are walked as one sequence, so that only its last 64
+// are partly empty.  A ballot gives each lane that passes the number of passing
+// lanes before it, i.e. its entry index: the row holds the candidates in run
+// order and slot order within a run, the order of a sequential scan.  Rows are
+// gathered in LDS for a window of atoms and stored in whole 16-byte pieces,
+// zeros behind each sub-row's last entry (the CV passes read whole pieces);
+// entry e of a row lives in sub-row e % tpa at index e / tpa.
+//
+// VALU issue bounds it at size (85 instructions per atom of a q6 list, busy
+// 0.72), the latency of staging and setting up below.  Against the form before
+// (8 lanes per atom testing 8 candidates of one run at a time, each entry
+// stored by itself): 1,024,000 atoms q6 223 -> 190 us, 108,000 atoms at r_c 6
+// 127 -> 92, 96,000 q6 60 -> 51, 864 atoms at r_c 6 66 -> 21.
+//
+// Slots in cells across a periodic face are staged as the image beside the
+// brick (slot_image), so that every test is a plain difference: a candidate
+// lies in a cell next to the atom's, where that image is the nearest one or
+// both are farther than r_list.  Rounding the shifted coordinate moves r^2 by
+// up to 2.8e-7 Lmax / r_list (relative), which widens the band tested in FP64
+// for those bricks; the FP64 test reads the positions themselves.
+// EXACT: FP64 for every pair (coordinates outside the box).  STAGED: every halo
+// slot of the brick is in LDS (no per-candidate check for slots read from
+// global memory).
+constexpr int kBuildChunks = 3;  // 192 candidates: the 27 cells of a q6 list hold about 160
+
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// Position p of halo slot sl as the image in the halo cell that holds the slot.
+__device__ __forceinline__ float4 slot_image(float4 p, int32_t sl, const int32_t* hp, const BrickShape& s,
+                                             const BrickGeom& g, const CellGeom& cg) {
+  const int32_t hxy = s.h[0] * s.h[1];
+  int32_t lo = 0, hi = hxy * s.h[2];
+  while (hi - lo > 1) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (hp[mid] <= sl) lo = mid; else hi = mid;
+  }
+  int32_t c[3] = {lo, 0, 0};
+  for (; c[0] >= hxy; c[0] -= hxy) c[2]++;
+  for (; c[0] >= s.h[0]; c[0] -= s.h[0]) c[1]++;
+  float* x = &p.x;
 #pragma unroll
   for (int d = 0; d < 3; d++) {
-    Lf[d] = (float)cg.L[d];
-    iLf[d] = (float)cg.invL[d];
-    Llo[d] = (float)(cg.L[d] - (double)Lf[d]);
+    const int32_t at = s.o[d] - 1 + c[d];
+    if (at < 0) x[d] = (float)((double)x[d] - cg.L[d]);
+    if (at >= g.nc[d]) x[d] = (float)((double)x[d] + cg.L[d]);
   }
-  const float lo2 = (float)(rl2 * (1.0 - 4e-6)), hi2 = (float)(rl2 * (1.0 + 4e-6));
+  return p;
+}
+
+template <bool EXACT, bool STAGED, typename T>
+__device__ __forceinline__ void build_rows(const vec4_t<T>* __restrict__ pos_s, const CellGeom& cg,
+                                           const BrickGeom& g, const BrickShape& bs, const BrickIndex& bi, double rl2,
+                                           uint16_t* nbr, int32_t kmax, int32_t* cnt, int32_t* err, const float4* hpos,
+                                           uint16_t* rows, const int32_t* hp, int32_t hb, int32_t ob, int32_t O,
+                                           int32_t k0, int32_t k1, bool wrap, int32_t& mymax, double& mysum) {
+#pragma clang fp contract(off)
+  constexpr int U = kBuildChunks;
+  const int32_t hx = bs.h[0], hxy = bs.h[0] * bs.h[1];
+  const double Lmax = fmax(cg.L[0], fmax(cg.L[1], cg.L[2]));
+  const double eps = 4e-6 + (wrap ? 4e-7 * Lmax * __builtin_amdgcn_rsq(rl2) : 0.0);
+  const float lo2 = (float)(rl2 * (1.0 - eps)), hi2 = (float)(rl2 * (1.0 + eps));
   const int lane = (int)(threadIdx.x & 63);
-  const int lig = lane & (kBuildGroup - 1);
-  const int gshift = lane - lig;                  // the group's first lane
-  const uint32_t below = (1u << lig) - 1u;        // lanes of the group before this one
-  const int32_t groups = (int32_t)(blockDim.x / kBuildGroup);
   const int32_t tsh = g.tpa == 4 ? 2 : (g.tpa == 2 ? 1 : 0);
   const int32_t cap = g.build_cap;
-  for (int32_t k = k0 + (int32_t)(threadIdx.x / kBuildGroup); k < k1; k += groups) {
-    const int32_t si = bi.owned_slot[ob + k];
-    const int32_t hc = bi.owned_hcell[ob + k];
-    float4 pi;
-    if (si < cap) {
-      pi = hpos[si];
+  auto slot_pos = [&](int32_t sl) {
+    // staged slots (nearly all) read LDS; the rest global memory
+    float4 p;
+    if constexpr (STAGED) {
+      p = hpos[sl];
     } else {
-      const vec4_t<T> p = pos_s[bi.halo_rank[hb + si]];
-      pi = make_float4((float)p.x, (float)p.y, (float)p.z, 0.f);
+      p = hpos[min(sl, cap - 1)];
+      if (sl >= cap) {
+        const vec4_t<T> q = pos_s[bi.halo_rank[hb + sl]];
+        p = make_float4((float)q.x, (float)q.y, (float)q.z, 0.f);
+        if (wrap) p = slot_image(p, sl, hp, bs, g, cg);
+      }
     }
-    int32_t count = 0;  // the same in every lane of the group
-    // entry e goes to sub-row e % TPA at index x = e / TPA: piece x / 8 of
-    // that sub-row, pieces pstride8 entries apart (32-bit offsets from the
-    // brick's first piece)
-    uint16_t* const brow = nbr + row_first(g, ob, 0, 0);
-    const uint32_t row0 = (uint32_t)(k * g.tpa * 8);
-    const uint32_t pstride8 = (uint32_t)(piece_stride(g, O) * 8);
-    const uint32_t pmask = (uint32_t)(g.tpa - 1);
-    for (int cz = -1; cz <= 1; cz++)
-      for (int cy = -1; cy <= 1; cy++) {
-        const int h = hc + cz * hxy + cy * hx;  // middle cell of the x-run
-        const int32_t se = hp[h + 2];
-        for (int32_t base = hp[h - 1]; base < se; base += kBuildGroup) {
-          const int32_t sl = base + lig;
-          bool in = false;
-          if (sl < se && sl != si) {
-            // staged slots (nearly all) read LDS; the rest global memory
-            float4 pj;
-            if constexpr (STAGED) {
-              pj = hpos[sl];
-            } else {
-              pj = hpos[min(sl, cap - 1)];
-              if (sl >= cap) {
-                const vec4_t<T> p = pos_s[bi.halo_rank[hb + sl]];
-                pj = make_float4((float)p.x, (float)p.y, (float)p.z, 0.f);
+    return p;
+  };
+  // this wave's atoms, a window of at most build_win at a time, ending with a
+  // cell where it can: lane l holds atom base + l, and row l of the wave's
+  // share of `rows` collects its entries
+  const int32_t waves = (int32_t)(blockDim.x >> 6), wave = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
+  const int32_t each = (k1 - k0 + waves - 1) / waves, width = build_row_width(kmax);
+  const int32_t ka = k0 + wave * each, kb = min(ka + each, k1);
+  uint16_t* const mine = rows + wave * g.build_win * width;
+  uint16_t* const spare = rows + waves * g.build_win * width + lane;
+  for (int32_t base = ka, m; base < kb; base += m) {
+    const int32_t at = ob + min(base + lane, kb - 1);
+    const int32_t si_l = bi.owned_slot[at], hc_l = bi.owned_hcell[at];
+    const float4 pi_l = slot_pos(si_l);
+    m = min(g.build_win, kb - base);
+    if (base + m < kb) {
+      // the first atom of the cell that the next window would begin in
+      const uint64_t next = __ballot(hc_l == __builtin_amdgcn_readlane(hc_l, m));
+      const int32_t whole = __ffsll((unsigned long long)next) - 1;
+      m = whole > 0 ? whole : m;
+    }
+    int32_t count_l = 0;
+    // the atoms of one cell are consecutive: [a, b) of the window
+    for (int32_t a = 0, b; a < m; a = b) {
+      const int32_t h = __builtin_amdgcn_readlane(hc_l, a);
+      b = a + (int32_t)__popcll(__ballot(hc_l == h && lane < m));
+      // the runs (cells h + cz hxy + cy hx +- 1 along x): lane r < 9 has run r;
+      // run_d: what takes a candidate's number in the sequence to its slot
+      const int32_t r9 = min(lane, 8);
+      const int32_t rz = r9 >= 6 ? 1 : (r9 >= 3 ? 0 : -1), ry = r9 - 3 * rz - 4;
+      const int32_t row = h + rz * hxy + ry * hx;
+      const int32_t first = hp[row - 1];
+      const int32_t len = lane < 9 ? hp[row + 2] - first : 0;
+      int32_t before = len;  // inclusive prefix over the first 16 lanes, by register moves
+      before += __builtin_amdgcn_update_dpp(0, before, 0x111, 0xf, 0xf, true);
+      before += __builtin_amdgcn_update_dpp(0, before, 0x112, 0xf, 0xf, true);
+      before += __builtin_amdgcn_update_dpp(0, before, 0x114, 0xf, 0xf, true);
+      before += __builtin_amdgcn_update_dpp(0, before, 0x118, 0xf, 0xf, true);
+      const int32_t total = __builtin_amdgcn_readlane(before, 8);
+      before -= len;
+      const int32_t shift = first - before;
+      int32_t run_at[9], run_d[9];
+#pragma unroll
+      for (int r = 0; r < 9; r++) {
+        run_at[r] = __builtin_amdgcn_readlane(before, r);
+        run_d[r] = __builtin_amdgcn_readlane(shift, r);
+      }
+      // each z plane's three runs within 64 candidates (the usual case of a q6
+      // list): chunk u is plane u, whose slots take two comparisons
+      const bool planes = run_at[3] <= 64 && run_at[6] - run_at[3] <= 64 && total - run_at[6] <= 64;
+      for (int32_t c0 = 0; c0 < total; c0 += planes ? total : 64 * U) {
+        int32_t sl[U];
+        float4 pj[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const int32_t from = planes ? run_at[3 * u] : c0 + 64 * u;
+          const int32_t end = planes && u < 2 ? run_at[3 * u + 3] : total;
+          const int32_t c = from + lane, cc = max(min(c, end - 1), 0);
+          int32_t d;
+          if (planes) {
+            d = cc >= run_at[3 * u + 1] ? run_d[3 * u + 1] : run_d[3 * u];
+            d = cc >= run_at[3 * u + 2] ? run_d[3 * u + 2] : d;
+          } else {
+            d = run_d[0];
+#pragma unroll
+            for (int r = 1; r < 9; r++) d = cc >= run_at[r] ? run_d[r] : d;
+          }
+          sl[u] = cc + d;
+          pj[u] = slot_pos(sl[u]);
+          if (c >= end) pj[u].x = __builtin_nanf("");  // past the end: no test passes
+        }
+        const bool whole = planes || total <= 64 * U;  // every candidate is at hand
+        for (int32_t i = a; i < b; i++) {
+          const float px = lane_value(pi_l.x, i), py = lane_value(pi_l.y, i), pz = lane_value(pi_l.z, i);
+          float r2[U];
+          uint64_t pass[U];
+          int32_t open = 0;
+#pragma unroll
+          for (int u = 0; u < U; u++) {
+            const float ex = pj[u].x - px, ey = pj[u].y - py, ez = pj[u].z - pz;
+            r2[u] = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
+            // 0 < r2 < lo2 as one comparison of the bits (r2 is no negative; NaN
+            // lies above): an r2 of 0 is the atom itself, or rarely another
+            // atom at its place, and stays open like a pair between lo2 and hi2
+            pass[u] = __ballot(__float_as_uint(r2[u]) - 1u < __float_as_uint(lo2) - 1u);
+            open += (int32_t)__popcll(__ballot(r2[u] <= hi2)) - (int32_t)__popcll(pass[u]);
+          }
+          const int32_t have = c0 == 0 ? 0 : __builtin_amdgcn_readlane(count_l, i);
+          // the atom itself (in the middle run) is open wherever it is at hand
+          const int32_t si = __builtin_amdgcn_readlane(si_l, i);
+          const int32_t self = whole || (uint32_t)(si - run_d[4] - c0) < 64u * U ? 1 : 0;
+          if (EXACT || open != self) {
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+              const bool unsure = EXACT || (r2[u] <= hi2 && !(r2[u] > 0.f && r2[u] < lo2));
+              bool in = false;
+              if (unsure && sl[u] != si && pj[u].x == pj[u].x) {
+                const vec4_t<T> q = pos_s[bi.halo_rank[hb + sl[u]]];
+                double d0 = (double)q.x - (double)px;
+                double d1 = (double)q.y - (double)py;
+                double d2 = (double)q.z - (double)pz;
+                d0 = d0 - cg.L[0] * rint(d0 * cg.invL[0]);
+                d1 = d1 - cg.L[1] * rint(d1 * cg.invL[1]);
+                d2 = d2 - cg.L[2] * rint(d2 * cg.invL[2]);
+                in = d0 * d0 + d1 * d1 + d2 * d2 < rl2;
               }
-            }
-            float ex, ey, ez;
-            if constexpr (MODE == 1) {
-              // the minimum image on the axes whose halo reaches a face; on
-              // the others it is the plain difference (k = 0 in mic)
-              ex = (wmask & 1u) ? mic(pj.x, pi.x, Lf[0], iLf[0], Llo[0]) : pj.x - pi.x;
-              ey = (wmask & 2u) ? mic(pj.y, pi.y, Lf[1], iLf[1], Llo[1]) : pj.y - pi.y;
-              ez = (wmask & 4u) ? mic(pj.z, pi.z, Lf[2], iLf[2], Llo[2]) : pj.z - pi.z;
-            } else {
-              ex = pj.x - pi.x;
-              ey = pj.y - pi.y;
-              ez = pj.z - pi.z;
-            }
-            const float r2f = (ex * ex + ey * ey) + ez * ez;
-            in = MODE != 2 && r2f < lo2;
-            if (MODE == 2 || (!in && r2f <= hi2)) {
-              double d0 = (double)pj.x - (double)pi.x;
-              double d1 = (double)pj.y - (double)pi.y;
-              double d2 = (double)pj.z - (double)pi.z;
-              d0 = d0 - cg.L[0] * rint(d0 * cg.invL[0]);
-              d1 = d1 - cg.L[1] * rint(d1 * cg.invL[1]);
-              d2 = d2 - cg.L[2] * rint(d2 * cg.invL[2]);
-              in = d0 * d0 + d1 * d1 + d2 * d2 < rl2;
+              pass[u] = EXACT ? __ballot(in) : pass[u] | __ballot(in);
             }
           }
-          // the group's ballot bits
-          const uint32_t m8 = (uint32_t)(__ballot(in) >> gshift) & ((1u << kBuildGroup) - 1u);
-          if (in) {
-            const int32_t e = count + __popc(m8 & below);
-            if (e < kmax) {
-              const uint32_t x = (uint32_t)e >> tsh;
-              // piece index and stride below 2^24: the full-rate 24-bit multiply
-              brow[row0 + ((uint32_t)e & pmask) * 8u + __umul24(x >> 3, pstride8) + (x & 7u)] =
-                  (uint16_t)sl;
-            }
+          int32_t to[U + 1];
+          to[0] = have;
+#pragma unroll
+          for (int u = 0; u < U; u++) to[u + 1] = to[u] + (int32_t)__popcll(pass[u]);
+          uint16_t* const out = mine + i * width;
+          int32_t k[U];
+#pragma unroll
+          for (int u = 0; u < U; u++)
+            k[u] = (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(pass[u] >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)pass[u], 0u));
+          if (to[U] > kmax) {  // entries past the row's width are counted, not kept
+#pragma unroll
+            for (int u = 0; u < U; u++) pass[u] &= __ballot(to[u] + k[u] < kmax);
           }
-          count += __popc(m8);
+          // lanes that do not pass write to a place of their own that nothing
+          // reads: straight code instead of a branch per chunk
+#pragma unroll
+          for (int u = 0; u < U; u++)
+            *(__builtin_amdgcn_inverse_ballot_w64(pass[u]) ? out + to[u] + k[u] : spare) = (uint16_t)sl[u];
+          count_l = lane == i ? to[U] : count_l;
         }
       }
-    const int32_t stored = count < kmax ? count : kmax;
-    for (int32_t i = lig; i < 8 * g.tpa; i += kBuildGroup) {
-      const int32_t part = i >> 3;
-      const int32_t np = stored > part ? ((stored - 1 - part) >> tsh) + 1 : 0;
-      const int32_t at = np + (i & 7);
-      if (at < ((np + 7) & ~7)) nbr[row_entry(g, ob, O, k, part, at)] = 0;
     }
-    if (lig == 0) {
-      cnt[ob + k] = count;
-      if (count > kmax) atomicOr(err, kErrOverflow);
-      mymax = count > mymax ? count : mymax;
-      mysum += (double)count;
+    // the window's rows, one sub-row per lane (build_win tpa <= 64), 8 entries
+    // at a time
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int32_t i = min(lane >> tsh, m - 1), part = lane & (g.tpa - 1);
+    const int32_t n = min(__shfl(count_l, i, 64), kmax);
+    const int32_t np = (lane >> tsh) < m && n > part ? ((n - 1 - part) >> tsh) + 1 : 0;
+    const uint16_t* const src = mine + i * width + part;
+    uint4* dst = reinterpret_cast<uint4*>(nbr + row_first(g, ob, base + i, part));
+    for (int32_t x = 0; x < np; x += 8, dst += piece_stride(g, O)) {
+      uint32_t w[4];
+#pragma unroll
+      for (int q = 0; q < 8; q++) {
+        const uint32_t v = x + q < np ? src[(x + q) << tsh] : 0u;
+        w[q >> 1] = (q & 1) ? w[q >> 1] | (v << 16) : v;
+      }
+      *dst = make_uint4(w[0], w[1], w[2], w[3]);
     }
+    if (lane < m) {
+      cnt[ob + base + lane] = count_l;
+      if (count_l > kmax) atomicOr(err, kErrOverflow);
+      mymax = max(mymax, count_l);
+      mysum += (double)count_l;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // before the next window's entries
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -558,6 +678,7 @@ __device__ __forceinline__ void build_nbr_body(const vec4_t<T>* __restrict__ pos
                                                int32_t* err, int32_t* stats, int64_t lb) {
   extern __shared__ __align__(16) unsigned char smem[];
   float4* hpos = reinterpret_cast<float4*>(smem);
+  uint16_t* rows = reinterpret_cast<uint16_t*>(hpos + g.build_cap);
   __shared__ int32_t hp[kHaloCells + 1];
   __shared__ double red[MAXT / 64];
   __shared__ int32_t wmax[MAXT / 64];
@@ -566,51 +687,35 @@ __device__ __forceinline__ void build_nbr_body(const vec4_t<T>* __restrict__ pos
   // contiguous share of its owned atoms.
   const int64_t b = lb / g.build_split;
   const int32_t part = (int32_t)(lb - b * g.build_split);
-  const bool live = b < g.nbricks;
-  int32_t hb = 0, H = 0, ob = 0, O = 0, k0 = 0, k1 = 0, hx = 0, hxy = 0;
-  int mode = 2;
-  uint32_t wmask = 0;  // axes on which the halo reaches a periodic face
-  if (live) {
+  int32_t mymax = 0;
+  double mysum = 0.0;
+  if (b < g.nbricks) {
     const BrickShape s = brick_shape(b, g);
-    hx = s.h[0];
-    hxy = s.h[0] * s.h[1];
-    hb = bi.hb[b];
-    H = bi.hb[b + 1] - hb;
-    ob = bi.ob[b];
-    O = bi.ob[b + 1] - ob;
+    const int32_t hb = bi.hb[b], H = bi.hb[b + 1] - hb, ob = bi.ob[b], O = bi.ob[b + 1] - ob;
     const int32_t share = (O + g.build_split - 1) / g.build_split;
-    k0 = part * share < O ? part * share : O;
-    k1 = k0 + share < O ? k0 + share : O;
-    mode = err[1] != 0 ? 2 : (halo_touches_face(s, g) ? 1 : 0);
-    for (int d = 0; d < 3; d++)
-      if (s.o[d] < 2 || s.o[d] + s.e[d] > g.nc[d] - 2) wmask |= 1u << d;
+    const int32_t k0 = part * share < O ? part * share : O, k1 = k0 + share < O ? k0 + share : O;
+    const bool exact = err[1] != 0, wrap = !exact && halo_touches_face(s, g);
     const int nh = s.h[0] * s.h[1] * s.h[2];
     for (int h = threadIdx.x; h <= nh; h += blockDim.x) hp[h] = bi.hp[b * (kHaloCells + 1) + h];
+    if (wrap) __syncthreads();
     const int32_t ns = H < g.build_cap ? H : g.build_cap;
     for (int32_t sl = threadIdx.x; sl < ns; sl += blockDim.x) {
       const vec4_t<T> p = pos_s[bi.halo_rank[hb + sl]];
-      hpos[sl] = make_float4((float)p.x, (float)p.y, (float)p.z, 0.f);
+      float4 q = make_float4((float)p.x, (float)p.y, (float)p.z, 0.f);
+      if (wrap) q = slot_image(q, sl, hp, s, g, cg);
+      hpos[sl] = q;
     }
+    __syncthreads();
+    if (exact)
+      build_rows<true, false, T>(pos_s, cg, g, s, bi, rl2, nbr, kmax, cnt, err, hpos, rows, hp, hb, ob, O, k0, k1, false,
+                                 mymax, mysum);
+    else if (H <= g.build_cap)  // every halo slot in LDS
+      build_rows<false, true, T>(pos_s, cg, g, s, bi, rl2, nbr, kmax, cnt, err, hpos, rows, hp, hb, ob, O, k0, k1, wrap,
+                                 mymax, mysum);
+    else
+      build_rows<false, false, T>(pos_s, cg, g, s, bi, rl2, nbr, kmax, cnt, err, hpos, rows, hp, hb, ob, O, k0, k1, wrap,
+                                  mymax, mysum);
   }
-  __syncthreads();
-  int32_t mymax = 0;
-  double mysum = 0.0;
-  const bool staged = H <= g.build_cap;  // every halo slot in LDS
-  if (mode == 0 && staged)
-    build_rows<0, true, T>(pos_s, cg, g, bi, rl2, nbr, kmax, cnt, err, hpos, hp, hb, ob, O, k0, k1, hx, hxy, wmask, mymax,
-                           mysum);
-  else if (mode == 0)
-    build_rows<0, false, T>(pos_s, cg, g, bi, rl2, nbr, kmax, cnt, err, hpos, hp, hb, ob, O, k0, k1, hx, hxy, wmask, mymax,
-                            mysum);
-  else if (mode == 1 && staged)
-    build_rows<1, true, T>(pos_s, cg, g, bi, rl2, nbr, kmax, cnt, err, hpos, hp, hb, ob, O, k0, k1, hx, hxy, wmask, mymax,
-                           mysum);
-  else if (mode == 1)
-    build_rows<1, false, T>(pos_s, cg, g, bi, rl2, nbr, kmax, cnt, err, hpos, hp, hb, ob, O, k0, k1, hx, hxy, wmask, mymax,
-                            mysum);
-  else
-    build_rows<2, false, T>(pos_s, cg, g, bi, rl2, nbr, kmax, cnt, err, hpos, hp, hb, ob, O, k0, k1, hx, hxy, wmask, mymax,
-                            mysum);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     const int32_t v = __shfl_down(mymax, o, 64);
@@ -867,7 +972,7 @@ template <typename T>
 hipError_t launch_build_nbr(const vec4_t<T>* pos_s, const CellGeom& cg, const BrickGeom& g, const BrickIndex& bi,
                             double rl2, uint16_t* nbr, int32_t kmax, int32_t* cnt, int32_t* err, int32_t* stats,
                             hipStream_t st) {
-  const size_t lds = (size_t)g.build_cap * sizeof(float4);
+  const size_t lds = build_lds_bytes(g, kmax);
   const unsigned grid = (unsigned)((int64_t)g.blocks * g.build_split);
   if (g.build_threads <= kBlock)
     k_build_nbr<T, kBlock><<<grid, (unsigned)g.build_threads, lds, st>>>(pos_s, cg, g, bi, rl2, nbr, kmax, cnt, err,
@@ -931,7 +1036,7 @@ hipError_t launch_build_batch(const BuildArgs* const* dev, const BuildArgs* host
       u.tab[u.k] = dev[w];
       u.blk[u.k + 1] = u.blk[u.k] + g.blocks * g.build_split;
       u.k++;
-      const size_t b = (size_t)g.build_cap * sizeof(float4);
+      const size_t b = build_lds_bytes(g, host[w].kmax);
       lds = b > lds ? b : lds;
     }
     if (u.k == 0) continue;

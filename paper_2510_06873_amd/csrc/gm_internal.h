@@ -11,7 +11,7 @@ namespace gm {
 
 constexpr int kBlock = 256;  // threads per block of the per-atom kernels (4 waves)
 constexpr int kBuildMaxThreads = 512;   // largest workgroup of the neighbour build
-constexpr int kBuildGroup = 8;          // lanes that build one atom's row together
+constexpr int kBuildAtoms = 4;          // atoms per wave below which a neighbour build splits no further
 constexpr int kBuildFillBlocks = 1024;  // workgroups a neighbour build aims for (4 per CU)
 constexpr int kBuildMaxSplit = 32;      // most workgroups sharing one brick in the build
 constexpr int kXcd = 8;      // workgroups are dealt to the 8 XCDs round-robin
@@ -93,10 +93,26 @@ struct BrickGeom {
   int32_t blocks;  // workgroups launched per brick pass (nbricks rounded up to the XCD count)
   int32_t tpa;     // threads per owned atom (1, 2 or 4): lanes that split one atom's rows
   int32_t kpart;   // length of one part's sub-row (multiple of 8 entries, 16-byte aligned)
-  int32_t build_threads;  // workgroup size of the neighbour build (kBuildGroup lanes per atom)
+  int32_t build_threads;  // workgroup size of the neighbour build
   int32_t build_split;    // workgroups per brick in the neighbour build (each takes a share of its atoms)
   int32_t build_cap;      // halo slots the neighbour build stages in LDS (slots beyond: global memory)
+  int32_t build_win;      // atoms whose rows a wave of the neighbour build collects in LDS at a time
 };
+
+// The neighbour build collects rows in LDS, kBuildWin atoms per wave (a
+// sub-row per lane: kBuildWin x 4 lanes per atom = 64) or as many as keep them
+// within kBuildRowBytes per workgroup (at least one); an odd number of words
+// per row, so that rows read side by side lie in different banks.
+constexpr int kBuildWin = 16;
+constexpr int kBuildRowBytes = 16384;
+__host__ __device__ inline int32_t build_row_width(int32_t kmax) { return (kmax + 3) / 4 * 4 + 2; }
+inline int32_t build_window(int32_t kmax, int threads) {
+  const int32_t w = kBuildRowBytes / (threads / 64 * build_row_width(kmax) * 2);
+  return w < 1 ? 1 : (w > kBuildWin ? kBuildWin : w);
+}
+inline size_t build_lds_bytes(const BrickGeom& g, int32_t kmax) {
+  return (size_t)g.build_cap * 16 + (size_t)(g.build_threads / 64 * g.build_win) * build_row_width(kmax) * 2 + 64 * 2;
+}
 
 struct BrickIndex {
   const int32_t* hb;          // [nbricks+1] first halo slot of each brick (global numbering)
