@@ -782,8 +782,8 @@ int gm_create(gm_ctx** out, const gm_params* params, int64_t n_atoms, void* hip_
   c->r_list = params->r_c + params->skin;
   int32_t km = params->max_neighbors > 0 ? params->max_neighbors : 64;
   c->kmax = (km + 3) / 4 * 4;
-  int64_t hb = (params->hill_capacity + kBlock - 1) / kBlock;
-  c->bias_blocks = (int)(hb < 1 ? 1 : (hb > 1024 ? 1024 : hb));
+  const int64_t hb = (params->hill_capacity + kBlock - 1) / kBlock;
+  c->bias_blocks = params->hill_capacity <= kBiasOne ? 1 : (int)(hb > 1024 ? 1024 : hb);
   make_ycoef(c->ycf);
   make_ycoef(c->ycd);
   {

@@ -14,71 +14,115 @@ __device__ __forceinline__ double cv_delta(double s, double c, double period) {
   return period > 0.0 ? x - period * rint(x / period) : x;
 }
 
+// Fixed-order block sums of three values at once, valid in thread 0: wave sums,
+// then the first wave adds the waves' sums.  All threads call; lds holds
+// 3 kBiasBlock / 64 doubles and is free again when the block passes its next
+// barrier.
+__device__ __forceinline__ void block_sum3(double v[3], double (*lds)[3]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, waves = (int)(blockDim.x >> 6);
+#pragma unroll
+  for (int q = 0; q < 3; q++) {
+    v[q] = wave_sum(v[q]);
+    if (lane == 0) lds[w][q] = v[q];
+  }
+  __syncthreads();
+  if (w == 0)
+#pragma unroll
+    for (int q = 0; q < 3; q++) {
+      v[q] = lane < waves ? lds[lane][q] : 0.0;
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) v[q] += __shfl_down(v[q], o, 64);
+    }
+}
+
+// V and dV/ds, or the deposit of one hill (thread 0, once per evaluation).
+__device__ __forceinline__ void bias_result(const BiasArgs& a, int64_t K, const double v[3]) {
+  if (!isfinite(v[0])) atomicOr(a.err, kErrNonFinite);
+  if (a.deposit) {
+    const double h = a.wt_scale == 0.0 ? a.w0 : a.w0 * exp(-v[0] * a.wt_scale);
+    if (K < a.capacity) {
+      for (int d = 0; d < a.dims; d++) a.centres[K * a.dims + d] = a.s[d];
+      a.heights[K] = h;
+      *a.count = K + 1;
+    } else {
+      atomicOr(a.err, kErrCapacity);
+    }
+  } else {
+    if (a.V_out) a.V_out[0] = v[0];
+    if (a.dV_out) {
+      a.dV_out[0] = v[1];
+      if (a.dims > 1) a.dV_out[1] = v[2];
+    }
+  }
+}
+
+// The sum over the hills.  One workgroup of 1,024 threads sums up to kBiasOne
+// hills and is done; more hills are shared by workgroups whose partial sums a
+// second launch adds in their order.  Latency bounds both: 2,000 hills 3.9 +
+// 2.4 us in two launches, 4.0 in one; 5,000 2-D hills 4.0 + 2.9 and 5.8.  At
+// 10,000 one workgroup, or a last-to-finish workgroup that adds the partials in
+// the same launch, takes longer (7.8 us) than the two launches (6.4).
 __device__ __forceinline__ void bias_body(const BiasArgs& a, int32_t blk, int32_t nblk) {
-  __shared__ double red[kBlock / 64];
+  static_assert(kBiasBlock / 64 <= 16, "block_sum3 adds 16 waves");
+  __shared__ double red[kBiasBlock / 64][3];
   const int64_t K = *a.count;
   double s[2] = {a.s[0], a.dims > 1 ? a.s[1] : 0.0};
-  double v = 0.0, g0 = 0.0, g1 = 0.0;
-  const int64_t stride = (int64_t)nblk * blockDim.x;
-  for (int64_t k = (int64_t)blk * blockDim.x + threadIdx.x; k < K; k += stride) {
-    const double x0 = cv_delta(s[0], a.centres[k * a.dims], a.period[0]);
-    double arg = x0 * x0 * a.inv2s2[0];
-    double x1 = 0.0;
-    if (a.dims > 1) {
-      x1 = cv_delta(s[1], a.centres[k * a.dims + 1], a.period[1]);
-      arg += x1 * x1 * a.inv2s2[1];
+  double v[3] = {0.0, 0.0, 0.0};  // V, dV/ds
+  // up to 4 hills per thread and round, loaded as one batch (the last hill in
+  // the place of those past the end, which add zero); several workgroups use
+  // kBlock threads each, however many a batched launch gives them
+  const int32_t threads = nblk > 1 ? kBlock : kBiasBlock;
+  const int64_t stride = (int64_t)nblk * threads;
+  const int64_t mine = (int32_t)threadIdx.x < threads ? (int64_t)blk * threads + threadIdx.x : K;
+  for (int64_t k0 = mine; k0 < K; k0 += 4 * stride) {
+    double c0[4], c1[4], h[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int64_t k = k0 + u * stride < K ? k0 + u * stride : K - 1;
+      c0[u] = a.centres[k * a.dims];
+      c1[u] = a.dims > 1 ? a.centres[k * a.dims + 1] : 0.0;
+      h[u] = a.heights[k];
     }
-    const double e = a.heights[k] * exp(-arg);
-    v += e;
-    g0 -= e * x0 * a.invs2[0];
-    g1 -= e * x1 * a.invs2[1];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      if (k0 + u * stride >= K) break;
+      const double x0 = cv_delta(s[0], c0[u], a.period[0]);
+      double arg = x0 * x0 * a.inv2s2[0];
+      double x1 = 0.0;
+      if (a.dims > 1) {
+        x1 = cv_delta(s[1], c1[u], a.period[1]);
+        arg += x1 * x1 * a.inv2s2[1];
+      }
+      const double e = h[u] * exp(-arg);
+      v[0] += e;
+      v[1] -= e * x0 * a.invs2[0];
+      v[2] -= e * x1 * a.invs2[1];
+    }
   }
-  v = block_sum(v, red);
-  g0 = block_sum(g0, red);
-  if (a.dims > 1) g1 = block_sum(g1, red);
-  if (threadIdx.x == 0) {
-    a.part[blk * 3 + 0] = v;
-    a.part[blk * 3 + 1] = g0;
-    a.part[blk * 3 + 2] = g1;
+  block_sum3(v, red);
+  if (threadIdx.x != 0) return;
+  if (nblk == 1) {
+    bias_result(a, K, v);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 3; q++) a.part[blk * 3 + q] = v[q];
   }
 }
 
-// Fixed-order sum of the bias partials (its own launch); V and dV/ds, or the
-// deposit of one hill.
+// Fixed-order sum of the partials of an evaluation by more than one workgroup.
 __device__ __forceinline__ void bias_finish_body(const BiasArgs& a, int32_t nblk) {
-  __shared__ double red[kBlock / 64];
+  __shared__ double red[kBlock / 64][3];
+  if (nblk == 1) return;
   const int64_t K = *a.count;
-  double V = 0.0, G0 = 0.0, G1 = 0.0;
-  for (int64_t i = threadIdx.x; i < (int64_t)nblk; i += blockDim.x) {
-    V += a.part[i * 3 + 0];
-    G0 += a.part[i * 3 + 1];
-    G1 += a.part[i * 3 + 2];
-  }
-  V = block_sum(V, red);
-  G0 = block_sum(G0, red);
-  if (a.dims > 1) G1 = block_sum(G1, red);
-  if (threadIdx.x == 0) {
-    if (!isfinite(V)) atomicOr(a.err, kErrNonFinite);
-    if (a.deposit) {
-      const double h = a.wt_scale == 0.0 ? a.w0 : a.w0 * exp(-V * a.wt_scale);
-      if (K < a.capacity) {
-        for (int d = 0; d < a.dims; d++) a.centres[K * a.dims + d] = a.s[d];
-        a.heights[K] = h;
-        *a.count = K + 1;
-      } else {
-        atomicOr(a.err, kErrCapacity);
-      }
-    } else {
-      if (a.V_out) a.V_out[0] = V;
-      if (a.dV_out) {
-        a.dV_out[0] = G0;
-        if (a.dims > 1) a.dV_out[1] = G1;
-      }
-    }
-  }
+  double v[3] = {0.0, 0.0, 0.0};
+  for (int32_t i = threadIdx.x; i < nblk; i += blockDim.x)
+#pragma unroll
+    for (int q = 0; q < 3; q++) v[q] += a.part[i * 3 + q];
+  block_sum3(v, red);
+  if (threadIdx.x == 0) bias_result(a, K, v);
 }
 
-__global__ __launch_bounds__(kBlock) void k_bias(BiasArgs a) { bias_body(a, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(kBiasBlock) void k_bias(BiasArgs a) { bias_body(a, blockIdx.x, gridDim.x); }
 
 __global__ __launch_bounds__(kBlock) void k_bias_finish(BiasArgs a, int32_t nblk) { bias_finish_body(a, nblk); }
 
@@ -90,8 +134,8 @@ __global__ __launch_bounds__(kBlock) void k_bias_finish_batch(const BiasArgs* __
 
 // One launch for many walkers: workgroup g serves walker w with
 // blk_start[w] <= g < blk_start[w+1].
-__global__ __launch_bounds__(kBlock) void k_bias_batch(const BiasArgs* __restrict__ tab,
-                                                       const int32_t* __restrict__ blk_start, int32_t W) {
+__global__ __launch_bounds__(kBiasBlock) void k_bias_batch(const BiasArgs* __restrict__ tab,
+                                                           const int32_t* __restrict__ blk_start, int32_t W) {
   const int64_t g = blockIdx.x;
   int32_t lo = 0, hi = W;
   while (hi - lo > 1) {
@@ -103,13 +147,13 @@ __global__ __launch_bounds__(kBlock) void k_bias_batch(const BiasArgs* __restric
 
 hipError_t launch_bias_batch(const BiasArgs* tab, const int32_t* blk_start, int32_t W, int32_t blocks,
                              hipStream_t st) {
-  k_bias_batch<<<(unsigned)blocks, kBlock, 0, st>>>(tab, blk_start, W);
-  k_bias_finish_batch<<<(unsigned)W, kBlock, 0, st>>>(tab, blk_start);
+  k_bias_batch<<<(unsigned)blocks, kBiasBlock, 0, st>>>(tab, blk_start, W);
+  if (blocks > W) k_bias_finish_batch<<<(unsigned)W, kBlock, 0, st>>>(tab, blk_start);
   return hipGetLastError();
 }
 
 // The same for a subset of a batch's walkers named by value.
-__global__ __launch_bounds__(kBlock) void k_bias_subset(BiasSubset s) {
+__global__ __launch_bounds__(kBiasBlock) void k_bias_subset(BiasSubset s) {
   const int32_t g = blockIdx.x;
   int32_t lo = 0, hi = s.k;
   while (hi - lo > 1) {
@@ -126,8 +170,8 @@ __global__ __launch_bounds__(kBlock) void k_bias_finish_subset(BiasSubset s) {
 
 hipError_t launch_bias_subset(const BiasSubset& s, hipStream_t st) {
   if (s.k < 1) return hipSuccess;
-  k_bias_subset<<<(unsigned)s.blk[s.k], kBlock, 0, st>>>(s);
-  k_bias_finish_subset<<<(unsigned)s.k, kBlock, 0, st>>>(s);
+  k_bias_subset<<<(unsigned)s.blk[s.k], kBiasBlock, 0, st>>>(s);
+  if (s.blk[s.k] > s.k) k_bias_finish_subset<<<(unsigned)s.k, kBlock, 0, st>>>(s);
   return hipGetLastError();
 }
 
@@ -157,8 +201,8 @@ hipError_t launch_batch_values(const double* const* tab, int32_t W, double* s, d
 }
 
 hipError_t launch_bias(const BiasArgs& a, int blocks, hipStream_t st) {
-  k_bias<<<(unsigned)blocks, kBlock, 0, st>>>(a);
-  k_bias_finish<<<1, kBlock, 0, st>>>(a, blocks);
+  k_bias<<<(unsigned)blocks, blocks > 1 ? kBlock : kBiasBlock, 0, st>>>(a);
+  if (blocks > 1) k_bias_finish<<<1, kBlock, 0, st>>>(a, blocks);
   return hipGetLastError();
 }
 

@@ -14,6 +14,8 @@ constexpr int kBuildMaxThreads = 512;   // largest workgroup of the neighbour bu
 constexpr int kBuildAtoms = 4;          // atoms per wave below which a neighbour build splits no further
 constexpr int kBuildFillBlocks = 1024;  // workgroups a neighbour build aims for (4 per CU)
 constexpr int kBuildMaxSplit = 32;      // most workgroups sharing one brick in the build
+constexpr int kBiasBlock = 1024;        // threads of a block that sums every hill alone
+constexpr int kBiasOne = 8192;          // hills up to which one block sums them
 constexpr int kXcd = 8;      // workgroups are dealt to the 8 XCDs round-robin
 constexpr int32_t kMaxTorsions = 1 << 16;   // torsion forces are summed by one workgroup in order
 constexpr int64_t kMaxFesBins = 1 << 24;
