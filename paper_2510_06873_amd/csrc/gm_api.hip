@@ -38,7 +38,7 @@ struct gm_ctx {
   int32_t* scan_tmp = nullptr;  // tile sums of the prefix scans
   // bricks
   int32_t *brick_H = nullptr, *brick_O = nullptr, *brick_hb = nullptr, *brick_ob = nullptr, *brick_hp = nullptr;
-  int32_t *halo_rank = nullptr, *owned_slot = nullptr, *owned_rank = nullptr, *owned_hcell = nullptr;
+  int32_t *halo_rank = nullptr, *halo_id = nullptr, *owned_slot = nullptr, *owned_rank = nullptr, *owned_hcell = nullptr;
   // neighbour rows and the per-step in-cutoff rows (16-bit halo slots)
   uint16_t *nbr = nullptr, *cut = nullptr;
   int32_t *cnt = nullptr, *ccnt = nullptr, *err = nullptr, *stats = nullptr;
@@ -47,6 +47,7 @@ struct gm_ctx {
   double *part_a = nullptr, *part_b = nullptr, *s_int = nullptr, *V_int = nullptr, *dV_int = nullptr;
   double *centres = nullptr, *heights = nullptr, *bias_part = nullptr;
   int64_t* hill_count = nullptr;
+  int32_t* ticket = nullptr;  // of the CV sum, zero between launches
   BuildArgs* build_dev = nullptr;  // this context's rebuild arguments in device memory (batched rebuilds)
   BuildArgs build_host;            // what build_dev holds (compared before re-uploading)
   bool build_dev_ok = false;
@@ -54,8 +55,9 @@ struct gm_ctx {
   unsigned char* arena = nullptr;  // the fixed-size buffers below, carved from one allocation
   // buffers that grow or go together, one allocation each: the neighbour and
   // in-cutoff rows; the q-hat and adjoint rows; the cell tables (counts,
-  // starts, scan tiles); the brick tables and per-workgroup partials
-  unsigned char *rows_blk = nullptr, *qg_blk = nullptr, *cells_blk = nullptr, *bricks_blk = nullptr;
+  // starts, scan tiles); the brick tables and per-workgroup partials; the halo
+  // slots' ranks and atoms
+  unsigned char *rows_blk = nullptr, *qg_blk = nullptr, *cells_blk = nullptr, *bricks_blk = nullptr, *halo_blk = nullptr;
   std::unordered_map<void*, size_t> held;  // device allocations of the context and their sizes
   size_t held_bytes = 0;
   bool built = false, fwd = false, bwd = false;
@@ -441,6 +443,7 @@ BrickIndex brick_index(gm_ctx* c) {
   bi.ob = c->brick_ob;
   bi.hp = c->brick_hp;
   bi.halo_rank = c->halo_rank;
+  bi.halo_id = c->halo_id;
   bi.owned_slot = c->owned_slot;
   bi.owned_rank = c->owned_rank;
   bi.owned_hcell = c->owned_hcell;
@@ -451,7 +454,7 @@ template <typename T>
 CvArgs<T> make_args(gm_ctx* c) {
   CvArgs<T> a;
   memset(&a, 0, sizeof(a));
-  a.pos_s = reinterpret_cast<const vec4_t<T>*>(c->pos_s);
+  a.pos_s = reinterpret_cast<vec4_t<T>*>(c->pos_s);
   a.nbr = c->nbr;
   a.cnt = c->cnt;
   a.cut = c->cut;
@@ -491,6 +494,7 @@ CvArgs<T> make_args(gm_ctx* c) {
   a.cn_grad = reinterpret_cast<T*>(c->cn_grad);
   a.part_a = c->part_a;
   a.part_b = c->part_b;
+  a.ticket = c->bg.blocks <= kFuseFinish ? c->ticket : nullptr;
   a.s_int = c->s_int;
   a.err = c->err;
   return a;
@@ -680,7 +684,8 @@ void free_all(gm_ctx* c) {
   dfree_c(c, c->qg_blk);
   dfree_c(c, c->cells_blk);
   dfree_c(c, c->bricks_blk);
-  dfree_c(c, c->halo_rank);
+  dfree_c(c, c->halo_blk);
+  c->halo_rank = c->halo_id = nullptr;
   c->cell = c->perm = c->owned_slot = c->owned_rank = c->owned_hcell = c->cnt = c->ccnt = nullptr;
   c->err = c->stats = nullptr;
   c->order = nullptr;
@@ -688,6 +693,7 @@ void free_all(gm_ctx* c) {
   c->s_int = c->V_int = c->dV_int = c->centres = c->heights = c->bias_part = nullptr;
   c->part_a = c->part_b = nullptr;
   c->hill_count = nullptr;
+  c->ticket = nullptr;
   c->nbr = c->cut = nullptr;
   c->count = c->start = c->scan_tmp = nullptr;
   c->brick_H = c->brick_O = c->brick_hb = c->brick_ob = c->brick_hp = nullptr;
@@ -726,8 +732,9 @@ static int ensure_rows(gm_ctx* c) {
 template <typename T>
 static int cv_forward_t(gm_ctx* c, const float* pos4, double* s_dev) {
   hipStream_t st = c->stream;
-  GM_TRY(hip_rc(launch_gather<T>(gather_args(c, pos4), st)));
   CvArgs<T> a = make_args<T>(c);
+  if (!c->halo_id) GM_TRY(hip_rc(launch_gather<T>(gather_args(c, pos4), st)));
+  a.pos_in = reinterpret_cast<const float4*>(pos4);
   a.s_out = s_dev;
   if (c->has_q6) return hip_rc(launch_q6_forward<T>(a, c->has_cn, st));
   return hip_rc(launch_cn_forward<T>(a, st));
@@ -817,6 +824,7 @@ int gm_create(gm_ctx** out, const gm_params* params, int64_t n_atoms, void* hip_
   const Piece pieces[] = {
       {(void**)&c->s_int, 16},       {(void**)&c->V_int, 16},      {(void**)&c->dV_int, 16},
       {(void**)&c->err, 16},         {(void**)&c->stats, 32},      {(void**)&c->hill_count, 16},
+      {(void**)&c->ticket, 16},
       {(void**)&c->nb, n * T},       {(void**)&c->cn_atom, n * T},  // zeroed up to here
       {(void**)&c->cell, n * 4},     {(void**)&c->perm, n * 4},    {(void**)&c->owned_slot, n * 4},
       {(void**)&c->owned_rank, n * 4}, {(void**)&c->owned_hcell, n * 4}, {(void**)&c->cnt, n * 4},
@@ -827,7 +835,7 @@ int gm_create(gm_ctx** out, const gm_params* params, int64_t n_atoms, void* hip_
       {(void**)&c->bias_part, (size_t)c->bias_blocks * 3 * 8},
       {(void**)&c->build_dev, sizeof(BuildArgs)},
   };
-  int rc = carve(c, &c->arena, pieces, (int)(sizeof(pieces) / sizeof(pieces[0])), 8);
+  int rc = carve(c, &c->arena, pieces, (int)(sizeof(pieces) / sizeof(pieces[0])), 9);
   if (rc == GM_OK && !c->external) rc = alloc_rows(c);
   if (rc == GM_OK && c->has_q6) rc = ensure_rows(c);
   if (rc != GM_OK) {
@@ -873,9 +881,11 @@ static int reserve_bricks(gm_ctx* c) {
     c->blocks_cap = np;
   }
   if (grow_h) {
-    dfree_c(c, c->halo_rank);
+    dfree_c(c, c->halo_blk);
+    c->halo_rank = c->halo_id = nullptr;
     c->halo_cap = 0;
-    GM_TRY(dalloc_c(c, &c->halo_rank, (size_t)hbound * 4));
+    const Piece pieces[] = {{(void**)&c->halo_rank, (size_t)hbound * 4}, {(void**)&c->halo_id, (size_t)hbound * 4}};
+    GM_TRY(carve(c, &c->halo_blk, pieces, c->n <= kFuseGather ? 2 : 1));
     c->halo_cap = hbound;
   }
   return GM_OK;
@@ -906,6 +916,7 @@ int prepare_build(gm_ctx* c, const float* pos4, const double* box) {
     const Piece pieces[] = {{(void**)&c->count, (size_t)ncells * 4}, {(void**)&c->start, (size_t)(ncells + 1) * 4},
                             {(void**)&c->scan_tmp, (size_t)tiles * 4}};
     GM_TRY(carve(c, &c->cells_blk, pieces, 3));
+    GM_TRY(hip_rc(launch_fill_i32(c->count, 0, ncells, c->stream)));  // zero between rebuilds
     c->ncells_cap = ncells;
   }
   c->ncells = ncells;
@@ -928,32 +939,25 @@ int prepare_build(gm_ctx* c, const float* pos4, const double* box) {
 int enqueue_build(gm_ctx* c, const float* pos4, hipStream_t st) {
   const int64_t ncells = c->ncells;
   const float4* p4 = reinterpret_cast<const float4*>(pos4);
-  // cell counts, list statistics and the out-of-box flag (see the gather)
-  GM_TRY(hip_rc(launch_reset_build(c->count, ncells, c->stats, c->err, st)));
   // each atom's slot in its cell goes to owned_slot and the scatter to
   // owned_rank (both rewritten by the brick fill below), then the rank by id
-  GM_TRY(hip_rc(launch_cell_ids(p4, c->n, c->geom, c->cell, c->count, c->owned_slot, c->err, st)));
-  GM_TRY(hip_rc(launch_scan(c->count, ncells, c->start, nullptr, c->scan_tmp, st)));
-  GM_TRY(hip_rc(launch_scatter(c->cell, c->n, c->start, c->owned_slot, c->owned_rank, st)));
-  GM_TRY(hip_rc(launch_rank_cells(c->cell, c->start, c->owned_rank, c->n, c->perm, st)));
-  // bricks: halo and owned sizes, their prefix sums, the slot tables
-  GM_TRY(hip_rc(launch_brick_count(c->start, c->bg, c->brick_H, c->brick_O, st)));
-  GM_TRY(hip_rc(launch_scan2(c->brick_H, c->brick_hb, c->brick_O, c->brick_ob, c->bg.nbricks, c->scan_tmp, st)));
+  GM_TRY(hip_rc(launch_cell_ids(p4, c->n, c->geom, c->cell, c->count, c->owned_slot, c->stats, c->err, st)));
+  GM_TRY(hip_rc(launch_scan(c->count, ncells, c->start, true, c->scan_tmp, st)));
+  GM_TRY(hip_rc(launch_scatter_count(c->cell, c->n, c->start, c->owned_slot, c->owned_rank, c->bg, c->brick_H,
+                                     c->brick_O, st)));
+  GM_TRY(hip_rc(launch_rank_scan(c->cell, c->start, c->owned_rank, c->n, c->perm, c->bg, c->brick_H, c->brick_hb,
+                                 c->brick_O, c->brick_ob, c->scan_tmp, st)));
   const BrickIndex bi = brick_index(c);
-  GM_TRY(hip_rc(launch_brick_fill(c->start, c->bg, bi, c->brick_hp, c->halo_rank, c->owned_slot, c->owned_rank,
-                                  c->owned_hcell, c->err, st)));
+  GM_TRY(hip_rc((c->fp64 ? launch_fill_gather<double> : launch_fill_gather<float>)(
+      c->start, c->bg, bi, c->perm, c->brick_hp, c->halo_rank, c->halo_id, c->owned_slot, c->owned_rank, c->owned_hcell,
+      c->err, gather_args(c, pos4), st)));
   const double rl2 = c->r_list * c->r_list;
-  if (c->fp64) {
-    auto* ps = reinterpret_cast<double4*>(c->pos_s);
-    GM_TRY(hip_rc(launch_gather<double>(gather_args(c, pos4), st)));
-    GM_TRY(hip_rc(launch_build_nbr<double>(ps, c->geom, c->bg, bi, rl2, c->nbr, c->kmax, c->cnt, c->err, c->stats,
-                                           st)));
-  } else {
-    auto* ps = reinterpret_cast<float4*>(c->pos_s);
-    GM_TRY(hip_rc(launch_gather<float>(gather_args(c, pos4), st)));
-    GM_TRY(hip_rc(launch_build_nbr<float>(ps, c->geom, c->bg, bi, rl2, c->nbr, c->kmax, c->cnt, c->err, c->stats,
-                                          st)));
-  }
+  if (c->fp64)
+    GM_TRY(hip_rc(launch_build_nbr<double>(reinterpret_cast<double4*>(c->pos_s), c->geom, c->bg, bi, rl2, c->nbr,
+                                           c->kmax, c->cnt, c->err, c->stats, st)));
+  else
+    GM_TRY(hip_rc(launch_build_nbr<float>(reinterpret_cast<float4*>(c->pos_s), c->geom, c->bg, bi, rl2, c->nbr, c->kmax,
+                                          c->cnt, c->err, c->stats, st)));
   return GM_OK;
 }
 
@@ -981,6 +985,7 @@ BuildArgs build_args(gm_ctx* c, const float* pos4) {
   a.brick_ob = c->brick_ob;
   a.brick_hp = c->brick_hp;
   a.halo_rank = c->halo_rank;
+  a.halo_id = c->halo_id;
   a.owned_slot = c->owned_slot;
   a.owned_rank = c->owned_rank;
   a.owned_hcell = c->owned_hcell;
@@ -997,7 +1002,11 @@ extern "C" {
 
 int gm_build_neighbors(gm_ctx* c, const float* pos4, const double* box) {
   GM_TRY(prepare_build(c, pos4, box));
-  GM_TRY(enqueue_build(c, pos4, c->stream));
+  const int rc = enqueue_build(c, pos4, c->stream);
+  if (rc != GM_OK) {
+    c->ncells_cap = 0;  // the counts may be left unscanned: allocate and clear them again
+    return rc;
+  }
   c->built = true;
   c->version++;
   return GM_OK;
@@ -1233,6 +1242,7 @@ struct gm_batch {
     void *d_cv = nullptr, *d_gather = nullptr, *d_bias = nullptr, *d_dep = nullptr;
     void *d_blk_cv = nullptr, *d_blk_gather = nullptr, *d_blk_bias = nullptr;
     int32_t blocks_cv = 0, blocks_gather = 0, blocks_bias = 0, cap = 0;
+    bool gather = true, finish = true;  // some member needs the gather / the separate finish of its sum
     // capacities of the device tables (kept across membership changes)
     size_t c_cv = 0, c_ga = 0, c_bi = 0, c_de = 0, c_bcv = 0, c_bga = 0, c_bbi = 0;
   };
@@ -1288,6 +1298,7 @@ int refresh_group(gm_batch* B, gm_batch::Group& g, bool force) {
   std::vector<int32_t> bcv{0}, bga{0}, bbi{0};
   std::vector<unsigned char> cv, ga, bi, de;
   g.cap = 0;
+  g.gather = g.finish = false;
   for (size_t i = 0; i < W; i++) {
     const int m = g.members[i];
     gm_ctx* c = B->walkers[m];
@@ -1297,6 +1308,7 @@ int refresh_group(gm_batch* B, gm_batch::Group& g, bool force) {
     if (force || e.serial != c->serial || e.version != c->version || e.pos != B->pos[m] || e.force != B->force[m]) {
       CvArgs<T> a = make_args<T>(c);
       a.s_out = nullptr;
+      a.pos_in = reinterpret_cast<const float4*>(B->pos[m]);
       a.seed = c->dV_int;
       a.mode = 0;
       a.out4 = B->force[m];
@@ -1324,6 +1336,8 @@ int refresh_group(gm_batch* B, gm_batch::Group& g, bool force) {
     bga.push_back(bga.back() + (int32_t)((c->n + kBlock - 1) / kBlock));
     bbi.push_back(bbi.back() + c->bias_blocks);
     g.cap = c->bg.cap > g.cap ? c->bg.cap : g.cap;
+    g.gather = g.gather || !c->halo_id;
+    g.finish = g.finish || c->bg.blocks > kFuseFinish;
   }
   g.blocks_cv = bcv.back();
   g.blocks_gather = bga.back();
@@ -1356,21 +1370,22 @@ int batch_step_t(gm_batch* B) {
     const auto* bcv = static_cast<const int32_t*>(g.d_blk_cv);
     const bool q6 = g.kind != GM_CV_COORD, cn = g.kind != GM_CV_Q6COUNT;
     hipStream_t st = B->stream;
-    GM_TRY(hip_rc(launch_gather_batch<T>(reinterpret_cast<const GatherArgs*>(g.d_gather),
-                                         static_cast<const int32_t*>(g.d_blk_gather), W, g.blocks_gather, st)));
+    const auto* bga = static_cast<const int32_t*>(g.d_blk_gather);
+    if (g.gather)
+      GM_TRY(hip_rc(launch_gather_batch<T>(reinterpret_cast<const GatherArgs*>(g.d_gather), bga, W, g.blocks_gather, st)));
     if (q6) {
-      GM_TRY(hip_rc(launch_pass_batch<T>(1, cn, true, tab, bcv, W, g.blocks_cv, g.cap, st)));
-      GM_TRY(hip_rc(launch_pass_batch<T>(2, cn, true, tab, bcv, W, g.blocks_cv, g.cap, st)));
+      GM_TRY(hip_rc(launch_pass_batch<T>(1, cn, tab, bcv, W, g.blocks_cv, g.cap, !g.gather, false, st)));
+      GM_TRY(hip_rc(launch_pass_batch<T>(2, cn, tab, bcv, W, g.blocks_cv, g.cap, false, g.finish, st)));
     } else {
-      GM_TRY(hip_rc(launch_pass_batch<T>(5, true, false, tab, bcv, W, g.blocks_cv, g.cap, st)));
+      GM_TRY(hip_rc(launch_pass_batch<T>(5, true, tab, bcv, W, g.blocks_cv, g.cap, !g.gather, g.finish, st)));
     }
     GM_TRY(hip_rc(launch_bias_batch(reinterpret_cast<const BiasArgs*>(g.d_bias),
                                     static_cast<const int32_t*>(g.d_blk_bias), W, g.blocks_bias, st)));
     if (q6) {
-      GM_TRY(hip_rc(launch_pass_batch<T>(3, cn, true, tab, bcv, W, g.blocks_cv, g.cap, st)));
-      GM_TRY(hip_rc(launch_pass_batch<T>(4, cn, true, tab, bcv, W, g.blocks_cv, g.cap, st)));
+      GM_TRY(hip_rc(launch_pass_batch<T>(3, cn, tab, bcv, W, g.blocks_cv, g.cap, false, false, st)));
+      GM_TRY(hip_rc(launch_pass_batch<T>(4, cn, tab, bcv, W, g.blocks_cv, g.cap, false, false, st)));
     } else {
-      GM_TRY(hip_rc(launch_pass_batch<T>(6, true, false, tab, bcv, W, g.blocks_cv, g.cap, st)));
+      GM_TRY(hip_rc(launch_cn_force_batch<T>(tab, bga, W, g.blocks_gather, st)));
     }
     for (int m : g.members) {
       gm_ctx* c = B->walkers[m];
@@ -1652,8 +1667,12 @@ int batch_build(gm_batch* B, const int32_t* which, int32_t count, const double* 
     gm_batch* B;
     const int32_t* which;
     int32_t count;
+    bool done = false;
     ~Restore() {
-      for (int32_t i = 0; i < count; i++) B->walkers[which[i]]->stream = B->stream;
+      for (int32_t i = 0; i < count; i++) {
+        B->walkers[which[i]]->stream = B->stream;
+        if (!done) B->walkers[which[i]]->ncells_cap = 0;  // counts that may be left unscanned are allocated again
+      }
     }
   } restore{B, which, count};
   for (int32_t i = 0; i < count; i++) B->walkers[which[i]]->stream = st;
@@ -1689,6 +1708,7 @@ int batch_build(gm_batch* B, const int32_t* which, int32_t count, const double* 
     c->built = true;
     c->version++;
   }
+  restore.done = true;
   return GM_OK;
 }
 

@@ -74,9 +74,15 @@ __device__ __forceinline__ int32_t wave_count_add(int32_t* base, int32_t key) {
 
 // Cell of atom i, its count, and its slot within the cell (the count it saw:
 // unique per atom, in arrival order), which the scatter uses after the scan.
+// The first launch of a rebuild: it also clears the list statistics and the
+// out-of-box flag.  The counts are zero between rebuilds (the scan that reads
+// them clears them).
 __device__ __forceinline__ void cell_ids_body(const float4* __restrict__ pos, int64_t n, const CellGeom& g,
                                               int32_t* __restrict__ cell, int32_t* __restrict__ count,
-                                              int32_t* __restrict__ slot, int32_t* err, int64_t i) {
+                                              int32_t* __restrict__ slot, int32_t* __restrict__ stats, int32_t* err,
+                                              int64_t i) {
+  if (i < 4) stats[i] = 0;
+  if (i == 0) err[1] = 0;
   if (i >= n) return;
   int32_t c[3];
   if (!cell_coords(pos[i], g, c)) atomicOr(err, kErrNonFinite);
@@ -88,29 +94,33 @@ __device__ __forceinline__ void cell_ids_body(const float4* __restrict__ pos, in
 __global__ __launch_bounds__(kBlock) void k_cell_ids(const float4* __restrict__ pos, int64_t n,
                                                      CellGeom g, int32_t* __restrict__ cell,
                                                      int32_t* __restrict__ count, int32_t* __restrict__ slot,
-                                                     int32_t* err) {
-  cell_ids_body(pos, n, g, cell, count, slot, err, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+                                                     int32_t* __restrict__ stats, int32_t* err) {
+  cell_ids_body(pos, n, g, cell, count, slot, stats, err, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // Exclusive prefix sum of n int32 values, out[n] = total, in three launches:
 // tile sums (1024 values per workgroup), a scan of the tile sums in one
-// workgroup, and the scan of each tile from its offset.  If zero != NULL it is
-// cleared alongside (the scatter cursors of the cell sort).
+// workgroup, and the scan of each tile from its offset, which also clears the
+// input where CLEAR asks for it.
 constexpr int kScanTile = 1024;
 
-__device__ __forceinline__ int32_t block_scan_incl(int32_t v, int32_t* lds) {
-  const int tid = threadIdx.x;
-  lds[tid] = v;
-  __syncthreads();
-  for (int off = 1; off < (int)blockDim.x; off <<= 1) {
-    const int32_t u = tid >= off ? lds[tid - off] : 0;
-    __syncthreads();
-    lds[tid] += u;
-    __syncthreads();
+// Inclusive prefix sum of v over the workgroup's threads in thread order
+// (blockDim.x a multiple of 64): shuffle scans within each wave, then each wave
+// adds the totals of the waves before it.  All threads call; wsum holds
+// blockDim.x / 64 ints of LDS.
+__device__ __forceinline__ int32_t block_scan_incl(int32_t v, int32_t* wsum) {
+  const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t u = __shfl_up(v, o, 64);
+    if (lane >= o) v += u;
   }
-  const int32_t r = lds[tid];
+  if (lane == 63) wsum[w] = v;
   __syncthreads();
-  return r;
+  int32_t add = 0;
+  for (int i = 0; i < w; i++) add += wsum[i];
+  __syncthreads();
+  return v + add;
 }
 
 __global__ __launch_bounds__(kScanTile) void k_tile_sums(const int32_t* __restrict__ in, int64_t n,
@@ -124,7 +134,7 @@ __global__ __launch_bounds__(kScanTile) void k_tile_sums(const int32_t* __restri
 
 __global__ __launch_bounds__(kScanTile) void k_scan_sums(int32_t* __restrict__ sums, int64_t ntiles,
                                                          int32_t* __restrict__ out, int64_t n) {
-  __shared__ int32_t lds[kScanTile];
+  __shared__ int32_t lds[kScanTile / 64];
   __shared__ int32_t total;
   int32_t carry = 0;
   for (int64_t base = 0; base < ntiles; base += kScanTile) {
@@ -140,72 +150,77 @@ __global__ __launch_bounds__(kScanTile) void k_scan_sums(int32_t* __restrict__ s
   if (threadIdx.x == 0) out[n] = carry;
 }
 
-__global__ __launch_bounds__(kScanTile) void k_scan_tiles(const int32_t* __restrict__ in, int64_t n,
-                                                          const int32_t* __restrict__ offs, int32_t* __restrict__ out,
-                                                          int32_t* __restrict__ zero) {
-  __shared__ int32_t lds[kScanTile];
+template <bool CLEAR>
+__global__ __launch_bounds__(kScanTile) void k_scan_tiles(int32_t* __restrict__ in, int64_t n,
+                                                          const int32_t* __restrict__ offs,
+                                                          int32_t* __restrict__ out) {
+  __shared__ int32_t lds[kScanTile / 64];
   const int64_t i = (int64_t)blockIdx.x * kScanTile + threadIdx.x;
   const int32_t v = i < n ? in[i] : 0;
   const int32_t incl = block_scan_incl(v, lds);
   if (i < n) {
     out[i] = offs[blockIdx.x] + incl - v;
-    if (zero) zero[i] = 0;
+    if (CLEAR) in[i] = 0;
   }
 }
 
-// Exclusive scan of up to two short arrays (n <= kScanSmall each) in one
-// workgroup: each thread sums a contiguous chunk, the chunk sums are scanned
-// in LDS, and each thread writes its chunk's prefixes; out[n] = total and
-// zero (if given) is cleared alongside.
+// Exclusive scan of a short array (n <= kScanSmall) in one workgroup: each
+// thread sums a contiguous chunk, the chunk sums are scanned, and each thread
+// writes its chunk's prefixes; out[n] = total.
 constexpr int kScanSmall = 16 * kScanTile;
 
-__device__ __forceinline__ void scan_small_one(const int32_t* __restrict__ in, int64_t n, int32_t* __restrict__ out,
-                                               int32_t* __restrict__ zero, int32_t* lds) {
-  const int64_t chunk = (n + kScanTile - 1) / kScanTile;  // <= kScanSmall / kScanTile
-  const int64_t lo = threadIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
-  // the chunk goes to registers in one batch of independent loads (a loop
-  // of loads and sums waits for each load in turn)
-  constexpr int kMaxChunk = kScanSmall / kScanTile;
-  int32_t v[kMaxChunk];
+template <bool CLEAR>
+__device__ __forceinline__ void scan_small_one(int32_t* __restrict__ in, int64_t n, int32_t* __restrict__ out,
+                                               int32_t* lds) {
+  // chunks of whole 16-byte pieces, loaded as one batch (a loop of loads and
+  // sums waits for each load in turn); the arrays are 256-byte aligned
+  constexpr int kPieces = kScanSmall / kScanTile / 4;
+  const int64_t pieces = (n + 4 * kScanTile - 1) / (4 * kScanTile);  // per thread, <= kPieces
+  const int64_t lo = threadIdx.x * pieces * 4;
+  int4 v[kPieces];
 #pragma unroll
-  for (int j = 0; j < kMaxChunk; j++) v[j] = lo + j < hi ? in[lo + j] : 0;
+  for (int j = 0; j < kPieces; j++) {
+    const int64_t i = lo + 4 * j;
+    v[j] = make_int4(0, 0, 0, 0);
+    if (j < pieces && i + 3 < n) {
+      v[j] = *reinterpret_cast<const int4*>(in + i);
+    } else if (j < pieces) {
+      if (i < n) v[j].x = in[i];
+      if (i + 1 < n) v[j].y = in[i + 1];
+      if (i + 2 < n) v[j].z = in[i + 2];
+    }
+  }
   int32_t sum = 0;
 #pragma unroll
-  for (int j = 0; j < kMaxChunk; j++) sum += v[j];
+  for (int j = 0; j < kPieces; j++) sum += (v[j].x + v[j].y) + (v[j].z + v[j].w);
   const int32_t incl = block_scan_incl(sum, lds);
   int32_t run = incl - sum;
 #pragma unroll
-  for (int j = 0; j < kMaxChunk; j++) {
-    if (lo + j < hi) {
-      out[lo + j] = run;
-      if (zero) zero[lo + j] = 0;
+  for (int j = 0; j < kPieces; j++) {
+    const int64_t i = lo + 4 * j;
+    const int4 e = make_int4(run, run + v[j].x, run + v[j].x + v[j].y, run + v[j].x + v[j].y + v[j].z);
+    run = e.w + v[j].w;
+    if (j < pieces && i + 3 < n) {
+      *reinterpret_cast<int4*>(out + i) = e;
+      if (CLEAR) *reinterpret_cast<int4*>(in + i) = make_int4(0, 0, 0, 0);
+    } else if (j < pieces) {
+      const int32_t w[3] = {e.x, e.y, e.z};
+#pragma unroll
+      for (int q = 0; q < 3; q++)
+        if (i + q < n) {
+          out[i + q] = w[q];
+          if (CLEAR) in[i + q] = 0;
+        }
     }
-    run += v[j];
   }
   if (threadIdx.x == kScanTile - 1) out[n] = incl;
 }
 
-__global__ __launch_bounds__(kScanTile) void k_scan_small(const int32_t* __restrict__ in0, int64_t n0,
-                                                          int32_t* __restrict__ out0, int32_t* __restrict__ zero0,
-                                                          const int32_t* __restrict__ in1, int64_t n1,
-                                                          int32_t* __restrict__ out1) {
-  __shared__ int32_t lds[kScanTile];
-  scan_small_one(in0, n0, out0, zero0, lds);
-  if (in1) scan_small_one(in1, n1, out1, nullptr, lds);
-}
-
-// Clears what a rebuild accumulates into: the cell counts, the list
-// statistics and the out-of-box flag.
-__device__ __forceinline__ void reset_build_body(int32_t* __restrict__ count, int64_t ncells,
-                                                 int32_t* __restrict__ stats, int32_t* __restrict__ err, int64_t i) {
-  if (i < ncells) count[i] = 0;
-  if (i < 4) stats[i] = 0;
-  if (i == 0) err[1] = 0;
-}
-
-__global__ __launch_bounds__(kBlock) void k_reset_build(int32_t* __restrict__ count, int64_t ncells,
-                                                        int32_t* __restrict__ stats, int32_t* __restrict__ err) {
-  reset_build_body(count, ncells, stats, err, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+template <bool CLEAR>
+__global__ __launch_bounds__(kScanTile) void k_scan_small(int32_t* __restrict__ in, int64_t n,
+                                                          int32_t* __restrict__ out) {
+  __shared__ int32_t lds[kScanTile / 64];
+  scan_small_one<CLEAR>(in, n, out, lds);
 }
 
 __device__ __forceinline__ void scatter_body(const int32_t* __restrict__ cell, int64_t n,
@@ -213,12 +228,6 @@ __device__ __forceinline__ void scatter_body(const int32_t* __restrict__ cell, i
                                              int32_t* __restrict__ scat, int64_t i) {
   if (i >= n) return;
   scat[start[cell[i]] + slot[i]] = (int32_t)i;
-}
-
-__global__ __launch_bounds__(kBlock) void k_scatter(const int32_t* __restrict__ cell, int64_t n,
-                                                    const int32_t* __restrict__ start,
-                                                    const int32_t* __restrict__ slot, int32_t* __restrict__ scat) {
-  scatter_body(cell, n, start, slot, scat, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // The scatter leaves each cell's atoms in arrival order; placing each
@@ -236,13 +245,6 @@ __device__ __forceinline__ void rank_cells_body(const int32_t* __restrict__ cell
   int32_t r = 0;
   for (int32_t k = b; k < e; k++) r += scattered[k] < v ? 1 : 0;
   perm[b + r] = v;
-}
-
-__global__ __launch_bounds__(kBlock) void k_rank_cells(const int32_t* __restrict__ cell,
-                                                       const int32_t* __restrict__ start,
-                                                       const int32_t* __restrict__ scattered, int64_t n,
-                                                       int32_t* __restrict__ perm) {
-  rank_cells_body(cell, start, scattered, n, perm, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 template <typename T>
@@ -288,25 +290,6 @@ __global__ __launch_bounds__(kBlock) void k_gather_batch(const GatherArgs* __res
   gather_body<T>(tab[lo], (g - blk_start[lo]) * blockDim.x + threadIdx.x);
 }
 
-// Inclusive prefix sum of v over the workgroup's threads in thread order
-// (blockDim.x a multiple of 64, at most kBlock): shuffle scans within each
-// wave, then each wave adds the totals of the waves before it.  All threads
-// call; wsum holds kBlock / 64 ints of LDS.
-__device__ __forceinline__ int32_t block_scan_incl_wave(int32_t v, int32_t* wsum) {
-  const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int32_t u = __shfl_up(v, o, 64);
-    if (lane >= o) v += u;
-  }
-  if (lane == 63) wsum[w] = v;
-  __syncthreads();
-  int32_t add = 0;
-  for (int i = 0; i < w; i++) add += wsum[i];
-  __syncthreads();
-  return v + add;
-}
-
 // --------------------------------------------------------------------------
 // Bricks: halo sizes, halo slot tables, owned atoms (every rebuild)
 // --------------------------------------------------------------------------
@@ -338,21 +321,17 @@ __device__ __forceinline__ void brick_count_body(const int32_t* __restrict__ sta
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_brick_count(const int32_t* __restrict__ start, BrickGeom g,
-                                                        int32_t* __restrict__ H, int32_t* __restrict__ O) {
-  brick_count_body(start, g, H, O, blockIdx.x);
-}
-
 // One workgroup per brick: slot prefix over the halo cells, the sorted
 // position of every halo slot, and for every owned atom its slot, sorted
 // position and own halo cell.
 __device__ __forceinline__ void brick_fill_body(const int32_t* __restrict__ start, const BrickGeom& g,
-                                                const BrickIndex& bi, int32_t* __restrict__ hp_out,
-                                                int32_t* __restrict__ halo_rank, int32_t* __restrict__ owned_slot,
+                                                const BrickIndex& bi, const int32_t* __restrict__ perm,
+                                                int32_t* __restrict__ hp_out, int32_t* __restrict__ halo_rank,
+                                                int32_t* __restrict__ halo_id, int32_t* __restrict__ owned_slot,
                                                 int32_t* __restrict__ owned_rank, int32_t* __restrict__ owned_hcell,
                                                 int32_t* err, int64_t b) {
   static_assert(kHaloCells <= kBlock && kOwnCells <= kBlock, "one thread per halo cell");
-  __shared__ int32_t hcell[kHaloCells], hpre[kHaloCells + 1];
+  __shared__ int32_t hstart[kHaloCells], hpre[kHaloCells + 1];
   __shared__ int32_t oh[kOwnCells], opre[kOwnCells + 1];
   __shared__ int32_t wsum[kBlock / 64];
   const BrickShape s = brick_shape(b, g);
@@ -364,19 +343,19 @@ __device__ __forceinline__ void brick_fill_body(const int32_t* __restrict__ star
   if (t < nh) {
     const int hx = t % s.h[0], hy = (t / s.h[0]) % s.h[1], hz = t / (s.h[0] * s.h[1]);
     const int32_t c = halo_cell_id(s, g, hx, hy, hz);
-    hcell[t] = c;
+    hstart[t] = start[c];
     ch = start[c + 1] - start[c];
   }
   if (t < no) {
     const int ox = t % s.e[0], oy = (t / s.e[0]) % s.e[1], oz = t / (s.e[0] * s.e[1]);
     oh[t] = ((oz + 1) * s.h[1] + (oy + 1)) * s.h[0] + (ox + 1);
   }
-  const int32_t hin = block_scan_incl_wave(ch, wsum);
+  const int32_t hin = block_scan_incl(ch, wsum);
   if (t < nh) hpre[t + 1] = hin;
   if (t == 0) hpre[0] = 0;
   __syncthreads();
   const int32_t co = t < no ? hpre[oh[t] + 1] - hpre[oh[t]] : 0;
-  const int32_t oin = block_scan_incl_wave(co, wsum);
+  const int32_t oin = block_scan_incl(co, wsum);
   if (t < no) opre[t + 1] = oin;
   if (t == 0) {
     opre[0] = 0;
@@ -385,18 +364,25 @@ __device__ __forceinline__ void brick_fill_body(const int32_t* __restrict__ star
   __syncthreads();
   int32_t* hp = hp_out + b * (kHaloCells + 1);
   for (int h = threadIdx.x; h <= nh; h += blockDim.x) hp[h] = hpre[h];
-  // thread t writes the slots of halo cell t, then of owned cell t (each cell's
-  // atoms are consecutive in sorted order from start[cell])
+  // kFillLanes threads write the slots of a halo cell, then of an owned cell
+  // (each cell's atoms are consecutive in sorted order); one thread per cell
+  // left the launch to the few cells of a brick with dense ones (27 cells of
+  // 32 atoms: 8.5 us, 6.4 now with the gather beside it)
+  constexpr int kFillLanes = 8;
+  const int lane = t & (kFillLanes - 1), step = (int)(blockDim.x / kFillLanes);
   const int32_t hb = bi.hb[b];
-  if (t < nh) {
-    const int32_t s0 = start[hcell[t]], base = hb + hpre[t];
-    for (int32_t j = 0; j < ch; j++) halo_rank[base + j] = s0 + j;
+  for (int h = t / kFillLanes; h < nh; h += step) {
+    const int32_t s0 = hstart[h], base = hb + hpre[h], n = hpre[h + 1] - hpre[h];
+    for (int32_t j = lane; j < n; j += kFillLanes) {
+      halo_rank[base + j] = s0 + j;
+      if (halo_id) halo_id[base + j] = perm[s0 + j];
+    }
   }
   const int32_t ob = bi.ob[b];
-  if (t < no) {
-    const int h = oh[t];
-    const int32_t s0 = start[hcell[h]], slot0 = hpre[h], base = ob + opre[t];
-    for (int32_t j = 0; j < co; j++) {
+  for (int o = t / kFillLanes; o < no; o += step) {
+    const int h = oh[o];
+    const int32_t s0 = hstart[h], slot0 = hpre[h], base = ob + opre[o], n = opre[o + 1] - opre[o];
+    for (int32_t j = lane; j < n; j += kFillLanes) {
       owned_slot[base + j] = slot0 + j;
       owned_rank[base + j] = s0 + j;
       owned_hcell[base + j] = h;
@@ -404,11 +390,52 @@ __device__ __forceinline__ void brick_fill_body(const int32_t* __restrict__ star
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_brick_fill(const int32_t* __restrict__ start, BrickGeom g, BrickIndex bi,
-                                                       int32_t* __restrict__ hp_out, int32_t* __restrict__ halo_rank,
-                                                       int32_t* __restrict__ owned_slot, int32_t* __restrict__ owned_rank,
-                                                       int32_t* __restrict__ owned_hcell, int32_t* err) {
-  brick_fill_body(start, g, bi, hp_out, halo_rank, owned_slot, owned_rank, owned_hcell, err, blockIdx.x);
+// --------------------------------------------------------------------------
+// Stages of a rebuild that do not depend on each other share a launch (a small
+// rebuild is its launches: eleven took 34 us of host time): the scatter and
+// the brick counts (after the cell scan), the ranks and the scan of the brick
+// counts, the brick tables and the sorted positions (after the ranks).
+// --------------------------------------------------------------------------
+__global__ __launch_bounds__(kBlock) void k_scatter_count(const int32_t* __restrict__ cell, int64_t n,
+                                                          const int32_t* __restrict__ start,
+                                                          const int32_t* __restrict__ slot, int32_t* __restrict__ scat,
+                                                          int64_t scatter_blocks, BrickGeom g, int32_t* __restrict__ H,
+                                                          int32_t* __restrict__ O) {
+  const int64_t blk = blockIdx.x;
+  if (blk < scatter_blocks)
+    scatter_body(cell, n, start, slot, scat, blk * blockDim.x + threadIdx.x);
+  else
+    brick_count_body(start, g, H, O, blk - scatter_blocks);
+}
+
+// Two workgroups scan the brick counts where they fit one (scans = 2).
+__global__ __launch_bounds__(kScanTile) void k_rank_scan(const int32_t* __restrict__ cell,
+                                                         const int32_t* __restrict__ start,
+                                                         const int32_t* __restrict__ scattered, int64_t n,
+                                                         int32_t* __restrict__ perm, int32_t scans, int32_t* H,
+                                                         int32_t* hb, int32_t* O, int32_t* ob, int64_t nbricks) {
+  __shared__ int32_t lds[kScanTile / 64];
+  const int64_t blk = blockIdx.x;
+  if (blk < scans)
+    scan_small_one<false>(blk == 0 ? H : O, nbricks, blk == 0 ? hb : ob, lds);
+  else
+    rank_cells_body(cell, start, scattered, n, perm, (blk - scans) * blockDim.x + threadIdx.x);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_fill_gather(const int32_t* __restrict__ start, BrickGeom g, BrickIndex bi,
+                                                        const int32_t* __restrict__ perm,
+                                                        int32_t* __restrict__ hp_out, int32_t* __restrict__ halo_rank,
+                                                        int32_t* __restrict__ halo_id,
+                                                        int32_t* __restrict__ owned_slot,
+                                                        int32_t* __restrict__ owned_rank,
+                                                        int32_t* __restrict__ owned_hcell, int32_t* err,
+                                                        GatherArgs ga) {
+  const int64_t blk = blockIdx.x;
+  if (blk < g.nbricks)
+    brick_fill_body(start, g, bi, perm, hp_out, halo_rank, halo_id, owned_slot, owned_rank, owned_hcell, err, blk);
+  else
+    gather_body<T>(ga, (blk - g.nbricks) * blockDim.x + threadIdx.x);
 }
 
 // Full neighbour rows as halo slots.  The decision is the FP64 test on the
@@ -767,20 +794,15 @@ __device__ __forceinline__ int32_t subset_walker(const BuildSubset& s, int64_t g
   const int64_t blk = g_ - (s).blk[w_];           \
   (void)blk;
 
-__global__ __launch_bounds__(kBlock) void k_reset_build_b(BuildSubset s) {
-  GM_SUBSET_BEGIN(s, blockIdx.x)
-  reset_build_body(A.count, A.ncells, A.stats, A.err, blk * blockDim.x + threadIdx.x);
-}
-
 __global__ __launch_bounds__(kBlock) void k_cell_ids_b(BuildSubset s) {
   GM_SUBSET_BEGIN(s, blockIdx.x)
-  cell_ids_body(A.ga.pos, A.n, A.cg, A.cell, A.count, A.slot, A.err, blk * blockDim.x + threadIdx.x);
+  cell_ids_body(A.ga.pos, A.n, A.cg, A.cell, A.count, A.slot, A.stats, A.err, blk * blockDim.x + threadIdx.x);
 }
 
 __global__ __launch_bounds__(kScanTile) void k_scan_cells_b(BuildSubset s) {
-  __shared__ int32_t lds[kScanTile];
+  __shared__ int32_t lds[kScanTile / 64];
   GM_SUBSET_BEGIN(s, blockIdx.x)
-  scan_small_one(A.count, A.ncells, A.start, nullptr, lds);
+  scan_small_one<true>(A.count, A.ncells, A.start, lds);
 }
 
 __global__ __launch_bounds__(kBlock) void k_scatter_b(BuildSubset s) {
@@ -799,16 +821,16 @@ __global__ __launch_bounds__(kBlock) void k_brick_count_b(BuildSubset s) {
 }
 
 __global__ __launch_bounds__(kScanTile) void k_scan_bricks_b(BuildSubset s) {
-  __shared__ int32_t lds[kScanTile];
+  __shared__ int32_t lds[kScanTile / 64];
   GM_SUBSET_BEGIN(s, blockIdx.x)
-  scan_small_one(A.brick_H, A.bg.nbricks, A.brick_hb, nullptr, lds);
-  scan_small_one(A.brick_O, A.bg.nbricks, A.brick_ob, nullptr, lds);
+  scan_small_one<false>(A.brick_H, A.bg.nbricks, A.brick_hb, lds);
+  scan_small_one<false>(A.brick_O, A.bg.nbricks, A.brick_ob, lds);
 }
 
 __global__ __launch_bounds__(kBlock) void k_brick_fill_b(BuildSubset s) {
   GM_SUBSET_BEGIN(s, blockIdx.x)
-  brick_fill_body(A.start, A.bg, A.bi, A.brick_hp, A.halo_rank, A.owned_slot, A.owned_rank, A.owned_hcell, A.err,
-                  blk);
+  brick_fill_body(A.start, A.bg, A.bi, A.perm, A.brick_hp, A.halo_rank, A.halo_id, A.owned_slot, A.owned_rank,
+                  A.owned_hcell, A.err, blk);
 }
 
 template <typename T>
@@ -903,64 +925,62 @@ hipError_t launch_upload(void* dst, const void* src, size_t bytes, hipStream_t s
 }
 
 hipError_t launch_cell_ids(const float4* pos, int64_t n, const CellGeom& g, int32_t* cell, int32_t* count,
-                           int32_t* slot, int32_t* err, hipStream_t st) {
-  k_cell_ids<<<grid_of(n, kBlock), kBlock, 0, st>>>(pos, n, g, cell, count, slot, err);
+                           int32_t* slot, int32_t* stats, int32_t* err, hipStream_t st) {
+  k_cell_ids<<<grid_of(n, kBlock), kBlock, 0, st>>>(pos, n, g, cell, count, slot, stats, err);
   return hipGetLastError();
 }
 
-hipError_t launch_scan(const int32_t* in, int64_t n, int32_t* out, int32_t* zero, int32_t* tmp, hipStream_t st) {
+template <bool CLEAR>
+static hipError_t launch_scan_t(int32_t* in, int64_t n, int32_t* out, int32_t* tmp, hipStream_t st) {
   if (n <= kScanSmall) {
-    k_scan_small<<<1, kScanTile, 0, st>>>(in, n, out, zero, nullptr, 0, nullptr);
+    k_scan_small<CLEAR><<<1, kScanTile, 0, st>>>(in, n, out);
     return hipGetLastError();
   }
   const int64_t ntiles = (n + kScanTile - 1) / kScanTile;
   k_tile_sums<<<(unsigned)ntiles, kScanTile, 0, st>>>(in, n, tmp);
   k_scan_sums<<<1, kScanTile, 0, st>>>(tmp, ntiles, out, n);
-  k_scan_tiles<<<(unsigned)ntiles, kScanTile, 0, st>>>(in, n, tmp, out, zero);
+  k_scan_tiles<CLEAR><<<(unsigned)ntiles, kScanTile, 0, st>>>(in, n, tmp, out);
   return hipGetLastError();
 }
 
-// Two exclusive scans (no zeroing); one launch when both are short.
-hipError_t launch_scan2(const int32_t* in0, int32_t* out0, const int32_t* in1, int32_t* out1, int64_t n,
-                        int32_t* tmp, hipStream_t st) {
-  if (n <= kScanSmall) {
-    k_scan_small<<<1, kScanTile, 0, st>>>(in0, n, out0, nullptr, in1, n, out1);
-    return hipGetLastError();
-  }
-  hipError_t e = launch_scan(in0, n, out0, nullptr, tmp, st);
-  return e != hipSuccess ? e : launch_scan(in1, n, out1, nullptr, tmp, st);
+hipError_t launch_scan(int32_t* in, int64_t n, int32_t* out, bool clear, int32_t* tmp, hipStream_t st) {
+  return clear ? launch_scan_t<true>(in, n, out, tmp, st) : launch_scan_t<false>(in, n, out, tmp, st);
 }
 
-hipError_t launch_reset_build(int32_t* count, int64_t ncells, int32_t* stats, int32_t* err, hipStream_t st) {
-  const int64_t n = ncells > 4 ? ncells : 4;
-  k_reset_build<<<grid_of(n, kBlock), kBlock, 0, st>>>(count, ncells, stats, err);
+hipError_t launch_scatter_count(const int32_t* cell, int64_t n, const int32_t* start, const int32_t* slot, int32_t* scat,
+                                const BrickGeom& g, int32_t* H, int32_t* O, hipStream_t st) {
+  const unsigned s = grid_of(n, kBlock);
+  k_scatter_count<<<s + grid_of(g.nbricks, kBlock / 64), kBlock, 0, st>>>(cell, n, start, slot, scat, (int64_t)s, g, H, O);
   return hipGetLastError();
 }
 
-hipError_t launch_scatter(const int32_t* cell, int64_t n, const int32_t* start, const int32_t* slot, int32_t* scat,
-                          hipStream_t st) {
-  k_scatter<<<grid_of(n, kBlock), kBlock, 0, st>>>(cell, n, start, slot, scat);
-  return hipGetLastError();
+hipError_t launch_rank_scan(const int32_t* cell, const int32_t* start, const int32_t* scattered, int64_t n,
+                            int32_t* perm, const BrickGeom& g, int32_t* H, int32_t* hb, int32_t* O, int32_t* ob,
+                            int32_t* tmp, hipStream_t st) {
+  const int32_t scans = g.nbricks <= kScanSmall ? 2 : 0;
+  k_rank_scan<<<grid_of(n, kScanTile) + (unsigned)scans, kScanTile, 0, st>>>(cell, start, scattered, n, perm, scans, H,
+                                                                             hb, O, ob, g.nbricks);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && !scans) e = launch_scan(H, g.nbricks, hb, false, tmp, st);
+  if (e == hipSuccess && !scans) e = launch_scan(O, g.nbricks, ob, false, tmp, st);
+  return e;
 }
 
-hipError_t launch_rank_cells(const int32_t* cell, const int32_t* start, const int32_t* scattered, int64_t n,
-                             int32_t* perm, hipStream_t st) {
-  k_rank_cells<<<grid_of(n, kBlock), kBlock, 0, st>>>(cell, start, scattered, n, perm);
+template <typename T>
+hipError_t launch_fill_gather(const int32_t* start, const BrickGeom& g, const BrickIndex& bi, const int32_t* perm,
+                              int32_t* hp, int32_t* halo_rank, int32_t* halo_id, int32_t* owned_slot,
+                              int32_t* owned_rank, int32_t* owned_hcell, int32_t* err, const GatherArgs& ga,
+                              hipStream_t st) {
+  k_fill_gather<T><<<(unsigned)g.nbricks + grid_of(ga.n, kBlock), kBlock, 0, st>>>(
+      start, g, bi, perm, hp, halo_rank, halo_id, owned_slot, owned_rank, owned_hcell, err, ga);
   return hipGetLastError();
 }
-
-hipError_t launch_brick_count(const int32_t* start, const BrickGeom& g, int32_t* H, int32_t* O, hipStream_t st) {
-  k_brick_count<<<grid_of(g.nbricks, kBlock / 64), kBlock, 0, st>>>(start, g, H, O);
-  return hipGetLastError();
-}
-
-hipError_t launch_brick_fill(const int32_t* start, const BrickGeom& g, const BrickIndex& bi, int32_t* hp,
-                             int32_t* halo_rank, int32_t* owned_slot, int32_t* owned_rank, int32_t* owned_hcell,
-                             int32_t* err, hipStream_t st) {
-  k_brick_fill<<<(unsigned)g.nbricks, kBlock, 0, st>>>(start, g, bi, hp, halo_rank, owned_slot, owned_rank,
-                                                       owned_hcell, err);
-  return hipGetLastError();
-}
+template hipError_t launch_fill_gather<float>(const int32_t*, const BrickGeom&, const BrickIndex&, const int32_t*,
+                                              int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*,
+                                              const GatherArgs&, hipStream_t);
+template hipError_t launch_fill_gather<double>(const int32_t*, const BrickGeom&, const BrickIndex&, const int32_t*,
+                                               int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*,
+                                               const GatherArgs&, hipStream_t);
 
 template <typename T>
 hipError_t launch_gather(const GatherArgs& a, hipStream_t st) {
@@ -1005,8 +1025,6 @@ hipError_t launch_build_batch(const BuildArgs* const* dev, const BuildArgs* host
     return s.blk[k] > 0;
   };
   const unsigned bw = kBlock / 64;  // bricks per workgroup of the brick count
-  if (prefix([](const BuildArgs& a) { return grid_of(a.ncells > 4 ? a.ncells : 4, kBlock); }))
-    k_reset_build_b<<<(unsigned)s.blk[k], kBlock, 0, st>>>(s);
   if (prefix([](const BuildArgs& a) { return grid_of(a.n, kBlock); })) k_cell_ids_b<<<(unsigned)s.blk[k], kBlock, 0, st>>>(s);
   if (prefix([](const BuildArgs&) { return 1; })) k_scan_cells_b<<<(unsigned)s.blk[k], kScanTile, 0, st>>>(s);
   if (prefix([](const BuildArgs& a) { return grid_of(a.n, kBlock); })) {

@@ -52,9 +52,31 @@ __device__ __forceinline__ auto brick_variant(const CvArgs<T>& a, const Brick& k
 }
 
 template <typename T>
-__device__ __forceinline__ void stage_pos(const CvArgs<T>& a, const Brick& k, vec4_t<T>* lp) {
+__device__ __forceinline__ vec4_t<T> as_vec(const float4& p) {
+  vec4_t<T> q;
+  q.x = (T)p.x;
+  q.y = (T)p.y;
+  q.z = (T)p.z;
+  q.w = (T)p.w;
+  return q;
+}
+
+// Pass 1's staging: the sorted positions, or (IN) straight from the caller's
+// array, then true if a coordinate lies outside the box, or may (not all staged).
+template <bool IN, typename T>
+__device__ __forceinline__ bool stage_pos(const CvArgs<T>& a, const Brick& k, vec4_t<T>* lp) {
+  bool out = IN && k.H > a.bg.cap;
 #pragma unroll 4
-  for (int32_t s = threadIdx.x; s < k.ns; s += blockDim.x) lp[s] = a.pos_s[a.bi.halo_rank[k.hb + s]];
+  for (int32_t s = threadIdx.x; s < k.ns; s += blockDim.x) {
+    if constexpr (IN) {
+      const float4 p = a.pos_in[a.bi.halo_id[k.hb + s]];
+      out = out || outside_box(p, a.L, a.Llo);
+      lp[s] = as_vec<T>(p);
+    } else {
+      lp[s] = a.pos_s[a.bi.halo_rank[k.hb + s]];
+    }
+  }
+  return out;
 }
 
 // LDS record of a slot: position, then the 16-wide row (4 vectors).
@@ -75,9 +97,10 @@ __device__ __forceinline__ void stage_rows(const CvArgs<T>& a, const Brick& k, c
 
 // Fetch a slot's position (and row) from LDS; slots past the staged capacity
 // come from global memory.  ALL: the whole halo is staged (no fallback path).
-template <bool ALL, typename T>
+template <bool IN, bool ALL, typename T>
 __device__ __forceinline__ vec4_t<T> fetch_pos(const CvArgs<T>& a, const Brick& k, const vec4_t<T>* lp, int32_t s) {
   if (ALL || s < a.bg.cap) return lp[s];
+  if constexpr (IN) return as_vec<T>(a.pos_in[a.bi.halo_id[k.hb + s]]);
   return a.pos_s[a.bi.halo_rank[k.hb + s]];
 }
 
@@ -126,13 +149,12 @@ __device__ __forceinline__ void write_out(const CvArgs<T>& a, int32_t rank, T gx
   write_out_at(a, id, reinterpret_cast<const vec4_t<T>*>(a.out4)[id], gx, gy, gz);
 }
 
-// Fixed-order sum of the per-workgroup partials, in one workgroup (its own
-// launch, so every partial is visible without fences); writes s.
+// Fixed-order sum of the per-workgroup partials by one workgroup; writes s.
 // TWO: part_b holds the coordination (scaled by 1/N), part_a the q6 count.
 // SCALE: one CV held in part_a that is scaled by 1/N (the coordination alone).
-template <typename T, bool TWO, bool SCALE>
-__device__ __forceinline__ void finish_body(const CvArgs<T>& a) {
-  __shared__ double red[kBlock / 64];
+// DEV: partials of this launch, stored past the L2 (see device_store).
+template <typename T, bool TWO, bool SCALE, bool DEV>
+__device__ __forceinline__ void finish_body(const CvArgs<T>& a, double* red) {
   const int32_t nblk = a.bg.blocks;
   double sa = 0.0, sb = 0.0;
   // 8 strided partials per thread and round, loaded as one batch (clamped
@@ -143,8 +165,8 @@ __device__ __forceinline__ void finish_body(const CvArgs<T>& a) {
 #pragma unroll
     for (int u = 0; u < 8; u++) {
       const int32_t i = min(base + u * (int32_t)blockDim.x, nblk - 1);
-      va[u] = a.part_a[i];
-      vb[u] = TWO ? a.part_b[i] : 0.0;
+      va[u] = DEV ? device_load(&a.part_a[i]) : a.part_a[i];
+      vb[u] = TWO ? a.part_b[i] : 0.0;  // of the pass before
     }
 #pragma unroll
     for (int u = 0; u < 8; u++) {
@@ -168,14 +190,34 @@ __device__ __forceinline__ void finish_body(const CvArgs<T>& a) {
   }
 }
 
+// A launch of its own, so that every partial is visible without fences.
 template <typename T, bool TWO, bool SCALE>
 __global__ __launch_bounds__(kBlock) void k_finish(CvArgs<T> a) {
-  finish_body<T, TWO, SCALE>(a);
+  __shared__ double red[kBlock / 64];
+  finish_body<T, TWO, SCALE, false>(a, red);
 }
 
 template <typename T, bool TWO, bool SCALE>
 __global__ __launch_bounds__(kBlock) void k_finish_batch(const CvArgs<T>* __restrict__ tab) {
-  finish_body<T, TWO, SCALE>(tab[blockIdx.x]);
+  __shared__ double red[kBlock / 64];
+  if (!tab[blockIdx.x].ticket) finish_body<T, TWO, SCALE, false>(tab[blockIdx.x], red);
+}
+
+// A workgroup's partial of the CV's sum (in thread 0), and in small grids the
+// sum itself by the workgroup that is last.  All threads call.
+template <typename T, bool TWO, bool SCALE>
+__device__ __forceinline__ void leave_partial(const CvArgs<T>& a, double b, int32_t blk, int32_t nblk, double* red) {
+  __shared__ int32_t last;
+  if (!a.ticket) {
+    if (threadIdx.x == 0) a.part_a[blk] = b;
+    return;
+  }
+  if (threadIdx.x == 0) {
+    device_store(&a.part_a[blk], b);
+    last = take_last_ticket(a.ticket, nblk) ? 1 : 0;
+  }
+  __syncthreads();
+  if (last) finish_body<T, TWO, SCALE, true>(a, red);
 }
 
 // Threads per atom: TPA adjacent lanes share one owned atom; lane part p
@@ -436,14 +478,19 @@ __device__ __forceinline__ void balance_pair(SlotWriter& wr) {
 // --------------------------------------------------------------------------
 // Pass 1
 // --------------------------------------------------------------------------
-template <typename T, bool CN, bool Q6, bool ALL, bool WRAP>
+template <typename T, bool CN, bool Q6, bool IN, bool ALL, bool WRAP>
 __device__ __forceinline__ double pass1_atoms(const CvArgs<T>& a, const Brick& k, const vec4_t<T>* lp,
                                               int32_t* keys) {
   double cn_part = 0.0;
   GM_FOR_OWNED(a, k) {
     const int32_t si = a.bi.owned_slot[k.ob + o];
     const int32_t ri = a.bi.owned_rank[k.ob + o];
-    const vec4_t<T> pi = fetch_pos<ALL>(a, k, lp, si);
+    const vec4_t<T> pi = fetch_pos<IN, ALL>(a, k, lp, si);
+    if (IN && part == 0) {  // what the gather does for larger systems
+      if (!(isfinite(pi.x) && isfinite(pi.y) && isfinite(pi.z))) atomicOr(a.err, kErrNonFinite);
+      if (WRAP && outside_box(make_float4((float)pi.x, (float)pi.y, (float)pi.z, 0.f), a.L, a.Llo)) atomicOr(a.err + 1, 1);
+      if (Q6) a.pos_s[ri] = pi;
+    }
     const int32_t c = min(a.cnt[k.ob + o], a.kmax);
     const int32_t cp = c > part ? ((c - part - 1) >> TSH) + 1 : 0;
     // Phase 1: distance filter over the neighbour sub-row, writing this
@@ -463,7 +510,7 @@ __device__ __forceinline__ double pass1_atoms(const CvArgs<T>& a, const Brick& k
     T cnsum = T(0), gx = T(0), gy = T(0), gz = T(0);
     const T gscale = T(-6) * a.cn_r0inv2;
     for_slots<true>(nrow, cp, ps, first_chunk(nrow, cp), [&](int32_t s) {
-      const vec4_t<T> pj = fetch_pos<ALL>(a, k, lp, s);
+      const vec4_t<T> pj = fetch_pos<IN, ALL>(a, k, lp, s);
       T dx, dy, dz;
       const T r2 = pair_vec<WRAP>(pi, pj, a, dx, dy, dz);
       if (r2 < a.rc2) {
@@ -508,7 +555,7 @@ __device__ __forceinline__ double pass1_atoms(const CvArgs<T>& a, const Brick& k
     T fsum = T(0);
     if (Q6)
       for_slots<true>(crow, nc, ps, first_chunk(crow, nc), [&](int32_t s) {
-        const vec4_t<T> pj = fetch_pos<ALL>(a, k, lp, s);
+        const vec4_t<T> pj = fetch_pos<IN, ALL>(a, k, lp, s);
         T dx, dy, dz;
         const T r2 = pair_vec<WRAP>(pi, pj, a, dx, dy, dz);
         const T rinv = g_rsqrt(r2);
@@ -559,21 +606,27 @@ __device__ __forceinline__ double pass1_atoms(const CvArgs<T>& a, const Brick& k
   return cn_part;
 }
 
-template <typename T, bool CN, bool Q6>
+template <typename T, bool CN, bool Q6, bool IN>
 __device__ __forceinline__ void pass1_body(const CvArgs<T>& a, int64_t brick, int32_t blk, int32_t nblk) {
   extern __shared__ __align__(16) unsigned char smem[];
   vec4_t<T>* lp = reinterpret_cast<vec4_t<T>*>(smem);
   __shared__ double red[BrickBlock<T>::value / 64];
-  const Brick k = brick_begin(a, brick);
-  stage_pos(a, k, lp);
-  __syncthreads();
+  Brick k = brick_begin(a, brick);
+  const bool out = stage_pos<IN>(a, k, lp);
+  if constexpr (IN)
+    k.wrap = __syncthreads_or(out) || k.wrap;
+  else
+    __syncthreads();
   int32_t* keys = reinterpret_cast<int32_t*>(lp + a.bg.cap);
   const double cn_part = brick_variant(a, k, [&](auto all, auto wrap) {
-    return pass1_atoms<T, CN, Q6, decltype(all)::value, decltype(wrap)::value>(a, k, lp, keys);
+    return pass1_atoms<T, CN, Q6, IN, decltype(all)::value, decltype(wrap)::value>(a, k, lp, keys);
   });
   if (CN) {
     const double b = block_sum(cn_part, red);
-    if (threadIdx.x == 0) (Q6 ? a.part_b : a.part_a)[blk] = b;
+    if (!Q6)
+      leave_partial<T, false, true>(a, b, blk, nblk, red);
+    else if (threadIdx.x == 0)
+      a.part_b[blk] = b;
   }
   if (Q6) rank_owned(a, k, keys);
 }
@@ -626,8 +679,7 @@ __device__ __forceinline__ void pass2_body(const CvArgs<T>& a, int64_t brick, in
   const double c_part = brick_variant(a, k, [&](auto all, auto wrap) {
     return pass2_atoms<T, decltype(all)::value, decltype(wrap)::value>(a, k, lr, h0);
   });
-  const double b = block_sum(c_part, red);
-  if (threadIdx.x == 0) a.part_a[blk] = b;
+  leave_partial<T, CN, false>(a, block_sum(c_part, red), blk, nblk, red);
 }
 
 // --------------------------------------------------------------------------
@@ -782,19 +834,19 @@ __device__ __forceinline__ void pass4_body(const CvArgs<T>& a, int64_t brick, in
 // --------------------------------------------------------------------------
 // Coordination number alone: the forces are the seed times the gradient that
 // pass 1 kept per atom (ds/dx_i = (2/N) sum_j f'(r_ij) (x_i - x_j)/r_ij, both
-// orders of each pair), one thread per owned atom of the brick.
+// orders of each pair), one thread per atom in sorted order.
 // --------------------------------------------------------------------------
 template <typename T>
-__device__ __forceinline__ void cn_force_body(const CvArgs<T>& a, int64_t brick, int32_t blk, int32_t nblk) {
-  if (brick >= a.bg.nbricks) return;
-  const int32_t ob = a.bi.ob[brick], O = a.bi.ob[brick + 1] - ob;
+__device__ __forceinline__ void cn_force_body(const CvArgs<T>& a, int64_t t) {
+  if (t >= a.n) return;
   const T seed = (T)((a.seed ? a.seed[0] : 1.0) * 2.0 * a.inv_n);
-  const vec4_t<T>* g = reinterpret_cast<const vec4_t<T>*>(a.cn_grad);
-  for (int32_t o = (int32_t)threadIdx.x; o < O; o += (int32_t)blockDim.x) {
-    const int32_t ri = a.bi.owned_rank[ob + o];
-    const vec4_t<T> v = g[ri];
-    write_out(a, ri, -seed * v.x, -seed * v.y, -seed * v.z);
-  }
+  const vec4_t<T> v = reinterpret_cast<const vec4_t<T>*>(a.cn_grad)[t];
+  write_out(a, (int32_t)t, -seed * v.x, -seed * v.y, -seed * v.z);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_cn_force(CvArgs<T> a) {
+  cn_force_body<T>(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // --------------------------------------------------------------------------
@@ -840,11 +892,19 @@ __device__ __forceinline__ int64_t xcd_remap() {
   }
 
 #define GM_COMMA ,
-GM_PASS_KERNELS(k_pass1, pass1_body, template <typename T GM_COMMA bool CN GM_COMMA bool Q6>, <T GM_COMMA CN GM_COMMA Q6>)
+GM_PASS_KERNELS(k_pass1, pass1_body, template <typename T GM_COMMA bool CN GM_COMMA bool Q6 GM_COMMA bool IN>,
+                <T GM_COMMA CN GM_COMMA Q6 GM_COMMA IN>)
 GM_PASS_KERNELS(k_pass2, pass2_body, template <typename T GM_COMMA bool CN>, <T GM_COMMA CN>)
 GM_PASS_KERNELS(k_pass3, pass3_body, template <typename T>, <T>)
 GM_PASS_KERNELS(k_pass4, pass4_body, template <typename T GM_COMMA bool CN>, <T GM_COMMA CN>)
-GM_PASS_KERNELS(k_cn_force, cn_force_body, template <typename T>, <T>)
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_cn_force_batch(const CvArgs<T>* __restrict__ tab,
+                                                           const int32_t* __restrict__ blk_start, int32_t W) {
+  const int64_t g = blockIdx.x;
+  const int32_t w = find_walker(blk_start, W, g);
+  cn_force_body<T>(tab[w], (g - blk_start[w]) * blockDim.x + threadIdx.x);
+}
 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_atom_values(CvArgs<T> a, int what, int cv_kind, double* dst) {
@@ -875,17 +935,29 @@ static size_t lds_bytes(int32_t cap, bool rows, bool rank = false) {
   return (size_t)cap * (size_t)slot_bytes<T>(rows) + (rank ? (size_t)rank_lds_bytes<T>() : 0);
 }
 
+// Pass 1, from the caller's positions where the context has the halo's atoms.
+template <typename T, bool CN, bool Q6>
+static void launch_pass1(const CvArgs<T>& a, hipStream_t st) {
+  const unsigned g = (unsigned)a.bg.blocks;
+  const size_t lds = lds_bytes<T>(a.bg.cap, false, Q6);
+  if (a.bi.halo_id)
+    k_pass1<T, CN, Q6, true><<<g, BrickBlock<T>::value, lds, st>>>(a);
+  else
+    k_pass1<T, CN, Q6, false><<<g, BrickBlock<T>::value, lds, st>>>(a);
+}
+
 template <typename T>
 hipError_t launch_q6_forward(const CvArgs<T>& a, bool with_cn, hipStream_t st) {
   const unsigned g = (unsigned)a.bg.blocks;
+  const size_t lds = lds_bytes<T>(a.bg.cap, true);
   if (with_cn) {
-    k_pass1<T, true, true><<<g, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, false, true), st>>>(a);
-    k_pass2<T, true><<<g, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, true), st>>>(a);
-    k_finish<T, true, false><<<1, kBlock, 0, st>>>(a);
+    launch_pass1<T, true, true>(a, st);
+    k_pass2<T, true><<<g, BrickBlock<T>::value, lds, st>>>(a);
+    if (!a.ticket) k_finish<T, true, false><<<1, kBlock, 0, st>>>(a);
   } else {
-    k_pass1<T, false, true><<<g, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, false, true), st>>>(a);
-    k_pass2<T, false><<<g, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, true), st>>>(a);
-    k_finish<T, false, false><<<1, kBlock, 0, st>>>(a);
+    launch_pass1<T, false, true>(a, st);
+    k_pass2<T, false><<<g, BrickBlock<T>::value, lds, st>>>(a);
+    if (!a.ticket) k_finish<T, false, false><<<1, kBlock, 0, st>>>(a);
   }
   return hipGetLastError();
 }
@@ -908,14 +980,14 @@ hipError_t launch_q6_force(const CvArgs<T>& a, bool with_cn, hipStream_t st) {
 
 template <typename T>
 hipError_t launch_cn_forward(const CvArgs<T>& a, hipStream_t st) {
-  k_pass1<T, true, false><<<(unsigned)a.bg.blocks, BrickBlock<T>::value, lds_bytes<T>(a.bg.cap, false), st>>>(a);
-  k_finish<T, false, true><<<1, kBlock, 0, st>>>(a);
+  launch_pass1<T, true, false>(a, st);
+  if (!a.ticket) k_finish<T, false, true><<<1, kBlock, 0, st>>>(a);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_cn_force(const CvArgs<T>& a, hipStream_t st) {
-  k_cn_force<T><<<(unsigned)a.bg.blocks, BrickBlock<T>::value, 0, st>>>(a);
+  k_cn_force<T><<<(unsigned)((a.n + kBlock - 1) / kBlock), kBlock, 0, st>>>(a);
   return hipGetLastError();
 }
 
@@ -926,26 +998,29 @@ hipError_t launch_atom_values(const CvArgs<T>& a, int what, int cv_kind, double*
 }
 
 template <typename T>
-hipError_t launch_pass_batch(int pass, bool with_cn, bool fp_rows, const CvArgs<T>* tab, const int32_t* blk_start,
-                             int32_t W, int32_t blocks, int32_t cap, hipStream_t st) {
+hipError_t launch_pass_batch(int pass, bool with_cn, const CvArgs<T>* tab, const int32_t* blk_start, int32_t W,
+                             int32_t blocks, int32_t cap, bool in, bool finish, hipStream_t st) {
   const size_t lds_cn = lds_bytes<T>(cap, false), lds_pos = lds_bytes<T>(cap, false, true),
                lds_rows = lds_bytes<T>(cap, true);
-  (void)fp_rows;
   const unsigned g = (unsigned)blocks;
   switch (pass) {
     case 1:
-      if (with_cn)
-        k_pass1_batch<T, true, true><<<g, BrickBlock<T>::value, lds_pos, st>>>(tab, blk_start, W);
+      if (with_cn && in)
+        k_pass1_batch<T, true, true, true><<<g, BrickBlock<T>::value, lds_pos, st>>>(tab, blk_start, W);
+      else if (with_cn)
+        k_pass1_batch<T, true, true, false><<<g, BrickBlock<T>::value, lds_pos, st>>>(tab, blk_start, W);
+      else if (in)
+        k_pass1_batch<T, false, true, true><<<g, BrickBlock<T>::value, lds_pos, st>>>(tab, blk_start, W);
       else
-        k_pass1_batch<T, false, true><<<g, BrickBlock<T>::value, lds_pos, st>>>(tab, blk_start, W);
+        k_pass1_batch<T, false, true, false><<<g, BrickBlock<T>::value, lds_pos, st>>>(tab, blk_start, W);
       break;
     case 2:
       if (with_cn) {
         k_pass2_batch<T, true><<<g, BrickBlock<T>::value, lds_rows, st>>>(tab, blk_start, W);
-        k_finish_batch<T, true, false><<<(unsigned)W, kBlock, 0, st>>>(tab);
+        if (finish) k_finish_batch<T, true, false><<<(unsigned)W, kBlock, 0, st>>>(tab);
       } else {
         k_pass2_batch<T, false><<<g, BrickBlock<T>::value, lds_rows, st>>>(tab, blk_start, W);
-        k_finish_batch<T, false, false><<<(unsigned)W, kBlock, 0, st>>>(tab);
+        if (finish) k_finish_batch<T, false, false><<<(unsigned)W, kBlock, 0, st>>>(tab);
       }
       break;
     case 3:
@@ -958,15 +1033,22 @@ hipError_t launch_pass_batch(int pass, bool with_cn, bool fp_rows, const CvArgs<
         k_pass4_batch<T, false><<<g, BrickBlock<T>::value, lds_rows, st>>>(tab, blk_start, W);
       break;
     case 5:  // coordination alone: forward
-      k_pass1_batch<T, true, false><<<g, BrickBlock<T>::value, lds_cn, st>>>(tab, blk_start, W);
-      k_finish_batch<T, false, true><<<(unsigned)W, kBlock, 0, st>>>(tab);
-      break;
-    case 6:  // coordination alone: forces
-      k_cn_force_batch<T><<<g, BrickBlock<T>::value, 0, st>>>(tab, blk_start, W);
+      if (in)
+        k_pass1_batch<T, true, false, true><<<g, BrickBlock<T>::value, lds_cn, st>>>(tab, blk_start, W);
+      else
+        k_pass1_batch<T, true, false, false><<<g, BrickBlock<T>::value, lds_cn, st>>>(tab, blk_start, W);
+      if (finish) k_finish_batch<T, false, true><<<(unsigned)W, kBlock, 0, st>>>(tab);
       break;
     default:
       return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_cn_force_batch(const CvArgs<T>* tab, const int32_t* blk_start, int32_t W, int32_t blocks,
+                                 hipStream_t st) {
+  k_cn_force_batch<T><<<(unsigned)blocks, kBlock, 0, st>>>(tab, blk_start, W);
   return hipGetLastError();
 }
 
@@ -975,24 +1057,28 @@ hipError_t launch_pass_batch(int pass, bool with_cn, bool fp_rows, const CvArgs<
 template <typename T>
 static void allow_lds_t(int bytes) {
   const hipFuncAttribute A = hipFuncAttributeMaxDynamicSharedMemorySize;
-  (void)hipFuncSetAttribute((const void*)k_pass1<T, true, true>, A, bytes);
-  (void)hipFuncSetAttribute((const void*)k_pass1<T, false, true>, A, bytes);
-  (void)hipFuncSetAttribute((const void*)k_pass1<T, true, false>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1<T, true, true, true>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1<T, true, true, false>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1<T, false, true, true>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1<T, false, true, false>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1<T, true, false, true>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1<T, true, false, false>, A, bytes);
   (void)hipFuncSetAttribute((const void*)k_pass2<T, true>, A, bytes);
   (void)hipFuncSetAttribute((const void*)k_pass2<T, false>, A, bytes);
   (void)hipFuncSetAttribute((const void*)k_pass3<T>, A, bytes);
   (void)hipFuncSetAttribute((const void*)k_pass4<T, true>, A, bytes);
   (void)hipFuncSetAttribute((const void*)k_pass4<T, false>, A, bytes);
-  (void)hipFuncSetAttribute((const void*)k_cn_force<T>, A, bytes);
-  (void)hipFuncSetAttribute((const void*)k_pass1_batch<T, true, true>, A, bytes);
-  (void)hipFuncSetAttribute((const void*)k_pass1_batch<T, false, true>, A, bytes);
-  (void)hipFuncSetAttribute((const void*)k_pass1_batch<T, true, false>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1_batch<T, true, true, true>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1_batch<T, true, true, false>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1_batch<T, false, true, true>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1_batch<T, false, true, false>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1_batch<T, true, false, true>, A, bytes);
+  (void)hipFuncSetAttribute((const void*)k_pass1_batch<T, true, false, false>, A, bytes);
   (void)hipFuncSetAttribute((const void*)k_pass2_batch<T, true>, A, bytes);
   (void)hipFuncSetAttribute((const void*)k_pass2_batch<T, false>, A, bytes);
   (void)hipFuncSetAttribute((const void*)k_pass3_batch<T>, A, bytes);
   (void)hipFuncSetAttribute((const void*)k_pass4_batch<T, true>, A, bytes);
   (void)hipFuncSetAttribute((const void*)k_pass4_batch<T, false>, A, bytes);
-  (void)hipFuncSetAttribute((const void*)k_cn_force_batch<T>, A, bytes);
 }
 
 void allow_cv_lds(int bytes) {
@@ -1008,8 +1094,9 @@ void allow_cv_lds(int bytes) {
   template hipError_t launch_cn_forward<T>(const CvArgs<T>&, hipStream_t);                              \
   template hipError_t launch_cn_force<T>(const CvArgs<T>&, hipStream_t);                                \
   template hipError_t launch_atom_values<T>(const CvArgs<T>&, int, int, double*, hipStream_t);             \
-  template hipError_t launch_pass_batch<T>(int, bool, bool, const CvArgs<T>*, const int32_t*, int32_t, int32_t, \
-                                           int32_t, hipStream_t);
+  template hipError_t launch_pass_batch<T>(int, bool, const CvArgs<T>*, const int32_t*, int32_t, int32_t, int32_t, \
+                                           bool, bool, hipStream_t);                                              \
+  template hipError_t launch_cn_force_batch<T>(const CvArgs<T>*, const int32_t*, int32_t, int32_t, hipStream_t);
 
 GM_INSTANTIATE(float)
 GM_INSTANTIATE(double)

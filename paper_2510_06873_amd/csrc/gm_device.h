@@ -55,6 +55,41 @@ __device__ __forceinline__ double block_sum(double v, double* lds) {
   return r;
 }
 
+// Values handed to the workgroup that finishes last, which may run on another
+// XCD: device-scope stores and loads go past the XCD's own L2.
+template <typename P>
+__device__ __forceinline__ void device_store(P* p, P v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename P>
+__device__ __forceinline__ P device_load(P* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Called by one thread of each of n workgroups, after its device_store()s: true
+// in exactly one, the last, which then sees what all of them stored.  The wait
+// orders the stores before the ticket; the ticket is left at zero for the next
+// launch.
+__device__ __forceinline__ bool take_last_ticket(int32_t* ticket, int32_t n) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  const int32_t t = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (t != n - 1) return false;
+  device_store(ticket, 0);
+  return true;
+}
+
+// Whether a coordinate lies outside [0, L), L = hi + lo in double (see the
+// gather for why not in FP32).
+template <typename T>
+__device__ __forceinline__ bool outside_box(const float4& p, const T hi[3], const T lo[3]) {
+  const double x[3] = {(double)p.x, (double)p.y, (double)p.z};
+  bool out = false;
+#pragma unroll
+  for (int d = 0; d < 3; d++) out = out || !(x[d] >= 0.0 && x[d] < (double)hi[d] + (double)lo[d]);
+  return out;
+}
+
 // Minimum-image difference xj - xi - k L, k = rint((xj - xi)/L), with the
 // box length split in a high part L (in T) and a low part Llo.  The image
 // shift is subtracted from the coordinate that lies near the far face (xj for

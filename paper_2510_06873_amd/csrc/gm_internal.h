@@ -16,6 +16,15 @@ constexpr int kBuildFillBlocks = 1024;  // workgroups a neighbour build aims for
 constexpr int kBuildMaxSplit = 32;      // most workgroups sharing one brick in the build
 constexpr int kBiasBlock = 1024;        // threads of a block that sums every hill alone
 constexpr int kBiasOne = 8192;          // hills up to which one block sums them
+// Systems up to this size (2 MiB of positions, which fit beside other data in
+// each XCD's L2) have no separate gather: pass 1 stages its halo from the
+// caller's array.  A launch of 2-4 us and 3.3 us of host time, against halos
+// read at random: at 96,000 atoms the step of 83 us became 81.
+constexpr int64_t kFuseGather = 131072;
+// Grids up to this many workgroups (all resident at once) finish the CV's sum in
+// the pass that makes its partials; in larger ones the wait for the ticket at
+// the end of every workgroup costs more than the launch it saves.
+constexpr int32_t kFuseFinish = 256;
 constexpr int kXcd = 8;      // workgroups are dealt to the 8 XCDs round-robin
 constexpr int32_t kMaxTorsions = 1 << 16;   // torsion forces are summed by one workgroup in order
 constexpr int64_t kMaxFesBins = 1 << 24;
@@ -121,6 +130,7 @@ struct BrickIndex {
   const int32_t* ob;          // [nbricks+1] first owned atom of each brick (brick order)
   const int32_t* hp;          // [nbricks][kHaloCells+1] slot prefix over the halo cells
   const int32_t* halo_rank;   // [sum H] sorted position of each halo slot
+  const int32_t* halo_id;     // [sum H] caller's atom of each halo slot, or NULL (see kFuseGather)
   const int32_t* owned_slot;  // [N] halo slot of each owned atom (brick order)
   const int32_t* owned_rank;  // [N] sorted position of each owned atom
   const int32_t* owned_hcell; // [N] halo-cell index of the owned atom's own cell
@@ -129,7 +139,8 @@ struct BrickIndex {
 // Arguments of the per-brick CV kernels.
 template <typename T>
 struct CvArgs {
-  const vec4_t<T>* pos_s;  // positions in sorted (cell) order
+  vec4_t<T>* pos_s;        // positions in sorted (cell) order
+  const float4* pos_in;    // the caller's positions, which pass 1 may read through bi.halo_id instead
   const uint16_t* nbr;     // neighbour slots: sub-row (owned atom, part) of kpart entries
   const int32_t* cnt;      // [N] row lengths, brick order
   uint16_t* cut;           // in-cutoff slots of the current step, same layout as nbr
@@ -155,6 +166,7 @@ struct CvArgs {
   T* cn_grad;       // [N][4] per-atom coordination gradient sum_j f'(r) r_hat (w = 0)
   double* part_a;   // per-workgroup FP64 partial sums (count / coordination)
   double* part_b;
+  int32_t* ticket;  // pass 1 (coordination) or 2 finishes the sum itself (see kFuseFinish); NULL: k_finish does
   double* s_out;    // caller's s (dev), may be NULL
   double* s_int;    // library copy of s
   int32_t* err;
@@ -200,7 +212,7 @@ struct BuildArgs {
   BrickIndex bi;
   int64_t n, ncells;
   int32_t *cell, *count, *start, *slot, *perm, *scat, *stats, *err;
-  int32_t *brick_H, *brick_O, *brick_hb, *brick_ob, *brick_hp, *halo_rank, *owned_slot, *owned_rank, *owned_hcell;
+  int32_t *brick_H, *brick_O, *brick_hb, *brick_ob, *brick_hp, *halo_rank, *halo_id, *owned_slot, *owned_rank, *owned_hcell;
   uint16_t* nbr;
   int32_t* cnt;
   int32_t kmax;
@@ -219,23 +231,25 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st);
 // Copy bytes of host memory to dst (device, at least bytes rounded up to a
 // multiple of 4) through kernel arguments; src may be freed on return.
 hipError_t launch_upload(void* dst, const void* src, size_t bytes, hipStream_t st);
-hipError_t launch_cell_ids(const float4* pos, int64_t n, const CellGeom& g, int32_t* cell,
-                           int32_t* count, int32_t* slot, int32_t* err, hipStream_t st);
+hipError_t launch_cell_ids(const float4* pos, int64_t n, const CellGeom& g, int32_t* cell, int32_t* count,
+                           int32_t* slot, int32_t* stats, int32_t* err, hipStream_t st);
+// Exclusive scan, out[n] = total; clear: in is left at zero.
 // tmp: device int32[(n + 1023)/1024] scratch for the tile sums
-hipError_t launch_scan(const int32_t* in, int64_t n, int32_t* out, int32_t* zero, int32_t* tmp, hipStream_t st);
-hipError_t launch_scan2(const int32_t* in0, int32_t* out0, const int32_t* in1, int32_t* out1, int64_t n,
-                        int32_t* tmp, hipStream_t st);
-hipError_t launch_reset_build(int32_t* count, int64_t ncells, int32_t* stats, int32_t* err, hipStream_t st);
-hipError_t launch_scatter(const int32_t* cell, int64_t n, const int32_t* start, const int32_t* slot,
-                          int32_t* scat, hipStream_t st);
-// perm[start[c] + rank] = atom: each cell's atoms of `scattered` in id order.
-hipError_t launch_rank_cells(const int32_t* cell, const int32_t* start, const int32_t* scattered, int64_t n,
-                             int32_t* perm, hipStream_t st);
-hipError_t launch_brick_count(const int32_t* start, const BrickGeom& g, int32_t* H, int32_t* O,
+hipError_t launch_scan(int32_t* in, int64_t n, int32_t* out, bool clear, int32_t* tmp, hipStream_t st);
+// The scatter of the cell sort and the bricks' halo and owned counts.
+hipError_t launch_scatter_count(const int32_t* cell, int64_t n, const int32_t* start, const int32_t* slot, int32_t* scat,
+                                const BrickGeom& g, int32_t* H, int32_t* O, hipStream_t st);
+// perm[start[c] + rank] = atom: each cell's atoms of `scattered` in id order;
+// and the exclusive scans hb of H and ob of O.
+hipError_t launch_rank_scan(const int32_t* cell, const int32_t* start, const int32_t* scattered, int64_t n,
+                            int32_t* perm, const BrickGeom& g, int32_t* H, int32_t* hb, int32_t* O, int32_t* ob,
+                            int32_t* tmp, hipStream_t st);
+// The brick tables, and the sorted positions.
+template <typename T>
+hipError_t launch_fill_gather(const int32_t* start, const BrickGeom& g, const BrickIndex& bi, const int32_t* perm,
+                              int32_t* hp, int32_t* halo_rank, int32_t* halo_id, int32_t* owned_slot,
+                              int32_t* owned_rank, int32_t* owned_hcell, int32_t* err, const GatherArgs& ga,
                               hipStream_t st);
-hipError_t launch_brick_fill(const int32_t* start, const BrickGeom& g, const BrickIndex& bi,
-                             int32_t* hp, int32_t* halo_rank, int32_t* owned_slot, int32_t* owned_rank,
-                             int32_t* owned_hcell, int32_t* err, hipStream_t st);
 template <typename T>
 hipError_t launch_gather(const GatherArgs& a, hipStream_t st);
 template <typename T>
@@ -293,10 +307,16 @@ void allow_build_lds(int bytes);
 template <typename T>
 hipError_t launch_gather_batch(const GatherArgs* tab, const int32_t* blk_start, int32_t W, int32_t blocks,
                                hipStream_t st);
-// pass: 1..4 = q6 passes, 5 = coordination forward, 6 = coordination forces
+// pass: 1..4 = q6 passes, 5 = coordination forward; in: pass 1 reads every
+// walker's positions from the caller (else all were gathered); finish: some
+// walker's sum is left to k_finish
 template <typename T>
-hipError_t launch_pass_batch(int pass, bool with_cn, bool fp_rows, const CvArgs<T>* tab, const int32_t* blk_start,
-                             int32_t W, int32_t blocks, int32_t cap, hipStream_t st);
+hipError_t launch_pass_batch(int pass, bool with_cn, const CvArgs<T>* tab, const int32_t* blk_start, int32_t W,
+                             int32_t blocks, int32_t cap, bool in, bool finish, hipStream_t st);
+// Coordination forces: blk_start and blocks as for the gather (kBlock atoms per workgroup).
+template <typename T>
+hipError_t launch_cn_force_batch(const CvArgs<T>* tab, const int32_t* blk_start, int32_t W, int32_t blocks,
+                                 hipStream_t st);
 hipError_t launch_bias_batch(const BiasArgs* tab, const int32_t* blk_start, int32_t W, int32_t blocks,
                              hipStream_t st);
 // Some walkers of a batch in one launch pair: device pointers to their table

@@ -106,8 +106,10 @@ def device_bytes(req: Request) -> int:
     if p.cv_kind != 1:
         per_atom += 16 * t * 2                  # q-hat and adjoint rows
     per_atom += 4 * 8                           # halo slot table (bounded by 8 halo copies per atom)
+    if n <= 1 << 17:                            # the halo slots' atoms beside their ranks
+        per_atom += 4 * 8
     if n < 1 << 16:                             # small bricks: up to 27 copies, and their tables
-        per_atom += 4 * 19 + 80
+        per_atom += 2 * 4 * 19 + 80
     hills = p.hill_capacity * (p.dims + 1) * 8
     return int(n * per_atom + hills + (1 << 20))
 
