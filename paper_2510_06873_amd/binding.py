@@ -128,6 +128,9 @@ def lib() -> C.CDLL:
     return _lib
 
 
+import torch  # noqa: E402  (_load has imported it)
+
+
 def _check(rc: int, call: str):
     if rc != GM_OK:
         raise GmError(rc, call)
@@ -239,8 +242,7 @@ class Pipeline:
         return _ptr(t, 4 * self.n, self.fdtype, name)
 
     def build_neighbors(self, pos4, box):
-        box_c = (C.c_double * 3)(*[float(b) for b in box])
-        _check(_lib.gm_build_neighbors(self.h, self._pos(pos4), box_c), "gm_build_neighbors")
+        _check(_lib.gm_build_neighbors(self.h, self._pos(pos4), _box(box)), "gm_build_neighbors")
 
     def cv_forward(self, pos4, s=None):
         s = self.s if s is None else s
@@ -545,19 +547,22 @@ def _grid(lo, hi, nbins, dims):
 
 
 def _stream(stream):
-    import torch
+    """The handle of `stream`, or of the current stream of the current device
+    (read directly: building a torch Stream object takes 3 us, half of a small
+    call)."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+
+_Box = C.c_double * 3
 
 
 def _box(box):
-    return (C.c_double * 3)(*[float(b) for b in box])
+    return _Box(*[float(b) for b in box])
 
 
 def _force(force4, n):
-    import torch
-
     if force4.dtype not in (torch.float32, torch.float64):
         raise ValueError("force4: expected float32 or float64")
     return _ptr(force4, 4 * n, None, "force4"), (FP64 if force4.dtype == torch.float64 else FP32)
@@ -565,8 +570,6 @@ def _force(force4, n):
 
 def torsions(pos4, quads, box, phi=None, stream=None):
     """Torsion angles (IUPAC sign) of the atom quadruples quads (dev int32 [m][4])."""
-    import torch
-
     n, m = pos4.shape[0], quads.shape[0]
     phi = torch.empty(m, dtype=torch.float64, device=pos4.device) if phi is None else phi
     _check(_lib.gm_torsions(_ptr(pos4, 4 * n, torch.float32, "pos4"), n, _ptr(quads, 4 * m, torch.int32, "quads"),
@@ -576,8 +579,6 @@ def torsions(pos4, quads, box, phi=None, stream=None):
 
 def torsion_forces(pos4, quads, box, dVdphi, force4, stream=None):
     """force4 -= sum_t dV/dphi_t dphi_t/dx (in place)."""
-    import torch
-
     n, m = pos4.shape[0], quads.shape[0]
     fp, prec = _force(force4, n)
     _check(_lib.gm_torsion_forces(_ptr(pos4, 4 * n, torch.float32, "pos4"), n,
@@ -589,8 +590,6 @@ def torsion_forces(pos4, quads, box, dVdphi, force4, stream=None):
 
 def nearest_distance(pos4, centre, members, box, s=None, nearest=None, stream=None):
     """Distance from atom centre to the nearest atom of members (dev int32 [k])."""
-    import torch
-
     n, k = pos4.shape[0], members.shape[0]
     s = torch.empty(1, dtype=torch.float64, device=pos4.device) if s is None else s
     _check(_lib.gm_nearest_distance(_ptr(pos4, 4 * n, torch.float32, "pos4"), n, int(centre),
@@ -601,8 +600,6 @@ def nearest_distance(pos4, centre, members, box, s=None, nearest=None, stream=No
 
 
 def nearest_distance_forces(pos4, centre, members, box, dVds, force4, stream=None):
-    import torch
-
     n, k = pos4.shape[0], members.shape[0]
     fp, prec = _force(force4, n)
     _check(_lib.gm_nearest_distance_forces(_ptr(pos4, 4 * n, torch.float32, "pos4"), n, int(centre),
@@ -623,8 +620,6 @@ def lattice_virial(box, dVdL):
 
 def fes_reweight(s, V, lo, hi, nbins, kBT, F=None, stream=None):
     """F per bin from samples s (dev double [T] or [T][dims]) and their bias V (dev double [T])."""
-    import torch
-
     T = V.shape[0]
     dims = 1 if s.dim() == 1 else s.shape[1]
     lo_c, hi_c, nb_c = _grid(lo, hi, nbins, dims)
@@ -641,8 +636,6 @@ def fes_reweight(s, V, lo, hi, nbins, kBT, F=None, stream=None):
 def fes_reweight_noalloc(s, V, lo, hi, nbins, kBT, F, stream=None):
     """fes_reweight into the caller's F (dev double [prod nbins]) with no device
     allocation (the library's fixed scratch; at most 65536 bins)."""
-    import torch
-
     T = V.shape[0]
     dims = 1 if s.dim() == 1 else s.shape[1]
     lo_c, hi_c, nb_c = _grid(lo, hi, nbins, dims)
