@@ -83,7 +83,7 @@ std::mutex g_pool_mu;
 hipMemPool_t g_pool[kMaxDevices] = {};
 
 std::mutex g_lds_mu;
-int g_lds_max = 0;  // largest LDS staging budget of any context so far (bytes)
+int g_lds_max[kMaxDevices] = {};  // per device: largest LDS staging budget of any context so far (bytes)
 
 hipMemPool_t device_pool() {
   int dev = 0;
@@ -808,12 +808,17 @@ int gm_create(gm_ctx** out, const gm_params* params, int64_t n_atoms, void* hip_
     // context: keep it at the largest budget any context asked for, so that a
     // context created later with a smaller one does not fail the launches of
     // an earlier one.
+    // Some 60 functions, so only when the device's largest budget grows.
     std::lock_guard<std::mutex> lock(g_lds_mu);
-    if (c->lds_budget > g_lds_max) g_lds_max = c->lds_budget;
-    allow_cv_lds(g_lds_max);
-    // the neighbour build's staging is at most the budget, its rows beside it
-    const int rows = kBuildMaxThreads / 64 * build_row_width(4096) * 2 + 64 * 2;
-    allow_build_lds(g_lds_max + rows < lim ? g_lds_max + rows : lim);
+    int any = 0;  // a device past the table: each time
+    int& seen = dev >= 0 && dev < kMaxDevices ? g_lds_max[dev] : any;
+    if (c->lds_budget > seen) {
+      seen = c->lds_budget;
+      allow_cv_lds(c->lds_budget);
+      // the neighbour build's staging is at most the budget, its rows beside it
+      const int rows = kBuildMaxThreads / 64 * build_row_width(4096) * 2 + 64 * 2;
+      allow_build_lds(c->lds_budget + rows < lim ? c->lds_budget + rows : lim);
+    }
   }
 
   const size_t n = c->external ? 1 : (size_t)n_atoms, T = c->fp64 ? 8 : 4;  // no atom buffers for external CVs
