@@ -44,6 +44,7 @@ struct gm_ctx {
   int32_t *cnt = nullptr, *ccnt = nullptr, *err = nullptr, *stats = nullptr;
   int4* order = nullptr;  // per brick, by rank: (atom, halo slot, sorted position, 0)
   void *pos_s = nullptr, *qrow = nullptr, *grow = nullptr, *nb = nullptr, *cn_atom = nullptr, *cn_grad = nullptr;
+  void *dc = nullptr, *qn = nullptr, *fsum = nullptr;
   double *part_a = nullptr, *part_b = nullptr, *s_int = nullptr, *V_int = nullptr, *dV_int = nullptr;
   double *centres = nullptr, *heights = nullptr, *bias_part = nullptr;
   int64_t* hill_count = nullptr;
@@ -489,6 +490,10 @@ CvArgs<T> make_args(gm_ctx* c) {
     a.yc = c->ycd;
   a.qrow = reinterpret_cast<T*>(c->qrow);
   a.grow = reinterpret_cast<T*>(c->grow);
+  a.dc = reinterpret_cast<T*>(c->dc);
+  a.qn = reinterpret_cast<T*>(c->qn);
+  a.fsum = reinterpret_cast<T*>(c->fsum);
+  a.rad = a.pos_s;
   a.nb = reinterpret_cast<T*>(c->nb);
   a.cn_atom = reinterpret_cast<T*>(c->cn_atom);
   a.cn_grad = reinterpret_cast<T*>(c->cn_grad);
@@ -689,7 +694,7 @@ void free_all(gm_ctx* c) {
   c->cell = c->perm = c->owned_slot = c->owned_rank = c->owned_hcell = c->cnt = c->ccnt = nullptr;
   c->err = c->stats = nullptr;
   c->order = nullptr;
-  c->pos_s = c->nb = c->cn_atom = c->cn_grad = c->qrow = c->grow = nullptr;
+  c->pos_s = c->nb = c->cn_atom = c->cn_grad = c->qrow = c->grow = c->dc = c->qn = c->fsum = nullptr;
   c->s_int = c->V_int = c->dV_int = c->centres = c->heights = c->bias_part = nullptr;
   c->part_a = c->part_b = nullptr;
   c->hill_count = nullptr;
@@ -836,6 +841,8 @@ int gm_create(gm_ctx** out, const gm_params* params, int64_t n_atoms, void* hip_
       {(void**)&c->ccnt, n * 4 * 4},  // up to 4 parts per atom
       {(void**)&c->order, n * 16},   {(void**)&c->pos_s, n * 4 * T},
       {(void**)&c->cn_grad, c->has_cn ? n * 4 * T : 16},
+      {(void**)&c->dc, c->has_q6 ? n * T : 16}, {(void**)&c->qn, c->has_q6 ? n * T : 16},
+      {(void**)&c->fsum, c->has_q6 ? n * T : 16},
       {(void**)&c->centres, cap * c->dims * 8}, {(void**)&c->heights, cap * 8},
       {(void**)&c->bias_part, (size_t)c->bias_blocks * 3 * 8},
       {(void**)&c->build_dev, sizeof(BuildArgs)},

@@ -79,19 +79,35 @@ __device__ __forceinline__ bool stage_pos(const CvArgs<T>& a, const Brick& k, ve
   return out;
 }
 
-// LDS record of a slot: position, then the 16-wide row (4 vectors).
 template <typename T>
-__device__ __forceinline__ void stage_rows(const CvArgs<T>& a, const Brick& k, const T* rows, vec4_t<T>* lr) {
+__device__ __forceinline__ vec4_t<T> row_pos(const T* v) {
+  vec4_t<T> p;
+  p.x = v[0];
+  p.y = v[1];
+  p.z = v[2];
+  p.w = T(0);
+  return p;
+}
+
+// Passes 2-4 stage the 16-wide rows (position and q-hat or g: one 64-byte
+// record in FP32), vector q of slot s at lr[q cap + s]: the lanes' random slots
+// spread over all banks, as records of a power-of-two stride would not, and
+// nothing pads.  EXTRA: the scalar of each slot behind them (pass 3's c').
+// Staging and walk are bound by LDS reads and their latency in pass 2, by the
+// arithmetic in pass 4; with the position beside a row of 16 (80 bytes, five
+// reads a pair) passes 2, 3 and 4 took 13.5, 14.3 and 17.6 us at 96,000 atoms
+// (11.0, 13.5 and 17.3 now) and 16, 18 and 20 at 16,632 in FP64 (14, 15, 17.6).
+template <bool EXTRA, typename T>
+__device__ __forceinline__ void stage_rows(const CvArgs<T>& a, const Brick& k, const T* rows, const T* extra,
+                                           vec4_t<T>* lr) {
+  const int32_t cap = a.bg.cap;
 #pragma unroll 4
   for (int32_t s = threadIdx.x; s < k.ns; s += blockDim.x) {
     const int32_t r = a.bi.halo_rank[k.hb + s];
     const vec4_t<T>* src = reinterpret_cast<const vec4_t<T>*>(rows + (int64_t)r * 16);
-    vec4_t<T>* dst = lr + 5 * s;
-    dst[0] = a.pos_s[r];
-    dst[1] = src[0];
-    dst[2] = src[1];
-    dst[3] = src[2];
-    dst[4] = src[3];
+#pragma unroll
+    for (int q = 0; q < 4; q++) lr[q * cap + s] = src[q];
+    if (EXTRA) reinterpret_cast<T*>(lr + 4 * cap)[s] = extra[r];
   }
 }
 
@@ -104,24 +120,24 @@ __device__ __forceinline__ vec4_t<T> fetch_pos(const CvArgs<T>& a, const Brick& 
   return a.pos_s[a.bi.halo_rank[k.hb + s]];
 }
 
-template <bool ALL, typename T>
+template <bool ALL, bool EXTRA, typename T>
 __device__ __forceinline__ void fetch_rec(const CvArgs<T>& a, const Brick& k, const vec4_t<T>* lr, const T* rows,
-                                          int32_t s, vec4_t<T>& p, T v[16]) {
-  if (ALL || s < a.bg.cap) {
-    const vec4_t<T>* src = lr + 5 * s;
-    p = src[0];
+                                          const T* extra, int32_t s, T v[16], T& e) {
+  const int32_t cap = a.bg.cap;
+  if (ALL || s < cap) {
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-      const vec4_t<T> x = src[1 + q];
+      const vec4_t<T> x = lr[q * cap + s];
       v[4 * q + 0] = x.x;
       v[4 * q + 1] = x.y;
       v[4 * q + 2] = x.z;
       v[4 * q + 3] = x.w;
     }
+    if (EXTRA) e = reinterpret_cast<const T*>(lr + 4 * cap)[s];
   } else {
     const int32_t r = a.bi.halo_rank[k.hb + s];
-    p = a.pos_s[r];
     load_row16(rows + (int64_t)r * 16, v);
+    if (EXTRA) e = extra[r];
   }
 }
 
@@ -265,12 +281,13 @@ __device__ __forceinline__ T group_sum(T v, int TPA) {
 // current record only; past the row's end the stream yields slots of the same
 // row (its zero padding or an earlier 16 bytes again), which are valid
 // records.  Otherwise a fetch may go to global memory and stays guarded.
-template <bool ALL, typename T, class Body>
+template <bool ALL, bool EXTRA, typename T, class Body>
 __device__ __forceinline__ void walk_records(const CvArgs<T>& a, const Brick& k, const vec4_t<T>* lr, const T* rows,
-                                             const uint16_t* crow, int32_t n, int32_t ps, uint4 first, Body body) {
+                                             const T* extra, const uint16_t* crow, int32_t n, int32_t ps, uint4 first,
+                                             Body body) {
   if (n <= 0) return;
-  vec4_t<T> pa, pb;
-  T va[16], vb[16];
+  T va[16], vb[16], ea, eb;
+  ea = eb = T(0);
   if constexpr (ALL) {
     // blocks of 8 slots, written out: slot e of a block by constant index,
     // the next block's 16 bytes loaded at the block start (its first slot is
@@ -278,31 +295,31 @@ __device__ __forceinline__ void walk_records(const CvArgs<T>& a, const Brick& k,
     const uint4* src = reinterpret_cast<const uint4*>(crow);
     const int32_t last = (n - 1) >> 3;
     uint4 cur = first;
-    fetch_rec<ALL>(a, k, lr, rows, (int32_t)(cur.x & 0xffffu), pa, va);
+    fetch_rec<ALL, EXTRA>(a, k, lr, rows, extra, (int32_t)(cur.x & 0xffffu), va, ea);
     for (int32_t b = 0; b < n; b += 8) {
       const uint4 nxt = src[min((b >> 3) + 1, last) * ps];
       const uint32_t w[4] = {cur.x, cur.y, cur.z, cur.w};
 #pragma unroll
       for (int e = 0; e < 8; e += 2) {
-        fetch_rec<ALL>(a, k, lr, rows, (int32_t)(w[e >> 1] >> 16), pb, vb);
-        if (b + e < n) body(pa, va);
+        fetch_rec<ALL, EXTRA>(a, k, lr, rows, extra, (int32_t)(w[e >> 1] >> 16), vb, eb);
+        if (b + e < n) body(va, ea);
         const int32_t s2 = e + 2 < 8 ? (int32_t)(w[(e + 2) >> 1] & 0xffffu) : (int32_t)(nxt.x & 0xffffu);
-        fetch_rec<ALL>(a, k, lr, rows, s2, pa, va);
-        if (b + e + 1 < n) body(pb, vb);
+        fetch_rec<ALL, EXTRA>(a, k, lr, rows, extra, s2, va, ea);
+        if (b + e + 1 < n) body(vb, eb);
       }
       cur = nxt;
     }
   } else {
     SlotStream st;
     st.init_first(crow, n, ps, first);
-    fetch_rec<ALL>(a, k, lr, rows, st.pop(), pa, va);
+    fetch_rec<ALL, EXTRA>(a, k, lr, rows, extra, st.pop(), va, ea);
     for (int32_t j = 0; j < n; j += 2) {
       const bool b_ok = j + 1 < n;
-      if (b_ok) fetch_rec<ALL>(a, k, lr, rows, st.pop(), pb, vb);
-      body(pa, va);
+      if (b_ok) fetch_rec<ALL, EXTRA>(a, k, lr, rows, extra, st.pop(), vb, eb);
+      body(va, ea);
       if (b_ok) {
-        if (j + 2 < n) fetch_rec<ALL>(a, k, lr, rows, st.pop(), pa, va);
-        body(pb, vb);
+        if (j + 2 < n) fetch_rec<ALL, EXTRA>(a, k, lr, rows, extra, st.pop(), va, ea);
+        body(vb, eb);
       }
     }
   }
@@ -489,7 +506,6 @@ __device__ __forceinline__ double pass1_atoms(const CvArgs<T>& a, const Brick& k
     if (IN && part == 0) {  // what the gather does for larger systems
       if (!(isfinite(pi.x) && isfinite(pi.y) && isfinite(pi.z))) atomicOr(a.err, kErrNonFinite);
       if (WRAP && outside_box(make_float4((float)pi.x, (float)pi.y, (float)pi.z, 0.f), a.L, a.Llo)) atomicOr(a.err + 1, 1);
-      if (Q6) a.pos_s[ri] = pi;
     }
     const int32_t c = min(a.cnt[k.ob + o], a.kmax);
     const int32_t cp = c > part ? ((c - part - 1) >> TSH) + 1 : 0;
@@ -583,13 +599,12 @@ __device__ __forceinline__ double pass1_atoms(const CvArgs<T>& a, const Brick& k
         for (int m = 0; m < 13; m++) qq += Q[m] * Q[m];
         const T qn = g_sqrt(qq);
         const T inv = qn >= T(1e-12) ? T(1) / qn : T(0);
-        T rowv[16];
+        T rowv[16] = {pi.x, pi.y, pi.z};
 #pragma unroll
-        for (int m = 0; m < 13; m++) rowv[m] = Q[m] * inv;
-        rowv[13] = qn;
-        rowv[14] = T(0);
-        rowv[15] = fsum;
+        for (int m = 0; m < 13; m++) rowv[3 + m] = Q[m] * inv;
         store_row16(a.qrow + (int64_t)ri * 16, rowv);
+        a.qn[ri] = qn;
+        a.fsum[ri] = fsum;
       }
       if (CN) {
         a.cn_atom[ri] = cnsum;
@@ -639,13 +654,17 @@ __device__ __forceinline__ double pass2_atoms(const CvArgs<T>& a, const Brick& k
                                               const AtomHead& h0) {
   double c_part = 0.0;
   GM_FOR_RANKED(a, k, h0) {
-    vec4_t<T> pi;
-    T qi[16];
-    fetch_rec<ALL>(a, k, lr, a.qrow, si, pi, qi);
+    T vi[16], none;
+    fetch_rec<ALL, false>(a, k, lr, a.qrow, (const T*)nullptr, si, vi, none);
+    const vec4_t<T> pi = row_pos(vi);
+    const T* qi = vi + 3;
     T nbond = T(0);
-    walk_records<ALL>(a, k, lr, a.qrow, a.cut + row_first(a.bg, k.ob, o, part), nc, piece_stride(a.bg, k.O), h.c0, [&](const vec4_t<T>& pj, const T* qj) {
+    const uint16_t* crow = a.cut + row_first(a.bg, k.ob, o, part);
+    walk_records<ALL, false>(a, k, lr, a.qrow, (const T*)nullptr, crow, nc, piece_stride(a.bg, k.O), h.c0,
+                             [&](const T* vj, T) {
       T dx, dy, dz;
-      const T r2 = pair_vec<WRAP>(pi, pj, a, dx, dy, dz);
+      const T r2 = pair_vec<WRAP>(pi, row_pos(vj), a, dx, dy, dz);
+      const T* qj = vj + 3;
       const T r = r2 * g_rsqrt(r2);  // the same r as passes 3 and 4
       T df;
       const T f = taper_w(r, a, df);
@@ -658,7 +677,7 @@ __device__ __forceinline__ double pass2_atoms(const CvArgs<T>& a, const Brick& k
     if (part == 0) {
       const T cc = logistic((nbond - a.count_n0) * a.inv_count_w);
       const T dc = cc * (T(1) - cc) * a.inv_count_w;
-      a.qrow[(int64_t)ri * 16 + 14] = dc;
+      a.dc[ri] = dc;
       a.nb[ri] = nbond;
       c_part += (double)cc;
     }
@@ -673,7 +692,7 @@ __device__ __forceinline__ void pass2_body(const CvArgs<T>& a, int64_t brick, in
   __shared__ double red[BrickBlock<T>::value / 64];
   const Brick k = brick_begin(a, brick);
   AtomHead h0 = head_begin(a, k);
-  stage_rows(a, k, a.qrow, lr);
+  stage_rows<false>(a, k, a.qrow, (const T*)nullptr, lr);
   head_end(a, k, h0);
   __syncthreads();
   const double c_part = brick_variant(a, k, [&](auto all, auto wrap) {
@@ -689,17 +708,20 @@ template <typename T, bool ALL, bool WRAP>
 __device__ __forceinline__ void pass3_atoms(const CvArgs<T>& a, const Brick& k, const vec4_t<T>* lr,
                                             const AtomHead& h0) {
   GM_FOR_RANKED(a, k, h0) {
-    vec4_t<T> pi;
-    T qi[16];
-    fetch_rec<ALL>(a, k, lr, a.qrow, si, pi, qi);
-    const T dci = qi[14];
+    T vi[16], dci;
+    fetch_rec<ALL, true>(a, k, lr, a.qrow, a.dc, si, vi, dci);
+    const vec4_t<T> pi = row_pos(vi);
+    const T* qi = vi + 3;
     T hs[13];
 #pragma unroll
     for (int m = 0; m < 13; m++) hs[m] = T(0);
     T rx = T(0), ry = T(0), rz = T(0);
-    walk_records<ALL>(a, k, lr, a.qrow, a.cut + row_first(a.bg, k.ob, o, part), nc, piece_stride(a.bg, k.O), h.c0, [&](const vec4_t<T>& pj, const T* qj) {
+    const uint16_t* crow = a.cut + row_first(a.bg, k.ob, o, part);
+    walk_records<ALL, true>(a, k, lr, a.qrow, a.dc, crow, nc, piece_stride(a.bg, k.O), h.c0,
+                            [&](const T* vj, T dcj) {
       T dx, dy, dz;
-      const T r2 = pair_vec<WRAP>(pi, pj, a, dx, dy, dz);
+      const T r2 = pair_vec<WRAP>(pi, row_pos(vj), a, dx, dy, dz);
+      const T* qj = vj + 3;
       const T rinv = g_rsqrt(r2);
       const T r = r2 * rinv;
       T df;
@@ -708,7 +730,7 @@ __device__ __forceinline__ void pass3_atoms(const CvArgs<T>& a, const Brick& k, 
 #pragma unroll
       for (int m = 0; m < 13; m++) d += qi[m] * qj[m];
       const T b = logistic((d - a.bond_d0) * a.inv_bond_w);
-      const T cs = dci + qj[14];
+      const T cs = dci + dcj;
       const T coef = f * b * (T(1) - b) * a.inv_bond_w * cs;
 #pragma unroll
       for (int m = 0; m < 13; m++) hs[m] += coef * qj[m];
@@ -727,16 +749,18 @@ __device__ __forceinline__ void pass3_atoms(const CvArgs<T>& a, const Brick& k, 
       T proj = T(0);
 #pragma unroll
       for (int m = 0; m < 13; m++) proj += qi[m] * hs[m];
-      const T inv = qi[13] >= T(1e-12) ? T(1) / qi[13] : T(0);
-      T g[16];
+      const T qn = a.qn[ri];
+      const T inv = qn >= T(1e-12) ? T(1) / qn : T(0);
+      T g[16] = {pi.x, pi.y, pi.z};
 #pragma unroll
-      for (int m = 0; m < 13; m++) g[m] = (hs[m] - proj * qi[m]) * inv;
-      // the taper radial sum rides in the row's last three lanes, which pass 4
-      // reads with the atom's own staged record
-      g[13] = rx;
-      g[14] = ry;
-      g[15] = rz;
+      for (int m = 0; m < 13; m++) g[3 + m] = (hs[m] - proj * qi[m]) * inv;
       store_row16(a.grow + (int64_t)ri * 16, g);
+      vec4_t<T> rv;
+      rv.x = rx;
+      rv.y = ry;
+      rv.z = rz;
+      rv.w = T(0);
+      a.rad[ri] = rv;
     }
   }
 }
@@ -747,7 +771,7 @@ __device__ __forceinline__ void pass3_body(const CvArgs<T>& a, int64_t brick, in
   vec4_t<T>* lr = reinterpret_cast<vec4_t<T>*>(smem);
   const Brick k = brick_begin(a, brick);
   AtomHead h0 = head_begin(a, k);
-  stage_rows(a, k, a.qrow, lr);
+  stage_rows<true>(a, k, a.qrow, a.dc, lr);
   head_end(a, k, h0);
   __syncthreads();
   brick_variant(a, k, [&](auto all, auto wrap) {
@@ -765,13 +789,17 @@ __device__ __forceinline__ void pass4_atoms(const CvArgs<T>& a, const Brick& k, 
   const T seed_q = a.seed ? (T)a.seed[a.dims - 1] : T(1);
   const T seed_cn = (CN && a.seed) ? (T)(a.seed[0] * 2.0 * a.inv_n) : T(0);
   GM_FOR_RANKED(a, k, h0) {
-    vec4_t<T> pi;
-    T gi[16];
-    fetch_rec<ALL>(a, k, lr, a.grow, si, pi, gi);
+    T vi[16], none;
+    fetch_rec<ALL, false>(a, k, lr, a.grow, (const T*)nullptr, si, vi, none);
+    const vec4_t<T> pi = row_pos(vi);
+    const T* gi = vi + 3;
     T ax = T(0), ay = T(0), az = T(0);
-    walk_records<ALL>(a, k, lr, a.grow, a.cut + row_first(a.bg, k.ob, o, part), nc, piece_stride(a.bg, k.O), h.c0, [&](const vec4_t<T>& pj, const T* gj) {
+    const uint16_t* crow = a.cut + row_first(a.bg, k.ob, o, part);
+    walk_records<ALL, false>(a, k, lr, a.grow, (const T*)nullptr, crow, nc, piece_stride(a.bg, k.O), h.c0,
+                             [&](const T* vj, T) {
       T dx, dy, dz;
-      const T r2 = pair_vec<WRAP>(pi, pj, a, dx, dy, dz);
+      const T r2 = pair_vec<WRAP>(pi, row_pos(vj), a, dx, dy, dz);
+      const T* gj = vj + 3;
       const T rinv = g_rsqrt(r2);
       const T r = r2 * rinv;
       const T ux = dx * rinv, uy = dy * rinv, uz = dz * rinv;
@@ -799,14 +827,10 @@ __device__ __forceinline__ void pass4_atoms(const CvArgs<T>& a, const Brick& k, 
     ay = group_sum(ay, TPA);
     az = group_sum(az, TPA);
     if (part == 0) {
-      // the taper radial sum: the last lanes of the atom's own record, read
-      // again here rather than held through the walk
-      vec4_t<T> po;
-      T go[16];
-      fetch_rec<ALL>(a, k, lr, a.grow, si, po, go);
-      ax += go[13];
-      ay += go[14];
-      az += go[15];
+      const vec4_t<T> rv = a.rad[ri];  // the taper radial sum
+      ax += rv.x;
+      ay += rv.y;
+      az += rv.z;
       // the coordination gradient, kept by the forward pass
       vec4_t<T> cg;
       cg.x = cg.y = cg.z = cg.w = T(0);
@@ -823,7 +847,7 @@ __device__ __forceinline__ void pass4_body(const CvArgs<T>& a, int64_t brick, in
   vec4_t<T>* lr = reinterpret_cast<vec4_t<T>*>(smem);
   const Brick k = brick_begin(a, brick);
   AtomHead h0 = head_begin(a, k);
-  stage_rows(a, k, a.grow, lr);
+  stage_rows<false>(a, k, a.grow, (const T*)nullptr, lr);
   head_end(a, k, h0);
   __syncthreads();
   brick_variant(a, k, [&](auto all, auto wrap) {
@@ -915,8 +939,8 @@ __global__ __launch_bounds__(kBlock) void k_atom_values(CvArgs<T> a, int what, i
     v = (double)a.cn_atom[t];
   } else if (cv_kind != GM_CV_COORD) {
     if (what == GM_ATOM_Q6) {
-      const double fs = (double)a.qrow[t * 16 + 15];
-      v = fs > 0.0 ? sqrt(4.0 * M_PI / 13.0) * (double)a.qrow[t * 16 + 13] / fs : 0.0;
+      const double fs = (double)a.fsum[t];
+      v = fs > 0.0 ? sqrt(4.0 * M_PI / 13.0) * (double)a.qn[t] / fs : 0.0;
     } else if (what == GM_ATOM_NB) {
       v = (double)a.nb[t];
     } else if (what == GM_ATOM_C) {

@@ -159,8 +159,13 @@ struct CvArgs {
   T cn_r0inv2;  // 1/r0^2 of the coordination switch
   double inv_n;
   YCoef<T> yc;
-  T* qrow;          // [N][16] by sorted position: qhat(13), |Q|, c', sum f
-  T* grow;          // [N][16]: g(13), then the sum over taper pairs of (c'_i + c'_j) b_ij f'(r) r_hat (3)
+  T* qrow;          // [N][16] by sorted position: position (3), qhat (13)
+  T* grow;          // [N][16]: position (3), g (13)
+  T* dc;            // [N] c'
+  T* qn;            // [N] |Q|
+  T* fsum;          // [N] sum f
+  vec4_t<T>* rad;   // [N] sum over taper pairs of (c'_i + c'_j) b_ij f'(r) r_hat; the memory of pos_s, which
+                    // nothing reads between pass 1 and the next gather or rebuild
   T* nb;            // [N] bond counts
   T* cn_atom;       // [N] per-atom coordination sums
   T* cn_grad;       // [N][4] per-atom coordination gradient sum_j f'(r) r_hat (w = 0)
@@ -330,10 +335,11 @@ struct BiasSubset {
 hipError_t launch_bias_subset(const BiasSubset& s, hipStream_t st);
 hipError_t launch_sum_i32(const int32_t* v, int64_t n, unsigned long long* out, hipStream_t st);
 
-// LDS bytes of one staged halo slot: position only, or position + 16-wide row.
+// LDS bytes of one staged halo slot: position only, or the 16-wide row (which
+// begins with the position) and the scalar that pass 3 takes beside it.
 template <typename T>
 constexpr int slot_bytes(bool with_row) {
-  return (int)sizeof(vec4_t<T>) * (with_row ? 5 : 1);
+  return with_row ? (int)(4 * sizeof(vec4_t<T>) + sizeof(T)) : (int)sizeof(vec4_t<T>);
 }
 
 // Number of blocks launched for n atoms: a multiple of the XCD count.

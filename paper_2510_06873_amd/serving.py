@@ -104,7 +104,7 @@ def device_bytes(req: Request) -> int:
     per_atom += 4 * 7 + 2 * 2 * kmax            # cell, perm, owned tables, counts, neighbour + cutoff rows
     per_atom += 4 * t + 2 * t                   # sorted positions, bond count, coordination
     if p.cv_kind != 1:
-        per_atom += 16 * t * 2                  # q-hat and adjoint rows
+        per_atom += 16 * t * 2 + 3 * t          # q-hat and adjoint rows, |Q|, c', sum f
     per_atom += 4 * 8                           # halo slot table (bounded by 8 halo copies per atom)
     if n <= 1 << 17:                            # the halo slots' atoms beside their ranks
         per_atom += 4 * 8
