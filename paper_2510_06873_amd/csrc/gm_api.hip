@@ -378,20 +378,12 @@ void unit_roots(const double* p, int deg, double* out) {
 template <typename T>
 void make_ycoef(YCoef<T>& c) {
   const double D0[4] = {-5, 105, -315, 231}, D1[3] = {210, -1260, 1386}, D2[3] = {210, -3780, 6930};
-  const double D3[2] = {-7560, 27720}, D4[2] = {-7560, 83160}, D5 = 166320, D6 = 166320;
+  const double D3[2] = {-7560, 27720}, D4[2] = {-7560, 83160}, D5 = 166320;  // D5: of z, and of z^0 for m = 6
   double A[7];
   for (int m = 0; m <= 6; m++) {
     double K = sqrt(13.0 / (4.0 * M_PI) * fact(6 - m) / fact(6 + m));
     A[m] = m == 0 ? K : sqrt(2.0) * ((m & 1) ? -K : K);
   }
-  for (int k = 0; k < 4; k++) c.e0[k] = (T)(A[0] * D0[k] / 16.0);
-  for (int k = 0; k < 3; k++) c.e1[k] = (T)(A[1] * D1[k] / 16.0);
-  for (int k = 0; k < 3; k++) c.e2[k] = (T)(A[2] * D2[k] / 16.0);
-  for (int k = 0; k < 2; k++) c.e3[k] = (T)(A[3] * D3[k] / 16.0);
-  for (int k = 0; k < 2; k++) c.e4[k] = (T)(A[4] * D4[k] / 16.0);
-  c.e5 = (T)(A[5] * D5 / 16.0);
-  c.e6 = (T)(A[6] * D6 / 16.0);
-  for (int m = 0; m < 6; m++) c.rat[m] = (T)(A[m] / A[m + 1]);
   // Product form: every d^m P_6/dz^m has its 6-m zeros real and inside
   // (-1, 1) (Rolle), so its even/odd part has real roots t = z^2 in (0, 1).
   const double* P[5] = {D0, D1, D2, D3, D4};
@@ -403,6 +395,7 @@ void make_ycoef(YCoef<T>& c) {
     unit_roots(P[m], deg[m], roots);
     for (int k = 0; k < deg[m]; k++) c.t[at++] = (T)roots[k];
   }
+  for (int m = 5; m <= 6; m++) c.lead[m] = (T)(A[m] * D5 / 16.0);
 }
 
 int validate(const gm_params* p, int64_t n) {

@@ -594,6 +594,8 @@ __device__ __forceinline__ double pass1_atoms(const CvArgs<T>& a, const Brick& k
     }
     if (part == 0) {
       if (Q6) {
+#pragma unroll
+        for (int m = 0; m < 13; m++) Q[m] *= a.yc.lead[(m + 1) / 2];
         T qq = T(0);
 #pragma unroll
         for (int m = 0; m < 13; m++) qq += Q[m] * Q[m];
@@ -753,7 +755,8 @@ __device__ __forceinline__ void pass3_atoms(const CvArgs<T>& a, const Brick& k, 
       const T inv = qn >= T(1e-12) ? T(1) / qn : T(0);
       T g[16] = {pi.x, pi.y, pi.z};
 #pragma unroll
-      for (int m = 0; m < 13; m++) g[3 + m] = (hs[m] - proj * qi[m]) * inv;
+      for (int m = 0; m < 13; m++)  // with the factors that grad_s leaves out
+        g[3 + m] = (hs[m] - proj * qi[m]) * (inv * (m == 0 ? T(6) : T((m + 1) / 2)) * a.yc.lead[(m + 1) / 2]);
       store_row16(a.grow + (int64_t)ri * 16, g);
       vec4_t<T> rv;
       rv.x = rx;
@@ -808,20 +811,18 @@ __device__ __forceinline__ void pass4_atoms(const CvArgs<T>& a, const Brick& k, 
       T w[13];
 #pragma unroll
       for (int m = 0; m < 13; m++) w[m] = gi[m] + gj[m];
-      T S, Sx, Sy, Sz;
-      grad_s(a.yc, ux, uy, uz, w, S, Sx, Sy, Sz);
-      const T ud = ux * Sx + uy * Sy + uz * Sz;
+      T Sx, Sy, Sz;
+      grad_s(ux, uy, uz, w, Sx, Sy, Sz);
+      // f/r times the part of the gradient across u, plus df S along u
       const T fr = f * rinv;
-      T px = fr * (Sx - ud * ux);
-      T py = fr * (Sy - ud * uy);
-      T pz = fr * (Sz - ud * uz);
-      const T dS = df * S;  // zero below the taper shell
-      px += dS * ux;
-      py += dS * uy;
-      pz += dS * uz;
-      ax += px;
-      ay += py;
-      az += pz;
+      T along = -fr * (ux * Sx + uy * Sy + uz * Sz);
+      if (df != T(0)) along += df * sum_s(ux, uy, uz, w);
+      ax += fr * Sx;
+      ay += fr * Sy;
+      az += fr * Sz;
+      ax += along * ux;
+      ay += along * uy;
+      az += along * uz;
     });
     ax = group_sum(ax, TPA);
     ay = group_sum(ay, TPA);

@@ -140,17 +140,14 @@ __device__ __forceinline__ T taper_w(T r, const CvArgs<T>& a, T& df) {
 
 // FP32: with t = pi (x - 1/2), |t| <= pi/2, cos(pi x) = -sin t and
 // sin(pi x) = cos t, taken from their Taylor series (through t^13 and t^12:
-// truncation below 7e-9) for every pair, then selected.  The library sincos
-// behind a branch costs every wave that holds one pair in the taper shell,
-// which in disordered regions is nearly every wave; a wave with no lane in
-// the shell (ordered regions) skips the series.
+// truncation below 7e-9), shorter than the library sincos.  A wave with no
+// lane in the shell skips the branch.
 __device__ __forceinline__ float taper_w(float r, const CvArgs<float>& a, float& df) {
   constexpr double kF3 = 6.0, kF5 = kF3 * 20.0, kF7 = kF5 * 42.0, kF9 = kF7 * 72.0, kF11 = kF9 * 110.0,
                    kF13 = kF11 * 156.0;
   constexpr double kF2 = 2.0, kF4 = kF2 * 12.0, kF6 = kF4 * 30.0, kF8 = kF6 * 56.0, kF10 = kF8 * 90.0,
                    kF12 = kF10 * 132.0;
-  const bool in = r > a.taper_lo;
-  if (__ballot(in) == 0) {  // no lane of the wave in the taper shell
+  if (r <= a.taper_lo) {
     df = 0.0f;
     return 1.0f;
   }
@@ -170,51 +167,85 @@ __device__ __forceinline__ float taper_w(float r, const CvArgs<float>& a, float&
   cs = fmaf(cs, t2, (float)(1.0 / kF4));
   cs = fmaf(cs, t2, (float)(-1.0 / kF2));
   cs = fmaf(cs, t2, 1.0f);  // cos t
-  df = in ? -a.half_pi_over_D * cs : 0.0f;
-  return in ? fmaf(-0.5f, sn, 0.5f) : 1.0f;
+  df = -a.half_pi_over_D * cs;
+  return fmaf(-0.5f, sn, 0.5f);
 }
 
+// The z parts of the harmonics are used without their leading factors L_m, as
+// monic polynomials M_m(z) = E_m / L_m: M_5 = z and M_6 = 1 cost nothing, and
+// the factors are applied once per atom, to the sums of pass 1 and to the g
+// that pass 3 leaves for pass 4, instead of once per pair.  In pass 1 they come
+// from their roots: the products stay accurate near the zeros, where the power
+// form loses digits to cancellation (about 2e-6 absolute in FP32 for E_0; the
+// bond dots of pass 2 amplify that through two steep logistics).
 template <typename T>
-__device__ __forceinline__ void eval_E(const YCoef<T>& c, T z, T E[7]) {
+__device__ __forceinline__ void monic_roots(const YCoef<T>& c, T z, T M[6]) {
   const T z2 = z * z;
-  E[0] = c.e0[0] + z2 * (c.e0[1] + z2 * (c.e0[2] + z2 * c.e0[3]));
-  E[1] = z * (c.e1[0] + z2 * (c.e1[1] + z2 * c.e1[2]));
-  E[2] = c.e2[0] + z2 * (c.e2[1] + z2 * c.e2[2]);
-  E[3] = z * (c.e3[0] + z2 * c.e3[1]);
-  E[4] = c.e4[0] + z2 * c.e4[1];
-  E[5] = z * c.e5;
-  E[6] = c.e6;
+  M[0] = (z2 - c.t[0]) * (z2 - c.t[1]) * (z2 - c.t[2]);
+  M[1] = z * (z2 - c.t[3]) * (z2 - c.t[4]);
+  M[2] = (z2 - c.t[5]) * (z2 - c.t[6]);
+  M[3] = z * (z2 - c.t[7]);
+  M[4] = z2 - c.t[8];
+  M[5] = z;
 }
 
-// E_m from the roots: the products stay accurate near the zeros, where the
-// power form loses digits to cancellation (about 2e-6 absolute in FP32 for
-// E_0; the bond dots of pass 2 amplify that through two steep logistics).
-template <typename T>
-__device__ __forceinline__ void eval_E_roots(const YCoef<T>& c, T z, T E[7]) {
-  const T z2 = z * z;
-  E[0] = c.lead[0] * (z2 - c.t[0]) * (z2 - c.t[1]) * (z2 - c.t[2]);
-  E[1] = c.lead[1] * z * (z2 - c.t[3]) * (z2 - c.t[4]);
-  E[2] = c.lead[2] * (z2 - c.t[5]) * (z2 - c.t[6]);
-  E[3] = c.lead[3] * z * (z2 - c.t[7]);
-  E[4] = c.lead[4] * (z2 - c.t[8]);
-  E[5] = z * c.e5;
-  E[6] = c.e6;
-}
-
-// Q += f * v(u), v the real 13-vector of l = 6 harmonics:
+// Q += f * v(u) / L, v the real 13-vector of l = 6 harmonics:
 // v_0 = E_0, v_{2m-1} = E_m Re (ux + i uy)^m, v_{2m} = E_m Im (ux + i uy)^m.
 template <typename T>
 __device__ __forceinline__ void accumulate_y(const YCoef<T>& c, T ux, T uy, T uz, T f, T Q[13]) {
-  T E[7];
-  eval_E_roots(c, uz, E);
-  Q[0] += f * E[0];
+  T M[6];
+  monic_roots(c, uz, M);
+  Q[0] += f * M[0];
   // (R, I) = f (ux + i uy)^m: the weight rides along the recurrence
   T R = f * ux, I = f * uy;
 #pragma unroll
-  for (int m = 1; m <= 6; m++) {
-    Q[2 * m - 1] += E[m] * R;
-    Q[2 * m] += E[m] * I;
-    if (m < 6) {
+  for (int m = 1; m <= 5; m++) {
+    Q[2 * m - 1] += M[m] * R;
+    Q[2 * m] += M[m] * I;
+    const T R2 = R * ux - I * uy;
+    const T I2 = R * uy + I * ux;
+    R = R2;
+    I = I2;
+  }
+  Q[11] += R;
+  Q[12] += I;
+}
+
+// Gradient of S = g . v(u) with respect to (ux, uy, uz) taken as free variables
+// (v is a polynomial in them), w the g's of both atoms with the factors 6 L_0
+// and m L_m applied.  With zeta = ux + i uy and c_m = w_{2m-1} - i w_{2m},
+//   Sx - i Sy = sum_{m>=1} M_m c_m zeta^(m-1)  (d zeta^m = m zeta^(m-1)),
+//   Sz = M_1 w_0 + sum_{k=1..5} (6 - k)/k M_{k+1} Re c_k zeta^k
+// (dE_m/dz is a multiple of E_{m+1}, whose leading factor is 6 - m times as
+// large).  Pass 4 is bound by this arithmetic: 122 vector instructions a pair
+// below the taper shell (160 with the factors and S in every pair's sum), 133 ->
+// 125 us at 1,024,000 atoms and 17.3 -> 16.0 at 96,000.  Against 64 bits the
+// FP32 gradient errs as before (1.04e-5 in norm, mean of 24 half melted slabs).
+template <typename T>
+__device__ __forceinline__ void grad_s(T ux, T uy, T uz, const T w[13], T& Sx, T& Sy, T& Sz) {
+  const T z2 = uz * uz;
+  const T m1 = uz * (T(5.0 / 33) + z2 * (z2 - T(10.0 / 11)));
+  const T M[5] = {T(1.0 / 33) + z2 * (z2 - T(6.0 / 11)), uz * (z2 - T(3.0 / 11)), z2 - T(1.0 / 11), uz, T(1)};
+  constexpr double beta[5] = {5.0, 2.0, 1.0, 0.5, 0.2};
+  Sx = m1 * w[1];
+  Sy = m1 * w[2];
+  Sz = m1 * w[0];
+  T R = ux, I = uy;
+#pragma unroll
+  for (int k = 1; k <= 5; k++) {
+    const T A = k < 5 ? M[k - 1] * R : R, B = k < 5 ? M[k - 1] * I : I;
+    // one product per statement: each is one fused multiply-add
+    Sx += A * w[2 * k + 1];
+    Sx += B * w[2 * k + 2];
+    Sy += A * w[2 * k + 2];
+    Sy -= B * w[2 * k + 1];
+    if (k == 3) {  // beta = 1
+      Sz += A * w[2 * k - 1];
+      Sz += B * w[2 * k];
+    } else {
+      Sz += T(beta[k - 1]) * (A * w[2 * k - 1] + B * w[2 * k]);
+    }
+    if (k < 5) {
       const T R2 = R * ux - I * uy;
       const T I2 = R * uy + I * ux;
       R = R2;
@@ -223,43 +254,30 @@ __device__ __forceinline__ void accumulate_y(const YCoef<T>& c, T ux, T uy, T uz
   }
 }
 
-// S = w . v(u) and its gradient with respect to (ux, uy, uz) taken as free
-// variables (v is a polynomial in them).  d(zeta^m)/dux = m zeta^(m-1),
-// d(zeta^m)/duy = i m zeta^(m-1), dE_m/duz = rat_m E_{m+1}.
+// S itself (same w), which only pairs in the taper shell need:
+// S = M_0 w_0 / 6 + sum_m M_m Re(c_m zeta^m) / m.
 template <typename T>
-__device__ __forceinline__ void grad_s(const YCoef<T>& c, T ux, T uy, T uz, const T w[13], T& S,
-                                       T& Sx, T& Sy, T& Sz) {
-  T E[7];
-  eval_E(c, uz, E);
-  // m = 1 on its own: zeta^0 = 1, so U = w_1 and V = w_2 (no products with
-  // the zero imaginary part, which IEEE rules keep the compiler from folding)
-  const T T1 = w[1] * ux + w[2] * uy;
-  S = w[0] * E[0] + E[1] * T1;
-  Sx = E[1] * w[1];
-  Sy = E[1] * w[2];
-  Sz = w[0] * c.rat[0] * E[1] + c.rat[1] * E[2] * T1;
-  T Rp = ux, Ip = uy;
-  T R = ux * ux - uy * uy, I = ux * uy + uy * ux;
+__device__ __forceinline__ T sum_s(T ux, T uy, T uz, const T w[13]) {
+  const T z2 = uz * uz;
+  const T M[6] = {uz * (T(5.0 / 33) + z2 * (z2 - T(10.0 / 11))),
+                  T(1.0 / 33) + z2 * (z2 - T(6.0 / 11)),
+                  uz * (z2 - T(3.0 / 11)),
+                  z2 - T(1.0 / 11),
+                  uz,
+                  T(1)};
+  T S = w[0] * T(1.0 / 6) * (z2 * (T(5.0 / 11) + z2 * (z2 - T(15.0 / 11))) - T(5.0 / 231));
+  T R = ux, I = uy;
 #pragma unroll
-  for (int m = 2; m <= 6; m++) {
-    const T wa = w[2 * m - 1], wb = w[2 * m];
-    const T Tm = wa * R + wb * I;
-    const T U = wa * Rp + wb * Ip;
-    const T V = wb * Rp - wa * Ip;
-    const T mE = T(m) * E[m];
-    S += E[m] * Tm;
-    Sx += mE * U;
-    Sy += mE * V;
+  for (int m = 1; m <= 6; m++) {
+    S += T(1.0 / m) * M[m - 1] * (w[2 * m - 1] * R + w[2 * m] * I);
     if (m < 6) {
-      Sz += c.rat[m] * E[m + 1] * Tm;
       const T R2 = R * ux - I * uy;
       const T I2 = R * uy + I * ux;
-      Rp = R;
-      Ip = I;
       R = R2;
       I = I2;
     }
   }
+  return S;
 }
 
 template <typename T>

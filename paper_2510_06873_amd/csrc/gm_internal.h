@@ -67,16 +67,13 @@ constexpr int rank_lds_bytes() {
   return (BrickBlock<T>::value * (3 + kRankBins / 64) + kRankBins) * 4;
 }
 
-// Coefficients of E_m(z) = A_m d^m P_6/dz^m (z), the z part of the real l = 6
-// harmonics (A_0 = K_0, A_m = sqrt2 (-1)^m K_m), split by parity of z, plus
-// the ratios A_m / A_{m+1} that turn dE_m/dz into a multiple of E_{m+1}.
+// E_m(z) = A_m d^m P_6/dz^m (z), the z part of the real l = 6 harmonics
+// (A_0 = K_0, A_m = sqrt2 (-1)^m K_m), is lead_m z^(6-m mod 2) prod_k (z^2 - t_k):
+// its leading factor and the roots t of E_0 (3), E_1 (2), E_2 (2), E_3 (1) and
+// E_4 (1), all in (0, 1).
 template <typename T>
 struct YCoef {
-  T e0[4], e1[3], e2[3], e3[2], e4[2], e5, e6;  // E_m as polynomials in z^2 (times z for odd 6-m)
-  T rat[6];                                     // dE_m/dz = rat_m E_{m+1}
-  // The same E_m as lead_m z^(6-m mod 2) prod_k (z^2 - t_k): the roots t of
-  // E_0 (3), E_1 (2), E_2 (2), E_3 (1), E_4 (1), all in (0, 1).
-  T lead[5], t[9];
+  T lead[7], t[9];
 };
 
 // Geometry of the cell grid (FP64: the cell ids are part of the bit-exact sort).
