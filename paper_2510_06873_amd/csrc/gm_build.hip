@@ -468,7 +468,8 @@ __global__ __launch_bounds__(kBlock) void k_fill_gather(const int32_t* __restric
 // 0.72), the latency of staging and setting up below.  Against the form before
 // (8 lanes per atom testing 8 candidates of one run at a time, each entry
 // stored by itself): 1,024,000 atoms q6 223 -> 190 us, 108,000 atoms at r_c 6
-// 127 -> 92, 96,000 q6 60 -> 51, 864 atoms at r_c 6 66 -> 21.
+// 127 -> 92, 96,000 q6 60 -> 51, 864 atoms at r_c 6 66 -> 21 (without the shell's
+// pairs first, which cost a q6 build a fifth: see shell_bits).
 //
 // Slots in cells across a periodic face are staged as the image beside the
 // brick (slot_image), so that every test is a plain difference: a candidate
@@ -483,6 +484,12 @@ constexpr int kBuildChunks = 3;  // 192 candidates: the 27 cells of a q6 list ho
 
 __device__ __forceinline__ float lane_value(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// from + the lanes below this one in mask
+__device__ __forceinline__ int32_t lanes_below(uint64_t mask, int32_t from) {
+  return (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mask, (uint32_t)from));
 }
 
 // Position p of halo slot sl as the image in the halo cell that holds the slot.
@@ -650,19 +657,37 @@ __device__ __forceinline__ void build_rows(const vec4_t<T>* __restrict__ pos_s, 
           for (int u = 0; u < U; u++) to[u + 1] = to[u] + (int32_t)__popcll(pass[u]);
           uint16_t* const out = mine + i * width;
           int32_t k[U];
+          // pairs about the taper shell first (see shell_bits)
+          uint64_t front[U];
+          int32_t nf = 0;
+          if (g.shell_span != 0 && whole && to[U] <= kmax) {
 #pragma unroll
-          for (int u = 0; u < U; u++)
-            k[u] = (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(pass[u] >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)pass[u], 0u));
-          if (to[U] > kmax) {  // entries past the row's width are counted, not kept
+            for (int u = 0; u < U; u++) {
+              front[u] = pass[u] & __ballot(__float_as_uint(r2[u]) - g.shell_lo <= g.shell_span);
+              nf += (int32_t)__popcll(front[u]);
+            }
+          }
+          if (nf != 0) {
+            int32_t f = 0;
 #pragma unroll
-            for (int u = 0; u < U; u++) pass[u] &= __ballot(to[u] + k[u] < kmax);
+            for (int u = 0; u < U; u++) {
+              const int32_t kf = lanes_below(front[u], f), kr = lanes_below(pass[u] & ~front[u], to[u] - f + nf);
+              k[u] = __builtin_amdgcn_inverse_ballot_w64(front[u]) ? kf : kr;
+              f += (int32_t)__popcll(front[u]);
+            }
+          } else {
+#pragma unroll
+            for (int u = 0; u < U; u++) k[u] = lanes_below(pass[u], to[u]);
+            if (to[U] > kmax) {  // entries past the row's width are counted, not kept
+#pragma unroll
+              for (int u = 0; u < U; u++) pass[u] &= __ballot(k[u] < kmax);
+            }
           }
           // lanes that do not pass write to a place of their own that nothing
           // reads: straight code instead of a branch per chunk
 #pragma unroll
           for (int u = 0; u < U; u++)
-            *(__builtin_amdgcn_inverse_ballot_w64(pass[u]) ? out + to[u] + k[u] : spare) = (uint16_t)sl[u];
+            *(__builtin_amdgcn_inverse_ballot_w64(pass[u]) ? out + k[u] : spare) = (uint16_t)sl[u];
           count_l = lane == i ? to[U] : count_l;
         }
       }
@@ -860,8 +885,14 @@ __global__ __launch_bounds__(kBlock) void k_neighbor_ranks(const uint16_t* __res
     const int32_t r = bi.owned_rank[ob + k];
     const int32_t c = cnt[ob + k];
     const int32_t m = c < kmax ? c : kmax;
-    for (int32_t e = 0; e < m; e++)
-      nbr_out[(int64_t)r * kmax + e] = bi.halo_rank[hb + nbr[row_entry(g, ob, O, k, e % g.tpa, e / g.tpa)]];
+    auto slot = [&](int32_t e) { return (int32_t)nbr[row_entry(g, ob, O, k, e % g.tpa, e / g.tpa)]; };
+    // in slot order: the pairs near the taper shell and the others (build_rows) are two ascending runs
+    int32_t mid = 1;
+    while (mid < m && slot(mid) > slot(mid - 1)) mid++;
+    for (int32_t e = 0, p = 0, q = mid; e < m; e++) {
+      const bool second = p >= mid || (q < m && slot(q) < slot(p));
+      nbr_out[(int64_t)r * kmax + e] = bi.halo_rank[hb + slot(second ? q++ : p++)];
+    }
     cnt_out[r] = c;
   }
 }

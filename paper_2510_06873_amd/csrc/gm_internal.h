@@ -105,6 +105,9 @@ struct BrickGeom {
   int32_t build_split;    // workgroups per brick in the neighbour build (each takes a share of its atoms)
   int32_t build_cap;      // halo slots the neighbour build stages in LDS (slots beyond: global memory)
   int32_t build_win;      // atoms whose rows a wave of the neighbour build collects in LDS at a time
+  // r^2 about the taper shell, as the bits of a float and a span of bits: the
+  // pairs that a neighbour row lists first (see shell_bits)
+  uint32_t shell_lo, shell_span;
 };
 
 // The neighbour build collects rows in LDS, kBuildWin atoms per wave (a
