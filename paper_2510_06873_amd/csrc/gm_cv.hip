@@ -19,24 +19,71 @@ namespace gm {
 struct Brick {
   int64_t b;
   int32_t hb, H, ob, O, ns;
-  bool wrap;  // pairs may cross a periodic face: minimum image needed
+  bool wrap;      // pairs may cross a periodic face: minimum image needed
+  int32_t shift;  // axes (bits) on which the staged coordinates are shifted (to_frame)
 };
 
+// Plain pair differences unless the halo touches a face or a coordinate lies
+// outside the box.  In FP64 a brick on a face takes plain differences too, of
+// coordinates staged shifted: the shift is exact, so they are the bits that mic
+// gives, without its nine operations per axis and pair (16,632 atoms: passes
+// 1-4 18/13.5/14.8/15.4 -> 17.5/13/14.8/14.8 us).  It needs every pair of the
+// halo within half the box on the axis: the halo's cells and what their atoms
+// have moved, with a cell to spare.  In FP32, where the box length's low part
+// would have to be added for pairs of a shifted and an unshifted atom, a third
+// variant for that was slower (1,024,000 atoms 4,606 -> 4,756 us a window); so
+// was the coordination alone in boxes of few cells (864 atoms 243 -> 248).
+template <bool Q6, typename T>
+__device__ __forceinline__ void brick_wrap(const CvArgs<T>& a, Brick& k) {
+  const BrickShape s = brick_shape(k.b, a.bg);
+  const bool outside = a.err[1] != 0;  // the gather flagged a coordinate
+  k.wrap = halo_touches_face(s, a.bg) || outside;
+  if (sizeof(T) == 4 || !Q6 || !k.wrap || outside || k.H > a.bg.cap) return;
+  int32_t faces = 0;
+  bool fits = true;
+#pragma unroll
+  for (int d = 0; d < 3; d++)
+    if (s.o[d] < 2 || s.o[d] + s.e[d] > a.bg.nc[d] - 2) {
+      faces |= 1 << d;
+      fits = fits && 2 * (s.e[d] + 3) <= a.bg.nc[d];
+    }
+  if (fits) {
+    k.wrap = false;
+    k.shift = faces;
+  }
+}
+
 template <typename T>
+__device__ __forceinline__ void shift_in(const CvArgs<T>& a, const Brick& k, vec4_t<T>& p) {
+  if constexpr (sizeof(T) == 8) {
+    if (k.shift & 1) p.x = to_frame(p.x, a.L[0]);
+    if (k.shift & 2) p.y = to_frame(p.y, a.L[1]);
+    if (k.shift & 4) p.z = to_frame(p.z, a.L[2]);
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ void shift_out(const CvArgs<T>& a, const Brick& k, T* v) {
+  if constexpr (sizeof(T) == 8)
+#pragma unroll
+    for (int d = 0; d < 3; d++)
+      if (k.shift & (1 << d)) v[d] = from_frame(v[d], a.L[d]);
+}
+
+template <bool Q6 = true, typename T>
 __device__ __forceinline__ Brick brick_begin(const CvArgs<T>& a, int64_t brick) {
   Brick k;
   k.b = brick;
   k.hb = k.H = k.ob = k.O = k.ns = 0;
   k.wrap = true;
+  k.shift = 0;
   if (k.b < a.bg.nbricks) {
     k.hb = a.bi.hb[k.b];
     k.H = a.bi.hb[k.b + 1] - k.hb;
     k.ob = a.bi.ob[k.b];
     k.O = a.bi.ob[k.b + 1] - k.ob;
     k.ns = k.H < a.bg.cap ? k.H : a.bg.cap;
-    // plain pair differences unless the halo touches a face or the gather
-    // flagged a coordinate outside the box
-    k.wrap = halo_touches_face(brick_shape(k.b, a.bg), a.bg) || a.err[1] != 0;
+    brick_wrap<Q6>(a, k);
   }
   return k;
 }
@@ -71,9 +118,13 @@ __device__ __forceinline__ bool stage_pos(const CvArgs<T>& a, const Brick& k, ve
     if constexpr (IN) {
       const float4 p = a.pos_in[a.bi.halo_id[k.hb + s]];
       out = out || outside_box(p, a.L, a.Llo);
-      lp[s] = as_vec<T>(p);
+      vec4_t<T> q = as_vec<T>(p);
+      shift_in(a, k, q);
+      lp[s] = q;
     } else {
-      lp[s] = a.pos_s[a.bi.halo_rank[k.hb + s]];
+      vec4_t<T> q = a.pos_s[a.bi.halo_rank[k.hb + s]];
+      shift_in(a, k, q);
+      lp[s] = q;
     }
   }
   return out;
@@ -106,7 +157,11 @@ __device__ __forceinline__ void stage_rows(const CvArgs<T>& a, const Brick& k, c
     const int32_t r = a.bi.halo_rank[k.hb + s];
     const vec4_t<T>* src = reinterpret_cast<const vec4_t<T>*>(rows + (int64_t)r * 16);
 #pragma unroll
-    for (int q = 0; q < 4; q++) lr[q * cap + s] = src[q];
+    for (int q = 0; q < 4; q++) {
+      vec4_t<T> v = src[q];
+      if (q == 0) shift_in(a, k, v);
+      lr[q * cap + s] = v;
+    }
     if (EXTRA) reinterpret_cast<T*>(lr + 4 * cap)[s] = extra[r];
   }
 }
@@ -602,6 +657,7 @@ __device__ __forceinline__ double pass1_atoms(const CvArgs<T>& a, const Brick& k
         const T qn = g_sqrt(qq);
         const T inv = qn >= T(1e-12) ? T(1) / qn : T(0);
         T rowv[16] = {pi.x, pi.y, pi.z};
+        shift_out(a, k, rowv);
 #pragma unroll
         for (int m = 0; m < 13; m++) rowv[3 + m] = Q[m] * inv;
         store_row16(a.qrow + (int64_t)ri * 16, rowv);
@@ -628,12 +684,18 @@ __device__ __forceinline__ void pass1_body(const CvArgs<T>& a, int64_t brick, in
   extern __shared__ __align__(16) unsigned char smem[];
   vec4_t<T>* lp = reinterpret_cast<vec4_t<T>*>(smem);
   __shared__ double red[BrickBlock<T>::value / 64];
-  Brick k = brick_begin(a, brick);
+  Brick k = brick_begin<Q6>(a, brick);
   const bool out = stage_pos<IN>(a, k, lp);
-  if constexpr (IN)
+  if constexpr (IN) {
     k.wrap = __syncthreads_or(out) || k.wrap;
-  else
+    if (k.wrap && k.shift) {  // a coordinate outside the box: staged again as they are
+      k.shift = 0;
+      stage_pos<IN>(a, k, lp);
+      __syncthreads();
+    }
+  } else {
     __syncthreads();
+  }
   int32_t* keys = reinterpret_cast<int32_t*>(lp + a.bg.cap);
   const double cn_part = brick_variant(a, k, [&](auto all, auto wrap) {
     return pass1_atoms<T, CN, Q6, IN, decltype(all)::value, decltype(wrap)::value>(a, k, lp, keys);
@@ -754,6 +816,7 @@ __device__ __forceinline__ void pass3_atoms(const CvArgs<T>& a, const Brick& k, 
       const T qn = a.qn[ri];
       const T inv = qn >= T(1e-12) ? T(1) / qn : T(0);
       T g[16] = {pi.x, pi.y, pi.z};
+      shift_out(a, k, g);
 #pragma unroll
       for (int m = 0; m < 13; m++)  // with the factors that grad_s leaves out
         g[3 + m] = (hs[m] - proj * qi[m]) * (inv * (m == 0 ? T(6) : T((m + 1) / 2)) * a.yc.lead[(m + 1) / 2]);

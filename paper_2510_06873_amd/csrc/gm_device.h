@@ -124,6 +124,12 @@ __device__ __forceinline__ T pair_vec(const vec4_t<T>& pi, const vec4_t<T>& pj, 
   return dx * dx + dy * dy + dz * dz;
 }
 
+// A coordinate in the frame of a brick on a periodic face: atoms on the far
+// half of the box move by -L (exact for x >= L/2) and carry the sign bit, also
+// at -0.
+__device__ __forceinline__ double to_frame(double x, double L) { return x >= 0.5 * L ? -(L - x) : x + 0.0; }
+__device__ __forceinline__ double from_frame(double x, double L) { return __double_as_longlong(x) < 0 ? x + L : x; }
+
 // Cosine-tapered q6 weight f(r) = (1 + cos(pi x))/2, x = (r - r_lo)/D on
 // (r_lo, r_c), 1 below r_lo, and f'(r).
 template <typename T>
