@@ -35,11 +35,11 @@ HBM_PEAK_GBS = 8000.0
 ALU_PEAK_TFLOPS = 157.3
 ALU_NONPACKED_TFLOPS = 256 * 64 * 2 * 2.4e9 / 1e12
 # Algorithmic flops of k_pass4 per ordered pair inside r_c (FMA = 2): pair
-# vector and r^2 8, 1/r and unit vector 5, g_i + g_j 13, E_m(z) 22, S and its
-# gradient by the complex recurrence 144, tangential projection and
+# vector and r^2 8, 1/r and unit vector 5, g_i + g_j 13, the monic z polynomials
+# 14, the gradient of S by the complex recurrence 92, projection and
 # accumulation 18.  The minimum image (bookkeeping, not arithmetic of the
 # method) and the taper terms of the pairs in the last 0.2 A are not counted.
-FLOPS_PER_PAIR_P4 = 210
+FLOPS_PER_PAIR_P4 = 150
 # k_pass4's HBM traffic as measured by the FETCH_SIZE / WRITE_SIZE counters
 # (scaled by a plain copy kernel of known size), with a digest of the kernel
 # sources it was taken on: reported only while those sources are unchanged.

@@ -336,7 +336,8 @@ int gm_batch_deposit(gm_batch* batch);
 
 /* The same for some walkers only (each deposit as gm_deposit_hill would make
  * it, bitwise): which = host array of count distinct member indices (the
- * order of the last create or update); two launches per 64 walkers.
+ * order of the last create or update); one launch per 64 walkers, two where a
+ * hill capacity is above 8,192.
  * GM_ERR_INVALID_ARG for an index out of range or repeated, GM_ERR_STATE for a
  * walker not yet stepped (no CV value to deposit at). */
 int gm_batch_deposit_some(gm_batch* batch, const int32_t* which, int32_t count);
@@ -404,7 +405,8 @@ int gm_lattice_virial(const double* box, const double* dVdL, int32_t dims, doubl
  * where no sample fell.  The per-bin sums use FP64 atomics: reproducible to
  * about 1e-15 relative, not bit for bit.  Host lo, hi (double[dims]), nbins
  * (int32[dims]); dims 1 or 2; at most 2^24 bins.  Temporary device memory
- * comes from the stream-ordered allocator. */
+ * comes from the blocks the library keeps for reuse in stream order (from the
+ * stream-ordered allocator while the stream is capturing). */
 int gm_fes_reweight(const double* s_dev, const double* V_dev, int64_t T, int32_t dims, const double* lo,
                     const double* hi, const int32_t* nbins, double kBT, double* F_dev, void* hip_stream);
 

@@ -530,7 +530,7 @@ double pass_cost(const PassCost& k, double own, double halo, double list, double
 // a disordered region's.  The margin is an eighth of the skin: wide enough for
 // nearly all pairs between two rebuilds, and a pair that comes in from outside
 // it costs time only.  At 1,024,000 atoms, half of them disordered: pass 4
-// 125 -> 117 us, passes 1-3 1-2 us each, for a build of 217 -> 263 us; at 16,632
+// 125 -> 117 us, passes 1-3 1-2 us each, for a build of 217 -> 246 us; at 16,632
 // in FP64 19/14/15.5/16.6 -> 18/13.5/14.5/15.4.  Where a row is copied out it is
 // put back into slot order.
 void shell_bits(const gm_ctx* c, BrickGeom& g) {

@@ -147,7 +147,8 @@ __device__ __forceinline__ vec4_t<T> row_pos(const T* v) {
 // Staging and walk are bound by LDS reads and their latency in pass 2, by the
 // arithmetic in pass 4; with the position beside a row of 16 (80 bytes, five
 // reads a pair) passes 2, 3 and 4 took 13.5, 14.3 and 17.6 us at 96,000 atoms
-// (11.0, 13.5 and 17.3 now) and 16, 18 and 20 at 16,632 in FP64 (14, 15, 17.6).
+// (11.0, 13.5 and 17.3; 10.9, 12.8 and 15.1 with what came after) and 16, 18
+// and 20 at 16,632 in FP64 (14, 15, 17.6; now 13, 15, 14.8).
 template <bool EXTRA, typename T>
 __device__ __forceinline__ void stage_rows(const CvArgs<T>& a, const Brick& k, const T* rows, const T* extra,
                                            vec4_t<T>* lr) {

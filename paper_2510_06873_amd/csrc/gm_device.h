@@ -225,7 +225,8 @@ __device__ __forceinline__ void accumulate_y(const YCoef<T>& c, T ux, T uy, T uz
 // (dE_m/dz is a multiple of E_{m+1}, whose leading factor is 6 - m times as
 // large).  Pass 4 is bound by this arithmetic: 122 vector instructions a pair
 // below the taper shell (160 with the factors and S in every pair's sum), 133 ->
-// 125 us at 1,024,000 atoms and 17.3 -> 16.0 at 96,000.  Against 64 bits the
+// 125 us at 1,024,000 atoms (117 with the rows in shell order) and 17.3 -> 16.0
+// at 96,000 (15.1).  Against 64 bits the
 // FP32 gradient errs as before (1.04e-5 in norm, mean of 24 half melted slabs).
 template <typename T>
 __device__ __forceinline__ void grad_s(T ux, T uy, T uz, const T w[13], T& Sx, T& Sy, T& Sz) {
