@@ -45,8 +45,8 @@ FLOPS_PER_PAIR_P4 = 150
 # sources it was taken on: reported only while those sources are unchanged.
 TRAFFIC_FILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "k_pass4_wz1m_hbm_traffic.txt")
 KERNEL_SOURCES = ("gm_cv.hip", "gm_device.h", "gm_internal.h")
-# k_pass4 per owned atom: slot/rank tables 8, cutoff count 4, position 16, adjoint
-# row 64 (its last three lanes hold the taper term), permutation 4, force read +
+# k_pass4 per owned atom: slot/rank tables 8, cutoff count 4, adjoint row with the
+# position 64, taper radial sum 16, permutation 4, force read +
 # write 32
 P4_BYTES_PER_ATOM = 128
 # one MD step per atom: gather (perm 4, positions 16 read + 16 write), pass 1
