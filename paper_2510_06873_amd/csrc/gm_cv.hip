@@ -33,10 +33,14 @@ struct Brick {
 // would have to be added for pairs of a shifted and an unshifted atom, a third
 // variant for that was slower (1,024,000 atoms 4,606 -> 4,756 us a window); so
 // was the coordination alone in boxes of few cells (864 atoms 243 -> 248).
-template <bool Q6, typename T>
+// FLAG: the out-of-box flag was set by an earlier launch and is read here.  The
+// pass 1 that stages the caller's positions sets it itself, so that a read
+// could differ from wave to wave of a workgroup, which then staged some slots
+// shifted and some not; it decides by what it stages instead.
+template <bool Q6, bool FLAG, typename T>
 __device__ __forceinline__ void brick_wrap(const CvArgs<T>& a, Brick& k) {
   const BrickShape s = brick_shape(k.b, a.bg);
-  const bool outside = a.err[1] != 0;  // the gather flagged a coordinate
+  const bool outside = FLAG && a.err[1] != 0;
   k.wrap = halo_touches_face(s, a.bg) || outside;
   if (sizeof(T) == 4 || !Q6 || !k.wrap || outside || k.H > a.bg.cap) return;
   int32_t faces = 0;
@@ -70,7 +74,7 @@ __device__ __forceinline__ void shift_out(const CvArgs<T>& a, const Brick& k, T*
       if (k.shift & (1 << d)) v[d] = from_frame(v[d], a.L[d]);
 }
 
-template <bool Q6 = true, typename T>
+template <bool Q6 = true, bool FLAG = true, typename T>
 __device__ __forceinline__ Brick brick_begin(const CvArgs<T>& a, int64_t brick) {
   Brick k;
   k.b = brick;
@@ -83,7 +87,7 @@ __device__ __forceinline__ Brick brick_begin(const CvArgs<T>& a, int64_t brick) 
     k.ob = a.bi.ob[k.b];
     k.O = a.bi.ob[k.b + 1] - k.ob;
     k.ns = k.H < a.bg.cap ? k.H : a.bg.cap;
-    brick_wrap<Q6>(a, k);
+    brick_wrap<Q6, FLAG>(a, k);
   }
   return k;
 }
@@ -685,7 +689,7 @@ __device__ __forceinline__ void pass1_body(const CvArgs<T>& a, int64_t brick, in
   extern __shared__ __align__(16) unsigned char smem[];
   vec4_t<T>* lp = reinterpret_cast<vec4_t<T>*>(smem);
   __shared__ double red[BrickBlock<T>::value / 64];
-  Brick k = brick_begin<Q6>(a, brick);
+  Brick k = brick_begin<Q6, !IN>(a, brick);
   const bool out = stage_pos<IN>(a, k, lp);
   if constexpr (IN) {
     k.wrap = __syncthreads_or(out) || k.wrap;
