@@ -67,6 +67,7 @@ struct gm_ctx {
   int64_t version = 0;  // bumped whenever the kernel arguments may change
   uint64_t serial = 0;  // unique per context created in this process
   int lds_budget = 0;   // bytes of dynamic LDS for the staged halo
+  int lds_limit = 0;    // bytes of dynamic LDS a kernel may have
   YCoef<float> ycf;
   YCoef<double> ycd;
 };
@@ -641,6 +642,10 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
   g.build_cap = expect < cap ? expect : cap;
   g.build_threads = g.build_cap * (int)sizeof(float4) > 32768 ? kBuildMaxThreads : kBlock;
   g.build_win = build_window(c->kmax, g.build_threads);
+  // the rows it collects lie beside the halo: both within the device's LDS (a
+  // budget near the limit leaves no room for them, wide rows take 64 KiB)
+  const int room = (c->lds_limit - build_row_bytes(g, c->kmax)) / (int)sizeof(float4);
+  if (g.build_cap > room) g.build_cap = room > 1 ? room : 1;
   g.build_split = 1;
   if (g.nbricks < kBuildFillBlocks) {
     int split = (kBuildFillBlocks + g.nbricks - 1) / g.nbricks;
@@ -830,6 +835,7 @@ int gm_create(gm_ctx** out, const gm_params* params, int64_t n_atoms, void* hip_
     int want = params->lds_kb > 0 ? params->lds_kb * 1024 : 80 * 1024;
     if (want > lim) want = lim;
     c->lds_budget = want - 2048;
+    c->lds_limit = lim - 2048;
     // The kernels' LDS limit is an attribute of the function, shared by every
     // context: keep it at the largest budget any context asked for, so that a
     // context created later with a smaller one does not fail the launches of
@@ -843,7 +849,7 @@ int gm_create(gm_ctx** out, const gm_params* params, int64_t n_atoms, void* hip_
       allow_cv_lds(c->lds_budget);
       // the neighbour build's staging is at most the budget, its rows beside it
       const int rows = kBuildMaxThreads / 64 * build_row_width(4096) * 2 + 64 * 2;
-      allow_build_lds(c->lds_budget + rows < lim ? c->lds_budget + rows : lim);
+      allow_build_lds(c->lds_budget + rows < c->lds_limit ? c->lds_budget + rows : c->lds_limit);
     }
   }
 

@@ -121,8 +121,11 @@ inline int32_t build_window(int32_t kmax, int threads) {
   const int32_t w = kBuildRowBytes / (threads / 64 * build_row_width(kmax) * 2);
   return w < 1 ? 1 : (w > kBuildWin ? kBuildWin : w);
 }
+inline int32_t build_row_bytes(const BrickGeom& g, int32_t kmax) {
+  return g.build_threads / 64 * g.build_win * build_row_width(kmax) * 2 + 64 * 2;
+}
 inline size_t build_lds_bytes(const BrickGeom& g, int32_t kmax) {
-  return (size_t)g.build_cap * 16 + (size_t)(g.build_threads / 64 * g.build_win) * build_row_width(kmax) * 2 + 64 * 2;
+  return (size_t)g.build_cap * 16 + (size_t)build_row_bytes(g, kmax);
 }
 
 struct BrickIndex {
