@@ -66,7 +66,7 @@ struct gm_ctx {
   int last_status = GM_OK;
   int64_t version = 0;  // bumped whenever the kernel arguments may change
   uint64_t serial = 0;  // unique per context created in this process
-  int lds_budget = 0;   // bytes of dynamic LDS for the staged halo
+  int lds_budget = 0;   // bytes of dynamic LDS for the staged halo (negative: too few for the static arrays)
   int lds_limit = 0;    // bytes of dynamic LDS a kernel may have
   YCoef<float> ycf;
   YCoef<double> ycd;
@@ -947,6 +947,7 @@ int prepare_build(gm_ctx* c, const float* pos4, const double* box) {
     if (k > 4096.0) return GM_ERR_INVALID_ARG;
     nc[a] = (int32_t)k;
   }
+  if (c->lds_budget < 0) return GM_ERR_HIP;  // no launch could stage anything
   const int64_t ncells = (int64_t)nc[0] * nc[1] * nc[2];
   if (ncells > c->ncells_cap) {
     dfree_c(c, c->cells_blk);

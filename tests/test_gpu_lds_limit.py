@@ -1,5 +1,6 @@
 """LDS budgets near the device's limit with halos that fill them, and rows as wide as they may be: the neighbour
-build's staging and its rows fit together, and the lists are those of brute force (halos staged in part among them)."""
+build's staging and its rows fit together, and the lists are those of brute force (halos staged in part among them).
+A budget that leaves nothing to stage in is refused before anything is launched."""
 import numpy as np
 import pytest
 
@@ -34,3 +35,15 @@ def test_dense_halos_near_the_limit(orc, r_list, lds_kb, brick, kmax, precision)
     assert torch.allclose(s, other.cv_forward(p4), rtol=1e-5 if precision == 0 else 1e-10, atol=0.0)
     pipe.close()
     other.close()
+
+
+@pytest.mark.parametrize("kind", [1, 2, 3])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_a_budget_below_the_static_arrays_is_refused(kind, precision):
+    from paper_2510_06873_amd import GmError, Params, Pipeline
+
+    d = W.wurtzite_slab(4, 3, 4, seed=32)
+    pipe = Pipeline(len(d["pos"]), Params(cv_kind=kind, precision=precision, sigma=[1.0, 1.0], hill_capacity=4, lds_kb=1))
+    with pytest.raises(GmError, match="HIP"):
+        pipe.build_neighbors(to_dev(W.as_float4(d["pos"])), d["box"])
+    pipe.close()
