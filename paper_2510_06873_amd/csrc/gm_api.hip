@@ -62,6 +62,7 @@ struct gm_ctx {
   std::unordered_map<void*, size_t> held;  // device allocations of the context and their sizes
   size_t held_bytes = 0;
   bool built = false, fwd = false, bwd = false;
+  bool counts_clear = false;  // the cell counts are zero after the work enqueued so far
   const float* fwd_pos = nullptr;  // positions of the last forward pass
   int last_status = GM_OK;
   int64_t version = 0;  // bumped whenever the kernel arguments may change
@@ -956,8 +957,8 @@ int prepare_build(gm_ctx* c, const float* pos4, const double* box) {
     const Piece pieces[] = {{(void**)&c->count, (size_t)ncells * 4}, {(void**)&c->start, (size_t)(ncells + 1) * 4},
                             {(void**)&c->scan_tmp, (size_t)tiles * 4}};
     GM_TRY(carve(c, &c->cells_blk, pieces, 3));
-    GM_TRY(hip_rc(launch_fill_i32(c->count, 0, ncells, c->stream)));  // zero between rebuilds
     c->ncells_cap = ncells;
+    c->counts_clear = false;
   }
   c->ncells = ncells;
   for (int a = 0; a < 3; a++) {
@@ -970,6 +971,16 @@ int prepare_build(gm_ctx* c, const float* pos4, const double* box) {
   choose_bricks(c, nc);
   GM_TRY(reserve_bricks(c));
   c->built = c->fwd = c->bwd = false;
+  return GM_OK;
+}
+
+// The cell counts are zero between rebuilds: the scan that reads them clears
+// them.  New ones, and those of a rebuild that was not enqueued whole, are
+// cleared first; so are those of a rebuild that goes into a graph, which may be
+// replayed after any other, or never (then what it did not do is still to do).
+int begin_counts(gm_ctx* c, bool graph, hipStream_t st) {
+  if (graph || !c->counts_clear) GM_TRY(hip_rc(launch_fill_i32(c->count, 0, c->ncells_cap, st)));
+  if (!graph) c->counts_clear = false;  // until its scan is enqueued too
   return GM_OK;
 }
 
@@ -1042,11 +1053,10 @@ extern "C" {
 
 int gm_build_neighbors(gm_ctx* c, const float* pos4, const double* box) {
   GM_TRY(prepare_build(c, pos4, box));
-  const int rc = enqueue_build(c, pos4, c->stream);
-  if (rc != GM_OK) {
-    c->ncells_cap = 0;  // the counts may be left unscanned: allocate and clear them again
-    return rc;
-  }
+  const bool graph = capturing(c->stream);
+  GM_TRY(begin_counts(c, graph, c->stream));
+  GM_TRY(enqueue_build(c, pos4, c->stream));
+  if (!graph) c->counts_clear = true;
   c->built = true;
   c->version++;
   return GM_OK;
@@ -1707,16 +1717,14 @@ int batch_build(gm_batch* B, const int32_t* which, int32_t count, const double* 
     gm_batch* B;
     const int32_t* which;
     int32_t count;
-    bool done = false;
     ~Restore() {
-      for (int32_t i = 0; i < count; i++) {
-        B->walkers[which[i]]->stream = B->stream;
-        if (!done) B->walkers[which[i]]->ncells_cap = 0;  // counts that may be left unscanned are allocated again
-      }
+      for (int32_t i = 0; i < count; i++) B->walkers[which[i]]->stream = B->stream;
     }
   } restore{B, which, count};
   for (int32_t i = 0; i < count; i++) B->walkers[which[i]]->stream = st;
   for (int32_t i = 0; i < count; i++) GM_TRY(prepare_build(B->walkers[which[i]], B->pos[which[i]], boxes + 3 * i));
+  const bool graph = capturing(st);
+  for (int32_t i = 0; i < count; i++) GM_TRY(begin_counts(B->walkers[which[i]], graph, st));
   std::vector<const BuildArgs*> dev;
   std::vector<BuildArgs> host;
   auto flush = [&]() -> int {
@@ -1745,10 +1753,10 @@ int batch_build(gm_batch* B, const int32_t* which, int32_t count, const double* 
   if (!dev.empty()) GM_TRY(flush());
   for (int32_t i = 0; i < count; i++) {
     gm_ctx* c = B->walkers[which[i]];
+    if (!graph) c->counts_clear = true;
     c->built = true;
     c->version++;
   }
-  restore.done = true;
   return GM_OK;
 }
 
