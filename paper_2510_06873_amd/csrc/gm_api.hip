@@ -500,31 +500,45 @@ CvArgs<T> make_args(gm_ctx* c) {
   return a;
 }
 
-// Time of the CV passes of one step (us, to a scale) for bricks of `own` owned
-// and `halo` staged atoms, nb workgroups of blk threads, tpa lanes per atom
-// and lists of `list` atoms: a launch, the walk of one workgroup's longest
-// lane (what a system of few workgroups takes however many CUs are idle), and
-// the work a CU gets when it holds several (staging, and each wave's walk).
-// Fitted to steps timed over 26 systems of 864 to 203,000 atoms, fcc and
-// wurtzite, with up to 42 brick shapes and lane counts each; its choice is
-// within 2% (mean) and 8% (worst) of the fastest of them.
-struct PassCost {
-  double launch, walk, stage_halo, cu_halo, cu_walk, cu_brick;
+// Estimated times of a brick shape, for the choice below (fitted, see there).
+struct ShapeCost {
+  double spread[3];  // atoms of a full brick above the mean, in square roots of it: three equally likely cases
+  // one step of one system (us): what it takes in any case, per atom of the
+  // longest lane's walk and per round of a workgroup's lanes (both for each set
+  // of workgroups that are resident together), and on the CU with the most
+  // workgroups per wave and walked atom, per wave, per staged atom and per
+  // workgroup; per atom of the system
+  double base, walk, round, cu_walk, cu_wave, cu_halo, cu_brick, atom;
+  // its share of a batch that fills the chip (us): per walker; per workgroup
+  // and atom of the longest lane's walk; per wave and walked atom; per wave; per
+  // staged atom; per workgroup; per atom
+  double b_base, b_walk, b_wwalk, b_wave, b_halo, b_brick, b_atom;
 };
-constexpr PassCost kCostQ6[2] = {{14.4, 0.954, 0.0, 0.00862, 0.0993, 6.71}, {14.3, 1.33, 0.0, 0.00408, 0.412, 13.8}};
-constexpr PassCost kCostCoord[2] = {{10.0, 0.0886, 0.162, 0.000925, 0.00855, 1.05},
-                                    {13.3, 0.0782, 0.0723, 0.00028, 0.0201, 0.725}};
+constexpr ShapeCost kCostQ6[2] = {{{0.75, 1.5, 2.8}, 16.8, 1.01, 2.11, 0.0172, 0.363, 0.00645, 1.78, 4.7e-05,
+                                   0.449, 0.00176, 0.00066, 0.0026, 1.96e-05, 0.0154, 0.0},
+                                  {{1.5, 1.5, 1.5}, 22.4, 1.38, 3.49, 0.0, 0.235, 0.0271, 0.0, 0.0,
+                                   0.714, 0.00223, 0.000579, 0.00298, 9.45e-05, 0.0127, 0.0}};
+constexpr ShapeCost kCostCoord[2] = {{{1.5, 1.5, 1.5}, 8.48, 0.138, 0.181, 0.00529, 0.0, 6.81e-05, 0.94, 7.22e-05,
+                                      0.159, 0.000406, 3.19e-05, 0.0, 0.0, 0.00723, 0.000133},
+                                     {{1.5, 1.5, 1.5}, 9.55, 0.155, 0.498, 0.00989, 0.0, 0.000563, 0.25, 8.7e-05,
+                                      0.185, 0.000293, 0.000103, 0.0, 0.0, 0.00651, 0.000169}};
+
+// Workgroups of a shape's passes per CU, by their LDS: two of a q6 CV (its rows
+// take half a CU).  The coordination stages positions only and its registers
+// allow four: the largest share of a CU's LDS (a quarter, a third, a half) that
+// still holds the halo it expects.
+int expected_halo(double halo) { return (int)std::ceil(1.25 * halo) + 64; }
+int lds_share(int wg, int rec) { return (160 * 1024 / wg - 2048) / rec; }
+int cu_workgroups(const gm_ctx* c, double halo, int rec) {
+  if (!c->has_q6)
+    for (int wg = 4; wg > 2; wg--)
+      if (lds_share(wg, rec) >= expected_halo(halo)) return wg;
+  return 2;
+}
 
 // Atoms of a full brick where the mean is `own`: a workgroup whose lanes the
-// mean just fills takes a second round in most of its bricks.
-double full_brick(double own) { return own + 1.5 * std::sqrt(own); }
-
-double pass_cost(const PassCost& k, double own, double halo, double list, double nb, int blk, int tpa) {
-  const double lanes = own * tpa, walk = list / tpa * std::ceil(tpa * full_brick(own) / blk);
-  const double waves = std::ceil((lanes < blk ? lanes : (double)blk) / 64.0), per_cu = nb < 256.0 ? 1.0 : nb / 256.0;
-  return k.launch + k.walk * walk + k.stage_halo * halo / blk +
-         per_cu * (k.cu_halo * halo + k.cu_walk * waves * walk + k.cu_brick);
-}
+// mean just fills takes a second round in some of its bricks.
+double full_brick(double own, double spread) { return own + spread * std::sqrt(own); }
 
 // The pairs of a q6 list that are, or by a small move come to be, in the taper
 // shell are listed first, so that the lanes of a wave meet the taper's series
@@ -547,22 +561,25 @@ void shell_bits(const gm_ctx* c, BrickGeom& g) {
   g.shell_span = hb - g.shell_lo;
 }
 
-// Brick size and threads per atom: among the bricks whose expected halo (atoms
-// of the (b+2)^3 cells around them, 5% margin) fits the LDS staging budget, the
-// pair of least estimated time.  Large systems get bricks that fill a
-// workgroup with few lanes per atom (the least staging per atom), small ones
-// small bricks and four lanes per atom (the shortest walk): with the large
-// bricks alone 864 atoms ran in 8 workgroups (30.6 us per step in FP64, now
-// 16.2) and 16,632 in 96 (46.7, now 36.3).
-//
-// q6 bricks may stage at most kStage times the cells they own: the choice must
-// not depend on what else runs (a batched walker equals the same walker alone),
-// and in a batch that fills the chip small bricks cost their staging (2x2x2
-// bricks of four lanes 215 us against 113 for 3x3x4 of two at 201,600 atoms,
-// 2x3x3 144).  Systems below kSmallAtoms, a small part of any such batch, and
-// FP64 ones may stage more: 5,376 atoms 45 -> 34 us, 2,048 in FP64 60 -> 45.
-constexpr double kStage = 5.6, kStageSmall = 8.0, kStageFp64 = 10.0;
-constexpr int64_t kSmallAtoms = 8192;
+// Brick size and threads per atom, among the bricks whose expected halo (atoms
+// of the (b+2)^3 cells around them, 5% margin) fits the LDS staging budget.
+// Small bricks of four lanes per atom give one system its shortest step, large
+// ones of one or two lanes, which stage less per atom, give a batch that fills
+// the chip its highest rate (3,120 atoms, q6 in FP32: 2x2x2 of four lanes 30.6 us
+// a step alone and 3.72 a walker in a batch, 3x3x3 of two 40.5 and 2.63).  One
+// choice serves both, since a batched walker equals the same walker alone: the
+// least product of the two times, both estimated, alone counting 2.5 times for
+// the q6 CVs.  (Counted once, some q6 systems get slower alone than with the
+// lanes best filled; counted 2.5 times, the coordination loses 2-3% in batches
+// for 1-2% alone.)
+// The estimates are fitted to the steps of 300 systems alone (768 to 384,160
+// atoms, fcc and wurtzite, most of the latter half melted, each with up to 187
+// shapes) and of 223 of them in batches of up to 64.  Fitted on two thirds of
+// them, their choice for the last third is above the fastest shape alone by
+// 2.8% (mean; 11% worst) for q6 in FP32, 3.5% (30%) in FP64, 3.7% (14%) for the
+// coordination in FP32 and 7.2% (32%) in FP64, and above the fastest batch by 31,
+// 14, 7 and 11%; the shape whose atoms best fill a workgroup's lanes is above
+// them by 9.6, 13, 47 and 54% alone and by 26, 22, 14 and 18% in batches.
 void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
   const int rec = c->fp64 ? slot_bytes<double>(c->has_q6) : slot_bytes<float>(c->has_q6);
   const int cap = c->lds_budget / rec;  // pass 1 of a q6 CV adds rank keys to its positions, still less than the rows
@@ -570,9 +587,9 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
   const double rho = (double)c->n / ((double)nc[0] * nc[1] * nc[2]);
   int best[3] = {1, 1, 1}, best_tpa = 1;
   double best_cost = -1.0;
-  const PassCost& model = (c->has_q6 ? kCostQ6 : kCostCoord)[c->fp64 ? 1 : 0];
-  const double list = 4.0 / 3.0 * M_PI * rho;  // atoms within one cell width
-  const double stage = c->fp64 ? kStageFp64 : (c->n < kSmallAtoms ? kStageSmall : kStage);
+  const ShapeCost& k = (c->has_q6 ? kCostQ6 : kCostCoord)[c->fp64 ? 1 : 0];
+  const double list = 4.0 / 3.0 * M_PI * c->r_list * c->r_list * c->r_list * (double)c->n /
+                      (c->box[0] * c->box[1] * c->box[2]);  // atoms of a mean list
   const bool fixed = c->p.brick[0] > 0;
   for (int bx = 1; bx <= kMaxBrick && bx <= nc[0]; bx++)
     for (int by = 1; by <= kMaxBrick && by <= nc[1]; by++)
@@ -585,19 +602,29 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
         const double own = (double)bx * by * bz * rho;
         if (!fixed && halo * 1.05 > cap) continue;
         // pass 1 ranks at most a workgroup of atoms (the others keep cell order)
-        if (!fixed && c->has_q6 && full_brick(own) > blk) continue;
-        const double nb = std::ceil((double)nc[0] / bx) * std::ceil((double)nc[1] / by) * std::ceil((double)nc[2] / bz);
-        const double over = c->has_q6 && halo > stage * own ? 1e9 : 0.0;  // only where nothing else fits
+        if (!fixed && c->has_q6 && full_brick(own, 1.5) > blk) continue;
+        const double nb[3] = {std::ceil((double)nc[0] / bx), std::ceil((double)nc[1] / by), std::ceil((double)nc[2] / bz)};
+        const double bricks = nb[0] * nb[1] * nb[2];
+        const double staged = (nc[0] + 2 * nb[0]) * (nc[1] + 2 * nb[1]) * (nc[2] + 2 * nb[2]) * rho;
+        const double full[3] = {full_brick(own, k.spread[0]), full_brick(own, k.spread[1]), full_brick(own, k.spread[2])};
+        const int wg = cu_workgroups(c, halo, rec);
+        const double sets = std::ceil(bricks / (256.0 * wg));
+        // workgroups on the CU with the most of them (in many sets: on average,
+        // and a half for the end)
+        const double most = bricks <= 512.0 ? std::ceil(bricks / 256.0) : bricks / 256.0 + 0.5;
         for (int tpa = 1; tpa <= 4; tpa *= 2) {
           if (c->p.tpa > 0 && tpa != c->p.tpa) continue;
-          const double cost = pass_cost(model, own, halo, list, nb, blk, tpa) + over;
-          // bricks of as many cells and lanes, in several rounds of workgroups:
-          // the one shorter along x, whose neighbours in launch order share
-          // more of its halo in their XCD's L2 (1,024,000 atoms: 3x4x4 cells
-          // 4,545 us a window, 4x4x3 4,615; in one round the cells' edges
-          // decide, 16,632 atoms in FP64 800 -> 849)
-          const bool same = nb > 1024.0 && tpa == best_tpa && bx * by * bz == best[0] * best[1] * best[2];
-          if (best_cost < 0.0 || cost < (same ? 0.99 : 1.0) * best_cost) {
+          double rounds = 0.0;
+          for (double f : full) rounds += std::ceil(tpa * f / blk) / 3.0;
+          const double walk = list / tpa;
+          const double waves = (double)c->n / bricks * tpa / 64.0 + 0.5;  // of a mean brick
+          const double alone = k.base + sets * rounds * (k.walk * walk + k.round) + k.atom * (double)c->n +
+                               most * (waves * (k.cu_walk * walk + k.cu_wave) + k.cu_halo * halo + k.cu_brick);
+          const double batched = k.b_base + k.b_halo * staged + k.b_atom * (double)c->n +
+                                 bricks * (2.0 / wg * (k.b_walk * rounds * walk + k.b_brick) +
+                                           waves * (k.b_wwalk * walk + k.b_wave));
+          const double cost = (c->has_q6 ? alone * alone * std::sqrt(alone) : alone) * batched;
+          if (best_cost < 0.0 || cost < best_cost) {
             best_cost = cost;
             best[0] = bx;
             best[1] = by;
@@ -617,19 +644,9 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
   shell_bits(c, g);
   const double own = (double)best[0] * best[1] * best[2] * rho;
   const double halo = (double)(best[0] + 2) * (best[1] + 2) * (best[2] + 2) * rho;
-  const int expect = (int)std::ceil(1.25 * halo) + 64;
-  // The coordination pass stages positions only and its registers allow four
-  // workgroups per CU: it takes the largest share of a CU's LDS (a quarter, a
-  // third, a half) that still holds the halo it expects.
+  const int expect = expected_halo(halo), wg = cu_workgroups(c, halo, rec);
   g.cap = cap;
-  if (!c->has_q6)
-    for (int wg = 4; wg > 2; wg--) {
-      const int share = (160 * 1024 / wg - 2048) / rec;
-      if (share >= expect) {
-        g.cap = share < cap ? share : cap;
-        break;
-      }
-    }
+  if (!c->has_q6 && wg > 2 && lds_share(wg, rec) < cap) g.cap = lds_share(wg, rec);
   g.blocks = (g.nbricks + kXcd - 1) / kXcd * kXcd;
   g.tpa = best_tpa;
   g.kpart = ((c->kmax + best_tpa - 1) / best_tpa + 7) / 8 * 8;
