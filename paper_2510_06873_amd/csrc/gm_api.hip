@@ -545,14 +545,20 @@ double full_brick(double own, double spread) { return own + spread * std::sqrt(o
 // (passes 1-4) and S (pass 4) in the same few iterations instead of in most of
 // a disordered region's.  The margin is an eighth of the skin: wide enough for
 // nearly all pairs between two rebuilds, and a pair that comes in from outside
-// it costs time only.  At 1,024,000 atoms, half of them disordered: pass 4
-// 125 -> 117 us, passes 1-3 1-2 us each, for a build of 217 -> 246 us; at 16,632
-// in FP64 19/14/15.5/16.6 -> 18/13.5/14.5/15.4.  Where a row is copied out it is
-// put back into slot order.
+// it costs time only.  Where a row is copied out it is put back into slot order.
+// The rebuild pays for it, and in FP32 the more the larger the system.  Step and
+// rebuild without and with it (us): FP64, 16,632 atoms 64.5 + 64.2 and 61.9 +
+// 64.9, 53,040 atoms 136.2 + 88.0 and 127.4 + 89.9; FP32, 96,000 atoms 66.0 +
+// 99.9 and 64.5 + 103.3, 262,144 atoms 141.6 + 133.8 and 138.3 + 138.7, which one or
+// two steps repay; 524,288 atoms 226.1 + 185.1 and 220.2 + 209.6, 1,024,000 atoms
+// 417.5 + 292.8 and 411.6 + 334.0, which take four and seven, so there rows stay
+// in slot order.  (All half melted; a crystal without pairs in the shell pays 1-3%
+// of a rebuild below that size.)
+constexpr int64_t kShellAtoms = 1 << 18;
 void shell_bits(const gm_ctx* c, BrickGeom& g) {
   g.shell_lo = 0x7f800000u;  // infinity: none
   g.shell_span = 0;
-  if (!c->has_q6) return;
+  if (!c->has_q6 || (!c->fp64 && c->n > kShellAtoms)) return;
   const double m = 0.125 * c->p.skin, lo = c->p.r_c - c->p.taper - m, hi = c->p.r_c + m;
   const float lo2 = lo > 0.0 ? (float)(lo * lo) : 0.0f, hi2 = (float)(hi * hi);
   uint32_t hb;
@@ -580,6 +586,12 @@ void shell_bits(const gm_ctx* c, BrickGeom& g) {
 // coordination in FP32 and 7.2% (32%) in FP64, and above the fastest batch by 31,
 // 14, 7 and 11%; the shape whose atoms best fill a workgroup's lanes is above
 // them by 9.6, 13, 47 and 54% alone and by 26, 22, 14 and 18% in batches.
+// A system of many sets of workgroups fills the chip like a batch, whose
+// estimate then serves alone: of six systems of 864,000 to 2,400,000 atoms it is
+// 0.7% above the fastest shape (mean; 2% worst), the other one 2.7% (1,024,000
+// atoms 424 for 412 us a step); below, at 92,000 cells, the other one is exact
+// and it 2% above.
+constexpr int64_t kFullChipCells = 1 << 17;
 void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
   const int rec = c->fp64 ? slot_bytes<double>(c->has_q6) : slot_bytes<float>(c->has_q6);
   const int cap = c->lds_budget / rec;  // pass 1 of a q6 CV adds rank keys to its positions, still less than the rows
@@ -590,7 +602,7 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
   const ShapeCost& k = (c->has_q6 ? kCostQ6 : kCostCoord)[c->fp64 ? 1 : 0];
   const double list = 4.0 / 3.0 * M_PI * c->r_list * c->r_list * c->r_list * (double)c->n /
                       (c->box[0] * c->box[1] * c->box[2]);  // atoms of a mean list
-  const bool fixed = c->p.brick[0] > 0;
+  const bool fixed = c->p.brick[0] > 0, full_chip = (int64_t)nc[0] * nc[1] * nc[2] > kFullChipCells;
   for (int bx = 1; bx <= kMaxBrick && bx <= nc[0]; bx++)
     for (int by = 1; by <= kMaxBrick && by <= nc[1]; by++)
       for (int bz = 1; bz <= kMaxBrick && bz <= nc[2]; bz++) {
@@ -623,7 +635,7 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
           const double batched = k.b_base + k.b_halo * staged + k.b_atom * (double)c->n +
                                  bricks * (2.0 / wg * (k.b_walk * rounds * walk + k.b_brick) +
                                            waves * (k.b_wwalk * walk + k.b_wave));
-          const double cost = (c->has_q6 ? alone * alone * std::sqrt(alone) : alone) * batched;
+          const double cost = (full_chip ? 1.0 : c->has_q6 ? alone * alone * std::sqrt(alone) : alone) * batched;
           if (best_cost < 0.0 || cost < best_cost) {
             best_cost = cost;
             best[0] = bx;

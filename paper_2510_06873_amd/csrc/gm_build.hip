@@ -469,7 +469,7 @@ __global__ __launch_bounds__(kBlock) void k_fill_gather(const int32_t* __restric
 // (8 lanes per atom testing 8 candidates of one run at a time, each entry
 // stored by itself): 1,024,000 atoms q6 223 -> 190 us, 108,000 atoms at r_c 6
 // 127 -> 92, 96,000 q6 60 -> 51, 864 atoms at r_c 6 66 -> 21 (without the shell's
-// pairs first, which cost a q6 build a fifth: see shell_bits).
+// pairs first, which cost a q6 build up to a sixth: see shell_bits).
 //
 // Slots in cells across a periodic face are staged as the image beside the
 // brick (slot_image), so that every test is a plain difference: a candidate
@@ -1025,7 +1025,7 @@ hipError_t launch_build_nbr(const vec4_t<T>* pos_s, const CellGeom& cg, const Br
                             hipStream_t st) {
   const size_t lds = build_lds_bytes(g, kmax);
   const unsigned grid = (unsigned)((int64_t)g.blocks * g.build_split);
-  // lists without a shell (the coordination) in a variant without its tests:
+  // lists without a shell (the coordination, large q6 systems) in a variant without its tests:
   // 108,000 atoms 97 -> 91 us
   auto launch = [&](auto kernel) {
     kernel<<<grid, (unsigned)g.build_threads, lds, st>>>(pos_s, cg, g, bi, rl2, nbr, kmax, cnt, err, stats);
