@@ -1613,8 +1613,9 @@ int gm_fes_hills(gm_ctx* c, const double* lo, const double* hi, const int32_t* n
   const BiasArgs b = make_bias(c, nullptr, 0);
   // The split sum wants a workspace; a captured stream (whose allocations
   // would belong to the graph) or a full device takes the direct sum.
+  const size_t bytes = fes_hills_scratch_doubles(b, nbins) * 8;
   double* part = nullptr;
-  if (capturing(c->stream) || dalloc(c->stream, &part, fes_hills_scratch_doubles(b, nbins) * 8) != GM_OK)
+  if (bytes && (capturing(c->stream) || dalloc(c->stream, &part, bytes) != GM_OK))
     return hip_rc(launch_fes_hills(b, lo, hi, nbins, scale, F_dev, c->stream));
   const hipError_t e = launch_fes_hills_split(b, lo, hi, nbins, scale, F_dev, part, c->stream);
   dfree(c->stream, part);

@@ -344,7 +344,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_fes_out(FesArgs a, int32_t nblk
 // point and hill bounds it (256 x 256 points, 20,000 hills: 4.44 ms).
 //
 // Otherwise the hills are split over workgroups that leave partial sums in a
-// workspace, summed in a fixed order by k_fes_hills_sum:
+// workspace, summed in a fixed order by k_fes_hills_sum.  The split is made for
+// the hill capacity; the workgroups that the present hills leave without any
+// write nothing, and their sums are not read (256 x 256 points, 100 hills of
+// 20,000: 33 us with all of them, now 16; the direct sum 32).  A grid that fills the chip unsplit writes F itself.
 //  * 1-D, k_fes_hills_line: the direct sum over the workgroup's share of the
 //    hills.  A 1-D grid alone fills a few workgroups (486 points: 2).
 //  * 2-D, k_fes_hills_grid: a hill is a product over the dimensions, so
@@ -387,11 +390,15 @@ __global__ __launch_bounds__(kSmallBlock) void k_fes_hills(BiasArgs b, double lo
   if (i < nbins) F[i] = -scale * v;
 }
 
-// The share of K hills that split `part` of `parts` sums: [*k0, *k1), whole
-// multiples of `step` hills apart from the last.
+// Hills per split of K over `parts`: whole multiples of `step`, but for the last.
+__device__ __forceinline__ int64_t hills_per_part(int64_t K, int32_t parts, int32_t step) {
+  return ((K + parts - 1) / parts + step - 1) / step * step;
+}
+
+// The share that split `part` sums: [*k0, *k1).
 __device__ __forceinline__ void hill_share(int64_t K, int32_t part, int32_t parts, int32_t step, int64_t* k0,
                                            int64_t* k1) {
-  const int64_t per = ((K + parts - 1) / parts + step - 1) / step * step;
+  const int64_t per = hills_per_part(K, parts, step);
   *k0 = part * per < K ? part * per : K;
   *k1 = *k0 + per < K ? *k0 + per : K;
 }
@@ -405,7 +412,8 @@ __device__ __forceinline__ double hill_factor(double g, double c, double period,
   return exp(-(x * x * inv2s2));
 }
 
-__global__ __launch_bounds__(kSmallBlock) void k_fes_hills_line(BiasArgs b, double lo, double w, int32_t nb,
+// scale: 1, or -scale of F where the one split writes it.
+__global__ __launch_bounds__(kSmallBlock) void k_fes_hills_line(BiasArgs b, double lo, double w, int32_t nb, double scale,
                                                                 double* __restrict__ part) {
   __shared__ double tc[kHillTile], th[kHillTile];
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -413,6 +421,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_fes_hills_line(BiasArgs b, doub
   const double period = b.period[0], ip = period > 0.0 ? 1.0 / period : 0.0, inv = b.inv2s2[0];
   int64_t k0, k1;
   hill_share(*b.count, (int32_t)blockIdx.y, (int32_t)gridDim.y, 1, &k0, &k1);
+  if (k0 == k1 && gridDim.y > 1) return;  // not read
   double v = 0.0;
   for (int64_t t0 = k0; t0 < k1; t0 += kHillTile) {
     const int32_t n = (int32_t)(k1 - t0 < kHillTile ? k1 - t0 : kHillTile);
@@ -424,7 +433,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_fes_hills_line(BiasArgs b, doub
     __syncthreads();
     for (int32_t q = 0; q < n; q++) v += th[q] * hill_factor(g, tc[q], period, ip, inv);
   }
-  if (i < nb) part[(int64_t)blockIdx.y * nb + i] = v;
+  if (i < nb) part[(int64_t)blockIdx.y * nb + i] = scale * v;
 }
 
 // The 2-D product on the FP64 matrix instruction.  A workgroup of 8 waves
@@ -443,7 +452,7 @@ constexpr int kGridTile = 128, kGridHills = 8, kGridThreads = 512, kGridRow = kG
 using dbl4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
 
 __global__ __launch_bounds__(kGridThreads) void k_fes_hills_grid(BiasArgs b, double lo0, double lo1, double w0,
-                                                                 double w1, int32_t nb0, int32_t nb1,
+                                                                 double w1, int32_t nb0, int32_t nb1, double scale,
                                                                  double* __restrict__ part) {
   __shared__ double tab[2][2][kGridHills][kGridRow];  // [half][dimension][hill][point]
   const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -451,6 +460,7 @@ __global__ __launch_bounds__(kGridThreads) void k_fes_hills_grid(BiasArgs b, dou
   const int32_t r0 = (int32_t)(blockIdx.x % tiles0) * kGridTile, c0 = (int32_t)(blockIdx.x / tiles0) * kGridTile;
   int64_t k0, k1;
   hill_share(*b.count, (int32_t)blockIdx.y, (int32_t)gridDim.y, kGridHills, &k0, &k1);
+  if (k0 == k1 && gridDim.y > 1) return;  // not read
   // table entries of this thread: dimension d, point p of it (both fixed), hills hq, hq + 2, ...
   const int d = (t >> 7) & 1, p = t & (kGridTile - 1), hq = t >> 8;
   const double g = d ? lo1 + ((c0 + p) + 0.5) * w1 : lo0 + ((r0 + p) + 0.5) * w0;
@@ -512,18 +522,23 @@ __global__ __launch_bounds__(kGridThreads) void k_fes_hills_grid(BiasArgs b, dou
 #pragma unroll
       for (int r = 0; r < 4; r++) {
         const int32_t x = r0 + w0p + 16 * j + l16, y = c0 + w1p + 16 * i + lk + 4 * r;
-        if (x < nb0 && y < nb1) out[x + (int64_t)y * nb0] = acc[i][j][r];
+        if (x < nb0 && y < nb1) out[x + (int64_t)y * nb0] = scale * acc[i][j][r];
       }
 }
 
-// F = -scale times the partial sums, added in the order of the splits.
-__global__ __launch_bounds__(kSmallBlock) void k_fes_hills_sum(const double* __restrict__ part, int32_t nbins,
-                                                               int32_t parts, double scale, double* __restrict__ F) {
+// F = -scale times the partial sums of the splits that have hills, added in
+// their order.
+__global__ __launch_bounds__(kSmallBlock) void k_fes_hills_sum(const double* __restrict__ part,
+                                                               const int64_t* __restrict__ count, int32_t nbins,
+                                                               int32_t parts, int32_t step, double scale,
+                                                               double* __restrict__ F) {
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nbins) return;
+  const int64_t K = *count, per = hills_per_part(K, parts, step);
+  const int32_t live = K > 0 ? (int32_t)((K + per - 1) / per) : 0;
   double v = 0.0;
 #pragma unroll 8
-  for (int32_t p = 0; p < parts; p++) v += part[(int64_t)p * nbins + i];
+  for (int32_t p = 0; p < live; p++) v += part[(int64_t)p * nbins + i];
   F[i] = -scale * v;
 }
 
@@ -691,24 +706,28 @@ static int32_t fes_hills_parts(const BiasArgs& b, const int32_t* nb) {
 }
 
 size_t fes_hills_scratch_doubles(const BiasArgs& b, const int32_t* nb) {
-  return (size_t)fes_hills_parts(b, nb) * nb[0] * (b.dims > 1 ? nb[1] : 1);
+  const int32_t parts = fes_hills_parts(b, nb);
+  return parts > 1 ? (size_t)parts * nb[0] * (b.dims > 1 ? nb[1] : 1) : 0;
 }
 
 hipError_t launch_fes_hills_split(const BiasArgs& b, const double* lo, const double* hi, const int32_t* nb, double scale,
                                   double* F, double* part, hipStream_t st) {
-  const int32_t parts = fes_hills_parts(b, nb);
-  const double w0 = (hi[0] - lo[0]) / nb[0];
+  const int32_t parts = fes_hills_parts(b, nb), step = b.dims > 1 ? kGridHills : 1;
+  const double w0 = (hi[0] - lo[0]) / nb[0], f = parts > 1 ? 1.0 : -scale;
+  double* out = parts > 1 ? part : F;
   int32_t nbins = nb[0];
   if (b.dims > 1) {
     const unsigned tiles = (unsigned)(((nb[0] + kGridTile - 1) / kGridTile) * ((nb[1] + kGridTile - 1) / kGridTile));
     nbins *= nb[1];
     k_fes_hills_grid<<<dim3(tiles, (unsigned)parts), kGridThreads, 0, st>>>(b, lo[0], lo[1], w0, (hi[1] - lo[1]) / nb[1],
-                                                                            nb[0], nb[1], part);
+                                                                            nb[0], nb[1], f, out);
   } else {
     k_fes_hills_line<<<dim3(grid_for(nb[0], kSmallBlock, 1 << 20), (unsigned)parts), kSmallBlock, 0, st>>>(b, lo[0], w0,
-                                                                                                        nb[0], part);
+                                                                                                        nb[0], f, out);
   }
-  k_fes_hills_sum<<<grid_for(nbins, kSmallBlock, 1 << 20), kSmallBlock, 0, st>>>(part, nbins, parts, scale, F);
+  if (parts > 1)
+    k_fes_hills_sum<<<grid_for(nbins, kSmallBlock, 1 << 20), kSmallBlock, 0, st>>>(part, b.count, nbins, parts, step,
+                                                                                  scale, F);
   return hipGetLastError();
 }
 

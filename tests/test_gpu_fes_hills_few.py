@@ -1,0 +1,34 @@
+"""The free energy from fewer hills than the context has room for (splits that have none) and on grids of
+one split, against the FP64 oracle, after a call whose partial sums a later one
+must not read.  Tolerance as for the split sum: 1e-12 of the largest value."""
+import math
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nb", [[70], [131073], [1 << 18], [130, 40], [400, 1], [1500, 2200]])
+def test_hills_below_the_capacity(orc, nb):
+    from paper_2510_06873_amd import CV_EXTERNAL, Params, Pipeline
+
+    dims = len(nb)
+    lo, hi, sigma = [-math.pi] * dims, [math.pi] * dims, [0.35, 0.2][:dims]
+    pipe = Pipeline(0, Params(cv_kind=CV_EXTERNAL, external_dims=dims, sigma=sigma, period=[2 * math.pi] * dims, w0=1.2,
+                              gamma=10.0, kBT=W.KBT_KJMOL, hill_capacity=4096))
+    few = 40 if int(np.prod(nb)) > 1 << 20 else 1500
+    for K in (few, 9, 1, 0, 33, 8):
+        cen = W.hill_centres(max(K, 1), lo, hi, seed=70 + K)[:K].reshape(K, dims)
+        hts = np.random.default_rng(71).uniform(0.2, 1.2, K)
+        pipe.hills_set(cen, hts)
+        F = pipe.fes_hills(lo, hi, nb).cpu().numpy()
+        if K == 0:
+            assert np.array_equal(F, np.zeros_like(F))
+            continue
+        Fr = orc.fes_hills(cen, hts, sigma, lo, hi, nb, gamma=10.0, period=[2 * math.pi] * dims)
+        assert np.max(np.abs(F - Fr)) <= 1e-12 * np.abs(Fr).max(), K
+    pipe.close()
