@@ -340,8 +340,9 @@ __global__ __launch_bounds__(kSmallBlock) void k_fes_out(FesArgs a, int32_t nblk
 // k_fes_hills is the direct sum, every hill in index order at every grid
 // point, hills through LDS in tiles (one coalesced read of each hill per
 // workgroup instead of one per wave).  It needs no workspace and serves the
-// calls that must not allocate (a captured stream); an FP64 exponential per
-// point and hill bounds it (256 x 256 points, 20,000 hills: 4.44 ms).
+// calls that must not allocate (a captured stream) and 2-D grids too thin for
+// the product's tiles (fes_hills_direct); an FP64 exponential per point and hill
+// bounds it (256 x 256 points, 20,000 hills: 4.44 ms).
 //
 // Otherwise the hills are split over workgroups that leave partial sums in a
 // workspace, summed in a fixed order by k_fes_hills_sum.  The split is made for
@@ -705,13 +706,27 @@ static int32_t fes_hills_parts(const BiasArgs& b, const int32_t* nb) {
   return (int32_t)(p < 1 ? 1 : p);
 }
 
+// 2-D grids that the direct sum evaluates in less time than the product its
+// tiles, which are mostly padding where an axis has one or two points.  Per hill
+// a tile takes the chip 0.75 ns, the direct sum 235 to 310 ns up to 131,072 points
+// and 2 ps a point beyond.  2,000 hills: 65,536 x 1 points 470 us (product 797),
+// 262,144 x 2 1.88 ms (3.04), 65,536 x 3 831 us (800, taken), 32,768 x 2 463 (405).
+static bool fes_hills_direct(const BiasArgs& b, const int32_t* nb) {
+  if (b.dims == 1) return false;
+  const int64_t tiles = (int64_t)((nb[0] + kGridTile - 1) / kGridTile) * ((nb[1] + kGridTile - 1) / kGridTile);
+  const int64_t points = (int64_t)nb[0] * nb[1];
+  return tiles * 131072 > 350 * (points > 131072 ? points : 131072);
+}
+
 size_t fes_hills_scratch_doubles(const BiasArgs& b, const int32_t* nb) {
+  if (fes_hills_direct(b, nb)) return 0;
   const int32_t parts = fes_hills_parts(b, nb);
   return parts > 1 ? (size_t)parts * nb[0] * (b.dims > 1 ? nb[1] : 1) : 0;
 }
 
 hipError_t launch_fes_hills_split(const BiasArgs& b, const double* lo, const double* hi, const int32_t* nb, double scale,
                                   double* F, double* part, hipStream_t st) {
+  if (fes_hills_direct(b, nb)) return launch_fes_hills(b, lo, hi, nb, scale, F, st);
   const int32_t parts = fes_hills_parts(b, nb), step = b.dims > 1 ? kGridHills : 1;
   const double w0 = (hi[0] - lo[0]) / nb[0], f = parts > 1 ? 1.0 : -scale;
   double* out = parts > 1 ? part : F;

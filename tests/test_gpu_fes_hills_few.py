@@ -1,5 +1,5 @@
-"""The free energy from fewer hills than the context has room for (splits that have none) and on grids of
-one split, against the FP64 oracle, after a call whose partial sums a later one
+"""The free energy from fewer hills than the context has room for (splits that have none), on grids on both sides of
+the line to the direct sum and of one split, against the FP64 oracle, after a call whose partial sums a later one
 must not read.  Tolerance as for the split sum: 1e-12 of the largest value."""
 import math
 
@@ -12,7 +12,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("nb", [[70], [131073], [1 << 18], [130, 40], [400, 1], [1500, 2200]])
+@pytest.mark.parametrize("nb", [[70], [131073], [1 << 18], [130, 40], [400, 1], [45057, 1], [1, 44800], [1500, 2200]])
 def test_hills_below_the_capacity(orc, nb):
     from paper_2510_06873_amd import CV_EXTERNAL, Params, Pipeline
 
