@@ -18,8 +18,10 @@ constexpr int kBiasBlock = 1024;        // threads of a block that sums every hi
 constexpr int kBiasOne = 8192;          // hills up to which one block sums them
 // Systems up to this size (2 MiB of positions, which fit beside other data in
 // each XCD's L2) have no separate gather: pass 1 stages its halo from the
-// caller's array.  A launch of 2-4 us and 3.3 us of host time, against halos
-// read at random: at 96,000 atoms the step of 83 us became 81.
+// caller's array: a launch of 2-4 us and 3.3 us of host time, against halos read
+// at random.  Steps of 50 systems of 896 to 118,800 atoms: 2-7% less for the q6
+// CVs, 4-18% for the coordination; at 142,968 to 267,840 atoms 0-2% (4% for the
+// coordination) for a rebuild of 1-2% more, and nothing from 524,288.
 constexpr int64_t kFuseGather = 131072;
 // Grids up to this many workgroups (all resident at once) finish the CV's sum in
 // the pass that makes its partials; in larger ones the wait for the ticket at
