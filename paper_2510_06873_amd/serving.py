@@ -101,15 +101,17 @@ def device_bytes(req: Request) -> int:
     t = 8 if p.precision == 1 else 4
     kmax = (max(p.max_neighbors, 4) + 3) // 4 * 4
     per_atom = 16 + 16 * t                      # caller positions + forces
-    per_atom += 4 * 7 + 2 * 2 * kmax            # cell, perm, owned tables, counts, neighbour + cutoff rows
+    per_atom += 4 * 7 + 2 * 2 * (kmax + 32)     # cell, perm, owned tables, counts, neighbour + cutoff rows
+    per_atom += 16 + 16                         # cutoff counts of four parts, atoms by rank
     per_atom += 4 * t + 2 * t                   # sorted positions, bond count, coordination
+    if p.cv_kind != 2:
+        per_atom += 4 * t                       # the coordination's gradient
     if p.cv_kind != 1:
         per_atom += 16 * t * 2 + 3 * t          # q-hat and adjoint rows, |Q|, c', sum f
-    per_atom += 4 * 8                           # halo slot table (bounded by 8 halo copies per atom)
-    if n <= 1 << 17:                            # the halo slots' atoms beside their ranks
-        per_atom += 4 * 8
-    if n < 1 << 16:                             # small bricks: up to 27 copies, and their tables
-        per_atom += 2 * 4 * 19 + 80
+    # halo slots: an atom is in up to 27 halos (bricks of one cell, or a last brick of one), their ranks and, up to
+    # 131,072 atoms, the atoms themselves
+    per_atom += 27 * 4 * (2 if n <= 1 << 17 else 1)
+    per_atom += 128 if n < 1 << 16 else 40      # the tables of small bricks
     hills = p.hill_capacity * (p.dims + 1) * 8
     return int(n * per_atom + hills + (1 << 20))
 
