@@ -337,7 +337,7 @@ int gm_batch_deposit(gm_batch* batch);
 /* The same for some walkers only (each deposit as gm_deposit_hill would make
  * it, bitwise): which = host array of count distinct member indices (the
  * order of the last create or update); one launch per 64 walkers, two where a
- * hill capacity is above 8,192.
+ * hill capacity is above 4,096.
  * GM_ERR_INVALID_ARG for an index out of range or repeated, GM_ERR_STATE for a
  * walker not yet stepped (no CV value to deposit at). */
 int gm_batch_deposit_some(gm_batch* batch, const int32_t* which, int32_t count);

@@ -14,34 +14,36 @@ __device__ __forceinline__ double cv_delta(double s, double c, double period) {
   return period > 0.0 ? x - period * rint(x / period) : x;
 }
 
-// Fixed-order block sums of three values at once, valid in thread 0: wave sums,
-// then the first wave adds the waves' sums.  All threads call; lds holds
-// 3 kBiasBlock / 64 doubles and is free again when the block passes its next
-// barrier.
-__device__ __forceinline__ void block_sum3(double v[3], double (*lds)[3]) {
+// Fixed-order block sums of N values at once, valid in thread 0: wave sums, then
+// the first wave adds the waves' sums.  All threads call; lds holds N kBiasBlock /
+// 64 doubles and is free again when the block passes its next barrier.
+template <int N>
+__device__ __forceinline__ void block_sums(double (&v)[N], double (*lds)[3]) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, waves = (int)(blockDim.x >> 6);
 #pragma unroll
-  for (int q = 0; q < 3; q++) {
+  for (int q = 0; q < N; q++) {
     v[q] = wave_sum(v[q]);
     if (lane == 0) lds[w][q] = v[q];
   }
   __syncthreads();
   if (w == 0)
 #pragma unroll
-    for (int q = 0; q < 3; q++) {
+    for (int q = 0; q < N; q++) {
       v[q] = lane < waves ? lds[lane][q] : 0.0;
 #pragma unroll
       for (int o = 8; o > 0; o >>= 1) v[q] += __shfl_down(v[q], o, 64);
     }
 }
 
-// V and dV/ds, or the deposit of one hill (thread 0, once per evaluation).
-__device__ __forceinline__ void bias_result(const BiasArgs& a, int64_t K, const double v[3]) {
+// V and dV/ds (v: V, then dV/ds), or the deposit of one hill (thread 0, once per
+// evaluation).
+template <int DIMS>
+__device__ __forceinline__ void bias_result(const BiasArgs& a, int64_t K, const double (&v)[1 + DIMS]) {
   if (!isfinite(v[0])) atomicOr(a.err, kErrNonFinite);
   if (a.deposit) {
     const double h = a.wt_scale == 0.0 ? a.w0 : a.w0 * exp(-v[0] * a.wt_scale);
     if (K < a.capacity) {
-      for (int d = 0; d < a.dims; d++) a.centres[K * a.dims + d] = a.s[d];
+      for (int d = 0; d < DIMS; d++) a.centres[K * DIMS + d] = a.s[d];
       a.heights[K] = h;
       *a.count = K + 1;
     } else {
@@ -49,77 +51,99 @@ __device__ __forceinline__ void bias_result(const BiasArgs& a, int64_t K, const 
     }
   } else {
     if (a.V_out) a.V_out[0] = v[0];
-    if (a.dV_out) {
-      a.dV_out[0] = v[1];
-      if (a.dims > 1) a.dV_out[1] = v[2];
-    }
+    if (a.dV_out)
+      for (int d = 0; d < DIMS; d++) a.dV_out[d] = v[1 + d];
   }
 }
 
 // The sum over the hills.  One workgroup of 1,024 threads sums up to kBiasOne
 // hills and is done; more hills are shared by workgroups whose partial sums a
-// second launch adds in their order.  Latency bounds both: 2,000 hills 3.9 +
-// 2.4 us in two launches, 4.0 in one; 5,000 2-D hills 4.0 + 2.9 and 5.8.  At
-// 10,000 one workgroup, or a last-to-finish workgroup that adds the partials in
-// the same launch, takes longer (7.8 us) than the two launches (6.4).
-__device__ __forceinline__ void bias_body(const BiasArgs& a, int32_t blk, int32_t nblk) {
-  static_assert(kBiasBlock / 64 <= 16, "block_sum3 adds 16 waves");
+// second launch adds in their order.  Latency bounds both (replayed from a graph):
+// 4,000 hills 4.7 us in one launch and 5.4 in two (2-D: 5.6 and 6.2), 6,000 hills
+// 6.6 and 5.4 (7.7 and 6.3).  A last-to-finish workgroup that adds the partials
+// in the same launch takes longer than the second launch (7.8 us and 6.4).
+template <int DIMS>
+__device__ __forceinline__ void bias_sum(const BiasArgs& a, int32_t blk, int32_t nblk) {
+  static_assert(kBiasBlock / 64 <= 16, "block_sums adds 16 waves");
   __shared__ double red[kBiasBlock / 64][3];
   const int64_t K = *a.count;
-  double s[2] = {a.s[0], a.dims > 1 ? a.s[1] : 0.0};
-  double v[3] = {0.0, 0.0, 0.0};  // V, dV/ds
-  // up to 4 hills per thread and round, loaded as one batch (the last hill in
-  // the place of those past the end, which add zero); several workgroups use
-  // kBlock threads each, however many a batched launch gives them
-  const int32_t threads = nblk > 1 ? kBlock : kBiasBlock;
-  const int64_t stride = (int64_t)nblk * threads;
-  const int64_t mine = (int32_t)threadIdx.x < threads ? (int64_t)blk * threads + threadIdx.x : K;
-  for (int64_t k0 = mine; k0 < K; k0 += 4 * stride) {
-    double c0[4], c1[4], h[4];
+  double s[DIMS], v[1 + DIMS] = {};
 #pragma unroll
-    for (int u = 0; u < 4; u++) {
-      const int64_t k = k0 + u * stride < K ? k0 + u * stride : K - 1;
-      c0[u] = a.centres[k * a.dims];
-      c1[u] = a.dims > 1 ? a.centres[k * a.dims + 1] : 0.0;
-      h[u] = a.heights[k];
+  for (int d = 0; d < DIMS; d++) s[d] = a.s[d];
+  auto add = [&](const double (&c)[DIMS], double h) {
+    double x[DIMS], arg = 0.0;
+#pragma unroll
+    for (int d = 0; d < DIMS; d++) {
+      x[d] = cv_delta(s[d], c[d], a.period[d]);
+      arg += x[d] * x[d] * a.inv2s2[d];
     }
+    const double e = h * exp(-arg);
+    v[0] += e;
 #pragma unroll
-    for (int u = 0; u < 4; u++) {
-      if (k0 + u * stride >= K) break;
-      const double x0 = cv_delta(s[0], c0[u], a.period[0]);
-      double arg = x0 * x0 * a.inv2s2[0];
-      double x1 = 0.0;
-      if (a.dims > 1) {
-        x1 = cv_delta(s[1], c1[u], a.period[1]);
-        arg += x1 * x1 * a.inv2s2[1];
+    for (int d = 0; d < DIMS; d++) v[1 + d] -= e * x[d] * a.invs2[d];
+  };
+  if (nblk == 1) {
+    // up to 4 hills per thread and round, loaded as one batch (the last hill in
+    // the place of those past the end, which are not added)
+    for (int64_t k0 = threadIdx.x; k0 < K; k0 += 4 * kBiasBlock) {
+      double c[4][DIMS], h[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const int64_t k = k0 + u * kBiasBlock < K ? k0 + u * kBiasBlock : K - 1;
+#pragma unroll
+        for (int d = 0; d < DIMS; d++) c[u][d] = a.centres[k * DIMS + d];
+        h[u] = a.heights[k];
       }
-      const double e = h[u] * exp(-arg);
-      v[0] += e;
-      v[1] -= e * x0 * a.invs2[0];
-      v[2] -= e * x1 * a.invs2[1];
+#pragma unroll
+      for (int u = 0; u < 4; u++)
+        if (k0 + u * kBiasBlock < K) add(c[u], h[u]);
+    }
+  } else {
+    // kBlock threads each, however many a batched launch gives them
+    const int64_t stride = (int64_t)nblk * kBlock;
+    for (int64_t k = threadIdx.x < kBlock ? (int64_t)blk * kBlock + threadIdx.x : K; k < K; k += stride) {
+      double c[DIMS];
+#pragma unroll
+      for (int d = 0; d < DIMS; d++) c[d] = a.centres[k * DIMS + d];
+      add(c, a.heights[k]);
     }
   }
-  block_sum3(v, red);
+  block_sums(v, red);
   if (threadIdx.x != 0) return;
   if (nblk == 1) {
-    bias_result(a, K, v);
+    bias_result<DIMS>(a, K, v);
   } else {
 #pragma unroll
-    for (int q = 0; q < 3; q++) a.part[blk * 3 + q] = v[q];
+    for (int q = 0; q <= DIMS; q++) a.part[blk * 3 + q] = v[q];
   }
 }
 
+__device__ __forceinline__ void bias_body(const BiasArgs& a, int32_t blk, int32_t nblk) {
+  if (a.dims > 1)
+    bias_sum<2>(a, blk, nblk);
+  else
+    bias_sum<1>(a, blk, nblk);
+}
+
 // Fixed-order sum of the partials of an evaluation by more than one workgroup.
-__device__ __forceinline__ void bias_finish_body(const BiasArgs& a, int32_t nblk) {
+template <int DIMS>
+__device__ __forceinline__ void bias_finish_sum(const BiasArgs& a, int32_t nblk) {
   __shared__ double red[kBlock / 64][3];
-  if (nblk == 1) return;
   const int64_t K = *a.count;
-  double v[3] = {0.0, 0.0, 0.0};
+  double v[1 + DIMS] = {};
   for (int32_t i = threadIdx.x; i < nblk; i += blockDim.x)
 #pragma unroll
-    for (int q = 0; q < 3; q++) v[q] += a.part[i * 3 + q];
-  block_sum3(v, red);
-  if (threadIdx.x == 0) bias_result(a, K, v);
+    for (int q = 0; q <= DIMS; q++) v[q] += a.part[i * 3 + q];
+  block_sums(v, red);
+  if (threadIdx.x == 0) bias_result<DIMS>(a, K, v);
+}
+
+__device__ __forceinline__ void bias_finish_body(const BiasArgs& a, int32_t nblk) {
+  if (nblk == 1) return;
+  if (a.dims > 1)
+    bias_finish_sum<2>(a, nblk);
+  else
+    bias_finish_sum<1>(a, nblk);
 }
 
 __global__ __launch_bounds__(kBiasBlock) void k_bias(BiasArgs a) { bias_body(a, blockIdx.x, gridDim.x); }

@@ -15,7 +15,7 @@ constexpr int kBuildAtoms = 4;          // atoms per wave below which a neighbou
 constexpr int kBuildFillBlocks = 1024;  // workgroups a neighbour build aims for (4 per CU)
 constexpr int kBuildMaxSplit = 32;      // most workgroups sharing one brick in the build
 constexpr int kBiasBlock = 1024;        // threads of a block that sums every hill alone
-constexpr int kBiasOne = 8192;          // hills up to which one block sums them
+constexpr int kBiasOne = 4096;          // hills up to which one block sums them
 // Systems up to this size (2 MiB of positions, which fit beside other data in
 // each XCD's L2) have no separate gather: pass 1 stages its halo from the
 // caller's array: a launch of 2-4 us and 3.3 us of host time, against halos read
