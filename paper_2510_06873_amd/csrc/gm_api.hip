@@ -69,6 +69,8 @@ struct gm_ctx {
   uint64_t serial = 0;  // unique per context created in this process
   int lds_budget = 0;   // bytes of dynamic LDS for the staged halo (negative: too few for the static arrays)
   int lds_limit = 0;    // bytes of dynamic LDS a kernel may have
+  double shape_box[3] = {0, 0, 0};  // the box that shape and shape_tpa (cells of a brick, lanes per atom) were chosen for
+  int shape[3] = {1, 1, 1}, shape_tpa = 1;
   YCoef<float> ycf;
   YCoef<double> ycd;
 };
@@ -502,7 +504,9 @@ CvArgs<T> make_args(gm_ctx* c) {
 
 // Estimated times of a brick shape, for the choice below (fitted, see there).
 struct ShapeCost {
-  double spread[3];  // atoms of a full brick above the mean, in square roots of it: three equally likely cases
+  // atoms of a full brick above the mean, in square roots of it, three equally
+  // likely cases: lanes that the mean just fills take a second round in some bricks
+  double spread[3];
   // one step of one system (us): what it takes in any case, per atom of the
   // longest lane's walk and per round of a workgroup's lanes (both for each set
   // of workgroups that are resident together), and on the CU with the most
@@ -536,9 +540,11 @@ int cu_workgroups(const gm_ctx* c, double halo, int rec) {
   return 2;
 }
 
-// Atoms of a full brick where the mean is `own`: a workgroup whose lanes the
-// mean just fills takes a second round in some of its bricks.
-double full_brick(double own, double spread) { return own + spread * std::sqrt(own); }
+// The next whole number up, of a positive one (std::ceil is a library call here).
+double round_up(double x) {
+  const double w = (double)(int64_t)x;
+  return w < x ? w + 1.0 : w;
+}
 
 // The pairs of a q6 list that are, or by a small move come to be, in the taper
 // shell are listed first, so that the lanes of a wave meet the taper's series
@@ -592,12 +598,12 @@ void shell_bits(const gm_ctx* c, BrickGeom& g) {
 // atoms 424 for 412 us a step); below, at 92,000 cells, the other one is exact
 // and it 2% above.
 constexpr int64_t kFullChipCells = 1 << 17;
-void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
+void choose_shape(const gm_ctx* c, const int32_t nc[3], int best[3], int& best_tpa) {
   const int rec = c->fp64 ? slot_bytes<double>(c->has_q6) : slot_bytes<float>(c->has_q6);
   const int cap = c->lds_budget / rec;  // pass 1 of a q6 CV adds rank keys to its positions, still less than the rows
   const int blk = c->fp64 ? BrickBlock<double>::value : BrickBlock<float>::value;
   const double rho = (double)c->n / ((double)nc[0] * nc[1] * nc[2]);
-  int best[3] = {1, 1, 1}, best_tpa = 1;
+  best[0] = best[1] = best[2] = best_tpa = 1;
   double best_cost = -1.0;
   const ShapeCost& k = (c->has_q6 ? kCostQ6 : kCostCoord)[c->fp64 ? 1 : 0];
   const double list = 4.0 / 3.0 * M_PI * c->r_list * c->r_list * c->r_list * (double)c->n /
@@ -614,20 +620,19 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
         const double own = (double)bx * by * bz * rho;
         if (!fixed && halo * 1.05 > cap) continue;
         // pass 1 ranks at most a workgroup of atoms (the others keep cell order)
-        if (!fixed && c->has_q6 && full_brick(own, 1.5) > blk) continue;
-        const double nb[3] = {std::ceil((double)nc[0] / bx), std::ceil((double)nc[1] / by), std::ceil((double)nc[2] / bz)};
-        const double bricks = nb[0] * nb[1] * nb[2];
-        const double staged = (nc[0] + 2 * nb[0]) * (nc[1] + 2 * nb[1]) * (nc[2] + 2 * nb[2]) * rho;
-        const double full[3] = {full_brick(own, k.spread[0]), full_brick(own, k.spread[1]), full_brick(own, k.spread[2])};
+        if (!fixed && c->has_q6 && own + 1.5 * std::sqrt(own) > blk) continue;
+        const int nb[3] = {(nc[0] + bx - 1) / bx, (nc[1] + by - 1) / by, (nc[2] + bz - 1) / bz};
+        const double bricks = (double)nb[0] * nb[1] * nb[2];
+        const double staged = (double)(nc[0] + 2 * nb[0]) * (nc[1] + 2 * nb[1]) * (nc[2] + 2 * nb[2]) * rho;
         const int wg = cu_workgroups(c, halo, rec);
-        const double sets = std::ceil(bricks / (256.0 * wg));
+        const double sets = round_up(bricks / (256.0 * wg)), root = std::sqrt(own);
         // workgroups on the CU with the most of them (in many sets: on average,
         // and a half for the end)
-        const double most = bricks <= 512.0 ? std::ceil(bricks / 256.0) : bricks / 256.0 + 0.5;
+        const double most = bricks <= 512.0 ? round_up(bricks / 256.0) : bricks / 256.0 + 0.5;
         for (int tpa = 1; tpa <= 4; tpa *= 2) {
           if (c->p.tpa > 0 && tpa != c->p.tpa) continue;
           double rounds = 0.0;
-          for (double f : full) rounds += std::ceil(tpa * f / blk) / 3.0;
+          for (double f : k.spread) rounds += round_up(tpa * (own + f * root) / blk) / 3.0;
           const double walk = list / tpa;
           const double waves = (double)c->n / bricks * tpa / 64.0 + 0.5;  // of a mean brick
           const double alone = k.base + sets * rounds * (k.walk * walk + k.round) + k.atom * (double)c->n +
@@ -646,6 +651,19 @@ void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
         }
       }
   if (best_cost < 0.0 && c->p.tpa > 0) best_tpa = c->p.tpa;  // no brick fits the lanes: 1x1x1
+}
+
+void choose_bricks(gm_ctx* c, const int32_t nc[3]) {
+  // the shape depends on the box alone, which most rebuilds leave as it is
+  // (2 us of host time each, for every walker of a batched rebuild)
+  if (memcmp(c->shape_box, c->box, sizeof(c->box)) != 0) {
+    choose_shape(c, nc, c->shape, c->shape_tpa);
+    memcpy(c->shape_box, c->box, sizeof(c->box));
+  }
+  const int* best = c->shape;
+  const int best_tpa = c->shape_tpa, rec = c->fp64 ? slot_bytes<double>(c->has_q6) : slot_bytes<float>(c->has_q6);
+  const int cap = c->lds_budget / rec;
+  const double rho = (double)c->n / ((double)nc[0] * nc[1] * nc[2]);
   BrickGeom& g = c->bg;
   for (int a = 0; a < 3; a++) {
     g.nc[a] = nc[a];
