@@ -1794,17 +1794,10 @@ int batch_build(gm_batch* B, const int32_t* which, int32_t count, const double* 
     host.clear();
     return rc;
   };
-  // walkers built together fill the device with fewer workgroups per brick, each
-  // of which stages the brick's whole halo (98,784 atoms in 21 q6 walkers: the
-  // neighbour build 96 -> 51 us)
-  int64_t bricks = 0;
-  for (int32_t i = 0; i < count; i++) bricks += B->walkers[which[i]]->bg.nbricks;
-  const int32_t split = bricks > 0 ? (int32_t)((kBuildFillBlocks + bricks - 1) / bricks) : 1;
   for (int32_t i = 0; i < count; i++) {
     gm_ctx* c = B->walkers[which[i]];
     const float* pos4 = B->pos[which[i]];
-    BuildArgs a = build_args(c, pos4);
-    if (split < a.bg.build_split) a.bg.build_split = split;
+    const BuildArgs a = build_args(c, pos4);
     if (!build_batchable(a)) {
       GM_TRY(enqueue_build(c, pos4, st));
       continue;
