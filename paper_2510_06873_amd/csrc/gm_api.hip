@@ -555,12 +555,15 @@ double round_up(double x) {
 // The rebuild pays for it, and in FP32 the more the larger the system.  Step and
 // rebuild without and with it (us): FP64, 16,632 atoms 64.5 + 64.2 and 61.9 +
 // 64.9, 53,040 atoms 136.2 + 88.0 and 127.4 + 89.9; FP32, 96,000 atoms 66.0 +
-// 99.9 and 64.5 + 103.3, 262,144 atoms 141.6 + 133.8 and 138.3 + 138.7, which one or
-// two steps repay; 524,288 atoms 226.1 + 185.1 and 220.2 + 209.6, 1,024,000 atoms
-// 417.5 + 292.8 and 411.6 + 334.0, which take four and seven, so there rows stay
-// in slot order.  (All half melted; a crystal without pairs in the shell pays 1-3%
-// of a rebuild below that size.)
-constexpr int64_t kShellAtoms = 1 << 18;
+// 99.9 and 64.5 + 103.3, 262,144 atoms 141.6 + 133.8 and 138.3 + 138.7, 524,288
+// atoms 228.8 + 185 and 220.0 + 209, 1,024,000 atoms 417.4 + 301 and 408.8 + 347,
+// 2,400,000 atoms 1044.6 + 642 and 1024.3 + 748: repaid by one or two steps at
+// the small sizes and by three to six at the large ones.  (All half melted; of
+// the rebuild of a crystal without pairs in the shell it takes 1-3% at the small
+// sizes and 10-15% at the large ones.)  The line lies where a rebuild is still
+// faster than eight lanes per atom in slot order made it (228 us at 524,288 atoms
+// and 436 at 1,024,000, but 709 at 2,400,000); above it rows stay in slot order.
+constexpr int64_t kShellAtoms = 1 << 20;
 void shell_bits(const gm_ctx* c, BrickGeom& g) {
   g.shell_lo = 0x7f800000u;  // infinity: none
   g.shell_span = 0;

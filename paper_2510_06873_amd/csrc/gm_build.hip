@@ -1044,7 +1044,7 @@ hipError_t launch_build_nbr(const vec4_t<T>* pos_s, const CellGeom& cg, const Br
                             hipStream_t st) {
   const size_t lds = build_lds_bytes(g, kmax);
   const unsigned grid = (unsigned)((int64_t)g.blocks * g.build_split);
-  // lists without a shell (the coordination, large q6 systems) in a variant without its tests:
+  // lists without a shell (the coordination, the largest q6 systems) in a variant without its tests:
   // 108,000 atoms 97 -> 91 us
   auto launch = [&](auto kernel) {
     kernel<<<grid, (unsigned)g.build_threads, lds, st>>>(pos_s, cg, g, bi, rl2, nbr, kmax, cnt, err, stats);
