@@ -428,8 +428,9 @@ int gm_fes_reweight_noalloc(const double* s_dev, const double* V_dev, int64_t T,
  * (lo_d + (i_d + 1/2) w_d): F = -V (plain metadynamics) or
  * F = -gamma/(gamma - 1) V (well-tempered).  The hills are split over
  * workgroups and summed in a fixed order (the same bits from call to call),
- * with a workspace from the library's device memory; on a captured stream, or
- * where no workspace can be had, in index order without one.
+ * with a workspace from the library's device memory; on a captured stream, on
+ * 2-D grids of a point or two on one axis, or where no workspace can be had,
+ * in index order without one.
  * Same grid arguments and F_dev layout as gm_fes_reweight (dims = the
  * context's). */
 int gm_fes_hills(gm_ctx* ctx, const double* lo, const double* hi, const int32_t* nbins, double* F_dev);
