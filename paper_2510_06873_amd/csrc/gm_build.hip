@@ -464,12 +464,12 @@ __global__ __launch_bounds__(kBlock) void k_fill_gather(const int32_t* __restric
 // zeros behind each sub-row's last entry (the CV passes read whole pieces);
 // entry e of a row lives in sub-row e % tpa at index e / tpa.
 //
-// VALU issue bounds it at size (85 instructions per atom of a q6 list, busy
-// 0.72), the latency of staging and setting up below.  Against the form before
+// VALU issue bounds it at size (102 instructions per atom of a q6 list in slot
+// order, busy 0.87), the latency of staging and setting up below.  Against the form before
 // (8 lanes per atom testing 8 candidates of one run at a time, each entry
-// stored by itself): 1,024,000 atoms q6 223 -> 190 us, 108,000 atoms at r_c 6
+// stored by itself): 1,024,000 atoms q6 223 -> 198 us, 108,000 atoms at r_c 6
 // 127 -> 92, 96,000 q6 60 -> 51, 864 atoms at r_c 6 66 -> 21 (without the shell's
-// pairs first, which cost a q6 build up to a sixth: see shell_bits).
+// pairs first, which cost a q6 build up to a fifth: see shell_bits).
 //
 // Slots in cells across a periodic face are staged as the image beside the
 // brick (slot_image), so that every test is a plain difference: a candidate
